@@ -340,8 +340,8 @@ aim_status aim_rcs(aim_plan *plan, int32_t nrhs, const void *x, int32_t ntheta,
  * forbid it): the same sigma_theta_theta, with theta, phi and sigma_tt in
  * device memory (theta[ntheta], phi[nphi] radians; sigma_tt [nmesh][nrhs]
  * [ntheta][nphi], m^2) and x as for aim_rcs; asynchronous on hip_stream, on
- * the plan's device (else AIM_ERR_ARG). Each quadrature point's current is
- * formed inside the kernel, and the partial sums over point chunks live in a
+ * the plan's device (else AIM_ERR_ARG). Each triangle's current is formed
+ * inside the kernel, and the partial sums over triangle chunks live in a
  * fixed array of 1,048,576 complex doubles (16 MiB) that the library holds on
  * each GPU it runs on until the process ends: ntheta * nphi * nrhs above
  * that gives AIM_ERR_ARG. Every call on a GPU shares that GPU's array (each

@@ -3,20 +3,24 @@
 // The paper measures accuracy through the VV bistatic RCS over the sphere of
 // directions (Section 2.2, eq. 1). With J = sum_n I_n f_n, the radiation
 // vector is N(r_hat) = int J exp(+j k r_hat . r') dS' and, for a unit incident
-// field, sigma_tt = (k eta)^2 / (4 pi) |theta_hat . N|^2. Work-groups cover a
-// tile of directions and a chunk of the triangles' quadrature points; each
-// thread sums its points for the tile's directions, the work-group reduces,
-// and the chunks' partial sums are added in a fixed order.
+// field, sigma_tt = (k eta)^2 / (4 pi) |theta_hat . N|^2.
 //
-// Two ways to feed the points: aim_rcs first collapses the current onto the
-// 7 quadrature points of every triangle (positions and A w J in temporary
-// buffers); the allocation-free variant forms each point's position and
-// current inside the kernel from the mesh and the triangle -> basis table,
-// and keeps its partial sums in a fixed device array (below).
+// On a triangle with centroid c the current is J = g (r - c) + c0 with the
+// complex scalar g = sum_i s_i l_i I_i / (2A) over its basis functions and
+// c0 = sum_i s_i l_i I_i (c - v_i) / (2A), and the 7 points of the rule lie at
+// c + gamma (3 (v_i - c)) with gamma = 1/3 - a, 1/3 - b (and c itself). So
+//   theta_hat . N_T = A e^{j k r_hat . c} [(theta_hat . c0) S + g T / k],
+//   S = w_c + sum_{gamma, i} w e^{j gamma p_i},
+//   T = sum_{gamma, i} w gamma q_i e^{j gamma p_i},
+// p_i = 3 k r_hat . (v_i - c), q_i = 3 k theta_hat . (v_i - c): S, T and the
+// phase of c are shared by all right-hand sides, each of which then costs 14
+// multiply-adds per triangle and direction.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
 #include "aim_internal.h"
+#include "fft_core.h"
 #include "geom_device.h"
 
 namespace aim {
@@ -34,160 +38,294 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices] = {};
 
-// position and A w J of quadrature point p (tri = p / 7) of one right-hand side
-__device__ __forceinline__ void point_current(const int32_t *tris, const double *verts,
-                                              const double *area, const int32_t *tri_basis,
-                                              const double *len, const double2 *xr, int64_t t,
-                                              D3 *r, double2 *J) {
-  const int64_t tri = t / 7;
-  const int p = (int)(t - tri * 7);
-  D3 T[3];
-  for (int c = 0; c < 3; ++c) T[c] = vtx(verts, tris[3 * tri + c]);
-  double w;
-  *r = quad_point(T, p, &w);
-  const double A = area[tri];
-  double jr[3] = {0, 0, 0}, ji[3] = {0, 0, 0};
-  for (int i = 0; i < 3; ++i) {
-    const int code = tri_basis[3 * tri + i];
-    if (code < 0) continue;
-    const int64_t n = code >> 1;
-    const double s = (code & 1) ? -1.0 : 1.0;
-    // f_n = s l / (2A) (r - v_i) on this triangle, v_i the free vertex
-    const double c = s * len[n] / (2.0 * A) * A * w;
-    const D3 d = *r - T[i];
-    const double2 I = xr[n];
-    jr[0] += c * d.x * I.x;
-    ji[0] += c * d.x * I.y;
-    jr[1] += c * d.y * I.x;
-    ji[1] += c * d.y * I.y;
-    jr[2] += c * d.z * I.x;
-    ji[2] += c * d.z * I.y;
+// Since p_1 + p_2 + p_3 = 0, S and T are functions of a = (p_1^2 + p_2^2 +
+// p_3^2) / 2 and b = p_1 p_2 p_3 alone (Newton's identities): the power sums are
+// P_n = sum_{2i+3j=n} n (i+j-1)!/(i! j!) a^i b^j (Waring's formula), and
+//   S = sum_n (j^n / n!) kappa_n P_n,  kappa_n = sum_gamma w gamma^n.
+// T is S's derivative along the change of p by q, times -j. The series through
+// n = 14 leaves less than 1e-16 of S and 1e-15 of T's terms while
+// |gamma_a p_i| <= 1/2 (kSeriesMax; a lambda/9 mesh has 0.3 to 0.4): 45
+// multiply-adds in place of six sines and cosines.
+constexpr int kSeriesDegree = 14;
+constexpr double kSeriesMax = 0.5;
+constexpr double kGa = 1.0 / 3.0 - kQa, kGb = 1.0 / 3.0 - kQb;
+constexpr double kappa(int n) {
+  double x = kWa, y = kWb;
+  for (int i = 0; i < n; ++i) {
+    x *= kGa;
+    y *= kGb;
   }
-  J[0] = make_double2(jr[0], ji[0]);
-  J[1] = make_double2(jr[1], ji[1]);
-  J[2] = make_double2(jr[2], ji[2]);
+  return x + y;
+}
+// coefficient of a^i b^j in the real (j even) or imaginary (j odd) part of S
+constexpr double series_coef(int i, int j) {
+  const int n = 2 * i + 3 * j;
+  if (n == 0) return 1.0;
+  double c = kappa(n) * n / (i + j);  // kappa n (i+j-1)!/(i! j!) / n!
+  for (int m = 2; m <= i + j; ++m) c *= m;
+  for (int m = 2; m <= i; ++m) c /= m;
+  for (int m = 2; m <= j; ++m) c /= m;
+  for (int m = 2; m <= n; ++m) c /= m;
+  return (n / 2) % 2 ? -c : c;
+}
+// sin and cos of 2 pi t: t is reduced by half turns (exactly), the sign taken
+// from the parity of their number, and both series run through x^21 / 21! and
+// x^20 / 20! on |x| <= pi / 2 (the first term left out is below 2e-17)
+constexpr double inv_factorial(int n) {
+  double f = 1.0;
+  for (int m = 2; m <= n; ++m) f /= m;
+  return n / 2 % 2 ? -f : f;
 }
 
-// per triangle quadrature point: position (3) and A w J (3 complex)
-__global__ void k_point_currents(const int32_t *tris, const double *verts, const double *area,
-                                 const int32_t *tri_basis, const double *len, const double2 *x,
-                                 int64_t ldx, int nrhs, int64_t nt, double *pos, double2 *J) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nt * 7) return;
-  for (int rr = 0; rr < nrhs; ++rr) {
-    D3 r;
-    double2 Jp[3];
-    point_current(tris, verts, area, tri_basis, len, x + (int64_t)rr * ldx, t, &r, Jp);
-    if (rr == 0) {
-      pos[3 * t] = r.x;
-      pos[3 * t + 1] = r.y;
-      pos[3 * t + 2] = r.z;
-    }
-    double2 *o = J + ((int64_t)rr * nt * 7 + t) * 3;
-    o[0] = Jp[0];
-    o[1] = Jp[1];
-    o[2] = Jp[2];
-  }
-}
-
-constexpr int kRcsThreads = 256;
-constexpr int kDirTile = 8;      // directions per work-group
-constexpr int kPtsChunk = 4096;  // quadrature points per work-group (aim_rcs)
-
-// The points a part kernel sums: precomputed (aim_rcs) or formed in place.
-struct PointsStored {
-  const double *pos;
-  const double2 *J;  // [nrhs][npts][3]
-  __device__ void get(int rr, int64_t npts, int64_t p, D3 *r, double2 *Jp) const {
-    *r = d3(pos[3 * p], pos[3 * p + 1], pos[3 * p + 2]);
-    const double2 *Jr = J + (int64_t)rr * npts * 3;
-    Jp[0] = Jr[3 * p];
-    Jp[1] = Jr[3 * p + 1];
-    Jp[2] = Jr[3 * p + 2];
+// The constants of both series, read with scalar loads where they are used: as
+// literals the compiler moves them all out of the triangle loop into vector
+// registers, and spills (54 of 128 for one right-hand side).
+struct RcsConst {
+  double s[11], c[11];  // sine and cosine, highest power first
+  double a[5][8];       // series_coef(i, j) as a[j][i]
+  constexpr RcsConst() : s{}, c{}, a{} {
+    for (int i = 0; i < 11; ++i) s[i] = inv_factorial(21 - 2 * i), c[i] = inv_factorial(20 - 2 * i);
+    for (int j = 0; j < 5; ++j)
+      for (int i = 0; i < 8; ++i) a[j][i] = series_coef(i, j);
   }
 };
-struct PointsInPlace {
+__constant__ constexpr RcsConst kRcsConst{};
+using RcsConstPtr = const __attribute__((address_space(4))) RcsConst *;  // scalar loads
+
+// A_j(a) = sum_i coef(i, j) a^i (DER 0) or its derivative (DER 1)
+template <int J, int DER>
+__device__ __forceinline__ double series_poly(RcsConstPtr k, double a) {
+  constexpr int imax = (kSeriesDegree - 3 * J) / 2;
+  double v = (DER ? imax : 1) * k->a[J][imax];
+  fftc::static_for<imax - DER>([&](auto i_) AIM_AI {
+    constexpr int i = imax - 1 - decltype(i_)::value;
+    v = fma(v, a, (DER ? i : 1) * k->a[J][i]);
+  });
+  return v;
+}
+
+__device__ __forceinline__ void sincos_turns(RcsConstPtr k, double t, double &sn, double &cs) {
+  constexpr double kRound = 6755399441055744.0;  // 1.5 * 2^52: rounds to an integer
+  const double z = fma(2.0, t, kRound);
+  const double x = (2.0 * 3.14159265358979323846) * fma(-0.5, z - kRound, t);
+  const double x2 = x * x;
+  double s = k->s[0], c = k->c[0];
+  fftc::static_for<10>([&](auto i_) AIM_AI {
+    constexpr int i = decltype(i_)::value + 1;
+    s = fma(s, x2, k->s[i]);
+    c = fma(c, x2, k->c[i]);
+  });
+  s *= x;
+  const int flip = (int)((unsigned)__double2loint(z) << 31);
+  sn = __hiloint2double(__double2hiint(s) ^ flip, __double2loint(s));
+  cs = __hiloint2double(__double2hiint(c) ^ flip, __double2loint(c));
+}
+
+// A triangle as the part kernel reads it from LDS (doubles): centroid in
+// wavelengths (0-2), 3 k (v_1 - c) (3-5), 3 k (v_2 - c) (6-8), 1 if its
+// |gamma_a p| can exceed kSeriesMax (9); then per right-hand side A c0 (6,
+// interleaved) and A g / k (2).
+constexpr int kTriGeom = 10, kTriRhs = 8;
+
+struct FarMesh {
   const int32_t *tris;
   const double *verts;
-  const double *area;
   const int32_t *tri_basis;
   const double *len;
-  const double2 *x;
-  int64_t ldx;
-  __device__ void get(int rr, int64_t, int64_t p, D3 *r, double2 *Jp) const {
-    point_current(tris, verts, area, tri_basis, len, x + (int64_t)rr * ldx, p, r, Jp);
-  }
+  int64_t nt;
+  double k;
 };
 
-// part[(rr ndir + d) nchunk + chunk] = sum over the chunk's points of
-// (theta_hat(d) . J) exp(+j k r_hat(d) . r); chunk = blockIdx.y covers
-// points [chunk * per_chunk, (chunk + 1) * per_chunk)
-template <class PTS>
-__global__ void __launch_bounds__(kRcsThreads)
-    k_rcs_part(PTS pts, int64_t npts, int64_t per_chunk, const double *theta, int ntheta,
-               const double *phi, int nphi, double k, int nchunk, double2 *part) {
-  __shared__ double dir[kDirTile][6];  // r_hat, theta_hat
-  __shared__ double red[kRcsThreads / 64][2 * kDirTile];
-  const int rr = blockIdx.z;
+__device__ __forceinline__ void load_tri(const FarMesh &fm, int64_t tri, D3 *T) {
+  for (int c = 0; c < 3; ++c) T[c] = vtx(fm.verts, fm.tris[3 * tri + c]);
+}
+__device__ __forceinline__ void stage_geometry(const FarMesh &fm, int64_t tri, double *o) {
+  D3 c = d3(0, 0, 0), p1 = c, p2 = c;
+  double coarse = 0.0;
+  if (tri < fm.nt) {
+    D3 T[3];
+    load_tri(fm, tri, T);
+    c = (fm.k * (0.5 / 3.14159265358979323846 / 3.0)) * (T[0] + T[1] + T[2]);
+    p1 = fm.k * ((T[1] - T[0]) + (T[1] - T[2]));
+    p2 = fm.k * ((T[2] - T[0]) + (T[2] - T[1]));
+    const double m = fmax(fmax(dot(p1, p1), dot(p2, p2)), dot(p1 + p2, p1 + p2));
+    constexpr double lim = kSeriesMax / kGa;
+    coarse = m > lim * lim ? 1.0 : 0.0;
+  }
+  o[0] = c.x, o[1] = c.y, o[2] = c.z;
+  o[3] = p1.x, o[4] = p1.y, o[5] = p1.z;
+  o[6] = p2.x, o[7] = p2.y, o[8] = p2.z;
+  o[9] = coarse;
+}
+__device__ __forceinline__ void stage_current(const FarMesh &fm, int64_t tri, const double2 *xr,
+                                              double *o) {
+  double cr[3] = {0, 0, 0}, ci[3] = {0, 0, 0}, gr = 0, gi = 0;
+  if (tri < fm.nt) {
+    D3 T[3];
+    load_tri(fm, tri, T);
+    const D3 c = (1.0 / 3.0) * (T[0] + T[1] + T[2]);
+    for (int i = 0; i < 3; ++i) {
+      const int code = fm.tri_basis[3 * tri + i];
+      if (code < 0) continue;
+      const int64_t n = code >> 1;
+      // A f_n = (s l / 2) (r - v_i) on this triangle, v_i the free vertex
+      const double f = ((code & 1) ? -0.5 : 0.5) * fm.len[n];
+      const double2 I = xr[n];
+      const D3 d = c - T[i];
+      const double fr = f * I.x, fi = f * I.y;
+      cr[0] += d.x * fr, ci[0] += d.x * fi;
+      cr[1] += d.y * fr, ci[1] += d.y * fi;
+      cr[2] += d.z * fr, ci[2] += d.z * fi;
+      gr += fr, gi += fi;
+    }
+  }
+  for (int q = 0; q < 3; ++q) o[2 * q] = cr[q], o[2 * q + 1] = ci[q];
+  o[6] = gr / fm.k, o[7] = gi / fm.k;
+}
+
+// part[(r ndir + d) nchunk + blockIdx.y] = theta_hat . N of the chunk's
+// triangles, r = r0 .. r0 + RB - 1 (those below nrhs).
+//
+// Bound by FP64 issue: 114 + 14 RB multiply-adds per triangle and direction. A
+// lane owns kDirs directions (their unit vectors and sums stay in registers), a
+// work-group 64 kDirs directions; its waves take the triangles of a batch in
+// turn, read from LDS at a wave-uniform address, and add their sums through LDS
+// at the end. Two directions per lane halve those broadcast reads, which cost
+// as much as four multiply-adds per double, and share the series' constants.
+// Summing the 7 points of every triangle separately, with the library sincos of
+// each and once more for every right-hand side, took 9.6 ms per call on the
+// 4-lambda sphere (36 980 triangles, 16 380 directions, one current) and 58 ms
+// on the 8-lambda plate (10 368 triangles, 16 currents); this takes 3.0 and 2.6
+// ms (2.2 and 1.6 ms is the multiply-adds' time at the FP64 vector rate).
+constexpr int kRcsWaves = 4;
+constexpr int kDirs = 2;
+constexpr int kDirGroup = 64 * kDirs;
+template <int RB>
+constexpr int rcs_batch() {  // triangles in LDS at a time
+  return RB <= 4 ? 64 : 32;
+}
+template <int RB>
+__global__ void __launch_bounds__(64 * kRcsWaves, RB <= 4 ? 4 : (RB <= 8 ? 3 : 2))
+    k_rcs_part(FarMesh fm, const double2 *__restrict__ x, int64_t ldx, int r0, int nrhs,
+               int64_t per_chunk, const double *__restrict__ theta, int ntheta,
+               const double *__restrict__ phi, int nphi, int nchunk, double2 *__restrict__ part) {
+  constexpr int TB = rcs_batch<RB>(), REC = kTriGeom + kTriRhs * RB;
+  constexpr int kRed = 2 * kRcsWaves * kDirGroup;  // the final sums' exchange
+  __shared__ __align__(16) double lds[TB * REC > kRed ? TB * REC : kRed];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ndir = (int64_t)ntheta * nphi;
-  const int64_t d0 = (int64_t)blockIdx.x * kDirTile;
-  if (threadIdx.x < kDirTile) {
-    const int64_t d = d0 + threadIdx.x;
-    double st = 0, ct = 1, sph = 0, cph = 1;
-    if (d < ndir) {
-      sincos(theta[d / nphi], &st, &ct);
-      sincos(phi[d % nphi], &sph, &cph);
-    }
-    double *o = dir[threadIdx.x];
-    o[0] = st * cph;
-    o[1] = st * sph;
-    o[2] = ct;
-    o[3] = ct * cph;
-    o[4] = ct * sph;
-    o[5] = -st;
-  }
-  __syncthreads();
-  double nr[kDirTile], ni[kDirTile];
+  const int64_t d0 = (int64_t)blockIdx.x * kDirGroup + lane;
+  D3 rh[kDirs], th[kDirs];
+  double ar[kDirs][RB], ai[kDirs][RB];
 #pragma unroll
-  for (int q = 0; q < kDirTile; ++q) nr[q] = ni[q] = 0;
-  const int64_t p0 = (int64_t)blockIdx.y * per_chunk;
-  const int64_t p1 = min(p0 + per_chunk, npts);
-  for (int64_t p = p0 + threadIdx.x; p < p1; p += kRcsThreads) {
-    D3 r;
-    double2 Jp[3];
-    pts.get(rr, npts, p, &r, Jp);
-    const double2 jx = Jp[0], jy = Jp[1], jz = Jp[2];
+  for (int q = 0; q < kDirs; ++q) {
+    const int64_t d = d0 + 64 * q < ndir ? d0 + 64 * q : ndir - 1;
+    double st, ct, sp, cp;
+    sincos(theta[d / nphi], &st, &ct);
+    sincos(phi[d % nphi], &sp, &cp);
+    rh[q] = d3(st * cp, st * sp, ct);
+    th[q] = d3(ct * cp, ct * sp, -st);
 #pragma unroll
-    for (int q = 0; q < kDirTile; ++q) {
-      const double *o = dir[q];
-      double s, c;
-      sincos(k * (o[0] * r.x + o[1] * r.y + o[2] * r.z), &s, &c);
-      const double jr = o[3] * jx.x + o[4] * jy.x + o[5] * jz.x;  // theta_hat . J
-      const double ji = o[3] * jx.y + o[4] * jy.y + o[5] * jz.y;
-      nr[q] += jr * c - ji * s;
-      ni[q] += jr * s + ji * c;
+    for (int r = 0; r < RB; ++r) ar[q][r] = ai[q][r] = 0.0;
+  }
+  const int64_t t0 = (int64_t)blockIdx.y * per_chunk;
+  const int64_t t1 = min(t0 + per_chunk, fm.nt);
+  for (int64_t b0 = t0; b0 < t1; b0 += TB) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < TB * (RB + 1); i += 64 * kRcsWaves) {
+      const int tl = i % TB, what = i / TB;
+      const int64_t tri = b0 + tl < t1 ? b0 + tl : fm.nt;  // past the chunk: zeros
+      if (what == 0)
+        stage_geometry(fm, tri, &lds[tl * REC]);
+      else
+        stage_current(fm, r0 + what - 1 < nrhs ? tri : fm.nt, x + (int64_t)(r0 + what - 1) * ldx,
+                      &lds[tl * REC + kTriGeom + kTriRhs * (what - 1)]);
+    }
+    __syncthreads();
+    const int tend = (int)min((int64_t)TB, t1 - b0);
+    for (int tl = wave; tl < tend; tl += kRcsWaves) {
+      const double *rec = &lds[tl * REC];
+      RcsConstPtr kc = (RcsConstPtr)&kRcsConst;
+      asm volatile("" : "+s"(kc));  // a new value each time: no load is moved out of the loop
+      const D3 c = d3(rec[0], rec[1], rec[2]);
+      const D3 v1 = d3(rec[3], rec[4], rec[5]), v2 = d3(rec[6], rec[7], rec[8]);
+      const bool coarse = __builtin_amdgcn_readfirstlane(__double2hiint(rec[9])) != 0;
+      double sr[kDirs], si[kDirs], tr[kDirs], ti[kDirs];  // e^{j k r_hat . c} (S, T)
+#pragma unroll
+      for (int q = 0; q < kDirs; ++q) {
+        const double p1 = dot(rh[q], v1), p2 = dot(rh[q], v2);
+        const double q1 = dot(th[q], v1), q2 = dot(th[q], v2);
+        double S_r, S_i, T_r, T_i;
+        if (!coarse) {
+          const double s = p1 + p2, m = p1 * p2, u = q1 + q2;
+          const double dm = p1 * q2 + q1 * p2;
+          const double a = s * s - m, b = -m * s;
+          const double da = 2.0 * s * u - dm, db = -(dm * s + m * u);
+          const double b2 = b * b;
+          const double A0 = series_poly<0, 0>(kc, a), A1 = series_poly<1, 0>(kc, a);
+          const double A2 = series_poly<2, 0>(kc, a), A3 = series_poly<3, 0>(kc, a);
+          const double A4 = series_poly<4, 0>(kc, a);
+          S_r = A0 + b2 * (A2 + b2 * A4);
+          S_i = b * (A1 + b2 * A3);
+          const double fa_r = series_poly<0, 1>(kc, a) +
+                              b2 * (series_poly<2, 1>(kc, a) + b2 * series_poly<4, 1>(kc, a));
+          const double fa_i = b * (series_poly<1, 1>(kc, a) + b2 * series_poly<3, 1>(kc, a));
+          const double fb_r = b * (2.0 * A2 + b2 * (4.0 * A4));
+          const double fb_i = A1 + b2 * (3.0 * A3);
+          T_r = fa_i * da + fb_i * db;  // -j (f_a da + f_b db)
+          T_i = -(fa_r * da + fb_r * db);
+        } else {
+          S_r = kWc, S_i = 0.0, T_r = 0.0, T_i = 0.0;
+#pragma unroll 1
+          for (int i = 0; i < 6; ++i) {
+            const double g = i < 3 ? kGa : kGb, w = i < 3 ? kWa : kWb;
+            const int v = i % 3;
+            const double p = v == 0 ? p1 : (v == 1 ? p2 : -(p1 + p2));
+            const double t = v == 0 ? q1 : (v == 1 ? q2 : -(q1 + q2));
+            double sn, cs;
+            sincos_turns(kc, p * (g * (0.5 / 3.14159265358979323846)), sn, cs);
+            S_r += w * cs, S_i += w * sn;
+            T_r += (w * g * t) * cs, T_i += (w * g * t) * sn;
+          }
+        }
+        double sn, cs;
+        sincos_turns(kc, dot(rh[q], c), sn, cs);
+        sr[q] = cs * S_r - sn * S_i, si[q] = cs * S_i + sn * S_r;
+        tr[q] = cs * T_r - sn * T_i, ti[q] = cs * T_i + sn * T_r;
+      }
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const double *o = rec + kTriGeom + kTriRhs * r;
+        const double xr = o[0], xi = o[1], yr = o[2], yi = o[3], zr = o[4], zi = o[5];
+        const double gr = o[6], gi = o[7];
+#pragma unroll
+        for (int q = 0; q < kDirs; ++q) {
+          const double cr = th[q].x * xr + th[q].y * yr + th[q].z * zr;
+          const double ci = th[q].x * xi + th[q].y * yi + th[q].z * zi;
+          ar[q][r] += cr * sr[q] - ci * si[q] + gr * tr[q] - gi * ti[q];
+          ai[q][r] += cr * si[q] + ci * sr[q] + gr * ti[q] + gi * tr[q];
+        }
+      }
     }
   }
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // the waves' sums, in wave order, one right-hand side at a time
+  double2 *red = reinterpret_cast<double2 *>(lds);  // [kRcsWaves][kDirGroup]
 #pragma unroll
-  for (int q = 0; q < kDirTile; ++q) {
-    for (int off = 32; off > 0; off >>= 1) {
-      nr[q] += __shfl_xor(nr[q], off, 64);
-      ni[q] += __shfl_xor(ni[q], off, 64);
+  for (int r = 0; r < RB; ++r) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kDirs; ++q)
+      red[wave * kDirGroup + 64 * q + lane] = make_double2(ar[q][r], ai[q][r]);
+    __syncthreads();
+    const int64_t d = (int64_t)blockIdx.x * kDirGroup + threadIdx.x;
+    if (threadIdx.x < kDirGroup && d < ndir && r0 + r < nrhs) {
+      double2 a = red[threadIdx.x];
+      for (int w = 1; w < kRcsWaves; ++w) {
+        a.x += red[w * kDirGroup + threadIdx.x].x;
+        a.y += red[w * kDirGroup + threadIdx.x].y;
+      }
+      part[((int64_t)(r0 + r) * ndir + d) * nchunk + blockIdx.y] = a;
     }
-    if (lane == 0) {
-      red[w][2 * q] = nr[q];
-      red[w][2 * q + 1] = ni[q];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < kDirTile && d0 + threadIdx.x < ndir) {
-    double a = 0, b = 0;
-    for (int i = 0; i < kRcsThreads / 64; ++i) {
-      a += red[i][2 * threadIdx.x];
-      b += red[i][2 * threadIdx.x + 1];
-    }
-    part[((int64_t)rr * ndir + d0 + threadIdx.x) * nchunk + blockIdx.y] = make_double2(a, b);
   }
 }
 
@@ -242,10 +380,57 @@ void *rcs_scratch_ptr(int device) {
   return g_scratch_ptr[device];
 }
 
+// Triangle chunks of the part kernel: enough work-groups for several rounds of
+// the chip (kRcsGroups), chunks of at least two batches, and at most `most`
+// partial sums per direction and right-hand side.
+constexpr int64_t kRcsGroups = 4096;
+static int64_t rcs_chunks(int64_t nt, int64_t ndir, int nrhs, int64_t most) {
+  const int64_t groups = (ndir + kDirGroup - 1) / kDirGroup * ((nrhs + 15) / 16);
+  int64_t n = std::min((kRcsGroups + groups - 1) / groups, (nt + 127) / 128);
+  n = std::min<int64_t>(std::min(n, most), 65535);
+  return std::max<int64_t>(n, 1);
+}
+
+// Partial sums of nchunk chunks into part, then sigma (all device memory). 16
+// right-hand sides share a launch; the rest takes the smallest kernel that
+// holds them (one with an unused right-hand side or three costs 14 multiply-adds
+// each, a second launch 114).
+static void rcs_launch(MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int ntheta,
+                       const double *theta, int nphi, const double *phi, double *sigma,
+                       double2 *part, int64_t nchunk, hipStream_t s) {
+  const HostPlan &h = md.hp;
+  const int64_t ndir = (int64_t)ntheta * nphi, groups = (ndir + kDirGroup - 1) / kDirGroup;
+  if (groups > INT32_MAX) throw Error(AIM_ERR_ARG, "rcs: too many directions");
+  const int64_t per_chunk = (h.nt + nchunk - 1) / nchunk;
+  const FarMesh fm{md.tris, md.verts, md.tri_basis, md.len, h.nt, h.k};
+  for (int r0 = 0; r0 < nrhs; r0 += 16) {
+    const int left = nrhs - r0;
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)nchunk), dim3(64 * kRcsWaves), 0,
+                         s, fm, x, ldx, r0, nrhs, per_chunk, theta, ntheta, phi, nphi, (int)nchunk,
+                         part);
+    };
+    if (left == 1)
+      go(k_rcs_part<1>);
+    else if (left == 2)
+      go(k_rcs_part<2>);
+    else if (left <= 4)
+      go(k_rcs_part<4>);
+    else if (left <= 8)
+      go(k_rcs_part<8>);
+    else
+      go(k_rcs_part<16>);
+    LAUNCHCHECK();
+  }
+  const double keta = h.k * kEta0;
+  const int64_t slots = ndir * nrhs;
+  hipLaunchKernelGGL(k_rcs_reduce, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, part,
+                     (int)nchunk, slots, keta * keta / (4.0 * kPi), sigma);
+  LAUNCHCHECK();
+}
+
 void rcs_mesh(Plan *pl, MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int ntheta,
               const double *theta, int nphi, const double *phi, double *sigma, hipStream_t s) {
-  const HostPlan &h = md.hp;
-  const int64_t nt = h.nt, npts = 7 * nt;
   std::vector<void *> tmp;
   auto alloc = [&](size_t bytes) {
     void *p = dev_alloc(pl, bytes);
@@ -253,29 +438,15 @@ void rcs_mesh(Plan *pl, MeshDev &md, int nrhs, const double2 *x, int64_t ldx, in
     return p;
   };
   try {
-    double *pos = (double *)alloc(sizeof(double) * 3 * npts);
-    double2 *J = (double2 *)alloc(sizeof(double2) * 3 * npts * nrhs);
     double *dth = (double *)alloc(sizeof(double) * ntheta);
     double *dph = (double *)alloc(sizeof(double) * nphi);
     const int64_t ndir = (int64_t)ntheta * nphi;
     double *dsig = (double *)alloc(sizeof(double) * ndir * nrhs);
     HIPCHECK(hipMemcpyAsync(dth, theta, sizeof(double) * ntheta, hipMemcpyHostToDevice, s));
     HIPCHECK(hipMemcpyAsync(dph, phi, sizeof(double) * nphi, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_point_currents, dim3((unsigned)((npts + 255) / 256)), dim3(256), 0, s,
-                       md.tris, md.verts, md.area, md.tri_basis, md.len, x, ldx, nrhs, nt, pos, J);
-    LAUNCHCHECK();
-    const double keta = h.k * kEta0;
-    const double scale = keta * keta / (4.0 * kPi);
-    const int nchunk = (int)((npts + kPtsChunk - 1) / kPtsChunk);
+    const int64_t nchunk = rcs_chunks(md.hp.nt, ndir, nrhs, INT32_MAX);
     double2 *part = (double2 *)alloc(sizeof(double2) * (size_t)ndir * nrhs * nchunk);
-    hipLaunchKernelGGL((k_rcs_part<PointsStored>),
-                       dim3((unsigned)((ndir + kDirTile - 1) / kDirTile), (unsigned)nchunk, nrhs),
-                       dim3(kRcsThreads), 0, s, PointsStored{pos, J}, npts, (int64_t)kPtsChunk,
-                       dth, ntheta, dph, nphi, h.k, nchunk, part);
-    LAUNCHCHECK();
-    hipLaunchKernelGGL(k_rcs_reduce, dim3((unsigned)((ndir * nrhs + 255) / 256)), dim3(256), 0, s,
-                       part, nchunk, ndir * nrhs, scale, dsig);
-    LAUNCHCHECK();
+    rcs_launch(md, nrhs, x, ldx, ntheta, dth, nphi, dph, dsig, part, nchunk, s);
     HIPCHECK(hipMemcpyAsync(sigma, dsig, sizeof(double) * ndir * nrhs, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
   } catch (...) {
@@ -288,30 +459,15 @@ void rcs_mesh(Plan *pl, MeshDev &md, int nrhs, const double2 *x, int64_t ldx, in
 void rcs_mesh_noalloc(MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int ntheta,
                       const double *theta, int nphi, const double *phi, double *sigma,
                       double2 *part, hipStream_t s) {
-  const HostPlan &h = md.hp;
-  const int64_t npts = 7 * h.nt;
   const int64_t ndir = (int64_t)ntheta * nphi;
   const int64_t slots = ndir * nrhs;  // partial sums needed per chunk
   if (slots > kRcsScratchElems)
     throw Error(AIM_ERR_ARG, "aim_rcs_noalloc: ntheta * nphi * nrhs = " + std::to_string(slots) +
                                  " exceeds its fixed scratch of " +
                                  std::to_string(kRcsScratchElems) + " partial sums");
-  // as many point chunks as aim_rcs uses, fewer if the scratch cannot hold them
-  int64_t nchunk = (npts + kPtsChunk - 1) / kPtsChunk;
-  if (nchunk * slots > kRcsScratchElems) nchunk = kRcsScratchElems / slots;
-  if (nchunk < 1) nchunk = 1;
-  const int64_t per_chunk = (npts + nchunk - 1) / nchunk;
-  const double keta = h.k * kEta0;
-  const double scale = keta * keta / (4.0 * kPi);
-  hipLaunchKernelGGL((k_rcs_part<PointsInPlace>),
-                     dim3((unsigned)((ndir + kDirTile - 1) / kDirTile), (unsigned)nchunk, nrhs),
-                     dim3(kRcsThreads), 0, s,
-                     PointsInPlace{md.tris, md.verts, md.area, md.tri_basis, md.len, x, ldx}, npts,
-                     per_chunk, theta, ntheta, phi, nphi, h.k, (int)nchunk, part);
-  LAUNCHCHECK();
-  hipLaunchKernelGGL(k_rcs_reduce, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, part,
-                     (int)nchunk, slots, scale, sigma);
-  LAUNCHCHECK();
+  // as many chunks as aim_rcs uses, fewer if the scratch cannot hold them
+  const int64_t nchunk = rcs_chunks(md.hp.nt, ndir, nrhs, kRcsScratchElems / slots);
+  rcs_launch(md, nrhs, x, ldx, ntheta, theta, nphi, phi, sigma, part, nchunk, s);
 }
 
 }  // namespace aim
