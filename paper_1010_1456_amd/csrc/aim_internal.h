@@ -253,6 +253,10 @@ void solver_release(Plan *pl);
 
 // set-up kernels (setup_kernels.hip)
 void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s);
+// near-zone matrix Z^MOM - Z^grid and the diagonal of Z^MOM (near_fill.hip);
+// area, anchor3: device, per triangle and 3 per basis
+void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *anchor3,
+                    hipStream_t s);
 // times the alternative kernel variants of one mesh and keeps the faster
 void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 

@@ -22,6 +22,7 @@
 #include "aim_internal.h"
 #include "fft_core.h"
 #include "geom_device.h"
+#include "turns.h"
 
 namespace aim {
 using namespace geo;
@@ -68,23 +69,13 @@ constexpr double series_coef(int i, int j) {
   for (int m = 2; m <= n; ++m) c /= m;
   return (n / 2) % 2 ? -c : c;
 }
-// sin and cos of 2 pi t: t is reduced by half turns (exactly), the sign taken
-// from the parity of their number, and both series run through x^21 / 21! and
-// x^20 / 20! on |x| <= pi / 2 (the first term left out is below 2e-17)
-constexpr double inv_factorial(int n) {
-  double f = 1.0;
-  for (int m = 2; m <= n; ++m) f /= m;
-  return n / 2 % 2 ? -f : f;
-}
-
 // The constants of both series, read with scalar loads where they are used: as
 // literals the compiler moves them all out of the triangle loop into vector
 // registers, and spills (54 of 128 for one right-hand side).
 struct RcsConst {
-  double s[11], c[11];  // sine and cosine, highest power first
-  double a[5][8];       // series_coef(i, j) as a[j][i]
-  constexpr RcsConst() : s{}, c{}, a{} {
-    for (int i = 0; i < 11; ++i) s[i] = inv_factorial(21 - 2 * i), c[i] = inv_factorial(20 - 2 * i);
+  TurnsConst turns;
+  double a[5][8];  // series_coef(i, j) as a[j][i]
+  constexpr RcsConst() : turns{}, a{} {
     for (int j = 0; j < 5; ++j)
       for (int i = 0; i < 8; ++i) a[j][i] = series_coef(i, j);
   }
@@ -102,23 +93,6 @@ __device__ __forceinline__ double series_poly(RcsConstPtr k, double a) {
     v = fma(v, a, (DER ? i : 1) * k->a[J][i]);
   });
   return v;
-}
-
-__device__ __forceinline__ void sincos_turns(RcsConstPtr k, double t, double &sn, double &cs) {
-  constexpr double kRound = 6755399441055744.0;  // 1.5 * 2^52: rounds to an integer
-  const double z = fma(2.0, t, kRound);
-  const double x = (2.0 * 3.14159265358979323846) * fma(-0.5, z - kRound, t);
-  const double x2 = x * x;
-  double s = k->s[0], c = k->c[0];
-  fftc::static_for<10>([&](auto i_) AIM_AI {
-    constexpr int i = decltype(i_)::value + 1;
-    s = fma(s, x2, k->s[i]);
-    c = fma(c, x2, k->c[i]);
-  });
-  s *= x;
-  const int flip = (int)((unsigned)__double2loint(z) << 31);
-  sn = __hiloint2double(__double2hiint(s) ^ flip, __double2loint(s));
-  cs = __hiloint2double(__double2hiint(c) ^ flip, __double2loint(c));
 }
 
 // A triangle as the part kernel reads it from LDS (doubles): centroid in
@@ -283,13 +257,13 @@ __global__ void __launch_bounds__(64 * kRcsWaves, RB <= 4 ? 4 : (RB <= 8 ? 3 : 2
             const double p = v == 0 ? p1 : (v == 1 ? p2 : -(p1 + p2));
             const double t = v == 0 ? q1 : (v == 1 ? q2 : -(q1 + q2));
             double sn, cs;
-            sincos_turns(kc, p * (g * (0.5 / 3.14159265358979323846)), sn, cs);
+            sincos_turns(&kc->turns, p * (g * (0.5 / 3.14159265358979323846)), sn, cs);
             S_r += w * cs, S_i += w * sn;
             T_r += (w * g * t) * cs, T_i += (w * g * t) * sn;
           }
         }
         double sn, cs;
-        sincos_turns(kc, dot(rh[q], c), sn, cs);
+        sincos_turns(&kc->turns, dot(rh[q], c), sn, cs);
         sr[q] = cs * S_r - sn * S_i, si[q] = cs * S_i + sn * S_r;
         tr[q] = cs * T_r - sn * T_i, ti[q] = cs * T_i + sn * T_r;
       }

@@ -13,18 +13,6 @@ using namespace geo;
 
 namespace {
 
-__device__ inline void basis_side(const int32_t *rwg, const double *len, const double *area,
-                                  const int32_t *tris, const double *verts, int64_t n, int side,
-                                  D3 *T, double *A, D3 *free_v, double *s, double *l) {
-  const int t = rwg[4 * n + side];
-  const int fv = rwg[4 * n + 2 + side];
-  for (int c = 0; c < 3; ++c) T[c] = vtx(verts, tris[3 * (int64_t)t + c]);
-  *A = area[t];
-  *free_v = vtx(verts, fv);
-  *s = side == 0 ? 1.0 : -1.0;
-  *l = len[n];
-}
-
 // Lambda[n][q][u] = sum_{T+-} A_T sum_p w_p F_q(r_p) l_u(r_p), q = x, y, z, div.
 __global__ void k_projection(const int32_t *rwg, const double *len, const double *area,
                              const int32_t *tris, const double *verts, const int32_t *anchor3,
@@ -64,12 +52,6 @@ __global__ void k_projection(const int32_t *rwg, const double *len, const double
     }
   }
   for (int q = 0; q < 4; ++q) lam[(b * 4 + q) * K + u] = acc[q];
-}
-
-// unit normal (v1 - v0) x (v2 - v0) of a triangle
-__device__ inline D3 tri_normal(const D3 *T) {
-  const D3 c = cross(T[1] - T[0], T[2] - T[0]);
-  return (1.0 / norm(c)) * c;
 }
 
 // l_s(xi) and its derivative for the nodes 0..M
@@ -159,14 +141,6 @@ __global__ void k_to_float(const double *in, float *out, int64_t n) {
   if (i < n) out[i] = (float)in[i];
 }
 
-__device__ inline double2 green(double k, double R) {
-  if (R == 0.0) return make_double2(0.0, 0.0);
-  double sn, cs;
-  sincos(k * R, &sn, &cs);
-  const double g = 0.25 / (3.14159265358979323846 * R);
-  return make_double2(g * cs, -g * sn);
-}
-
 // g on the circulant embedding [Px][Py][Pz]: index i folds to min(i, P - i)
 __global__ void k_embed_green(double2 *out, int Px, int Py, int Pz, int Nx, int Ny, int Nz,
                               double k, double h) {
@@ -242,134 +216,6 @@ __global__ void k_extract_octant(const double2 *full, double2 *oct, int Py, int 
   const int ii = (int)(t / ((int64_t)Hy * Hz));
   double2 v = full[((int64_t)ii * Py + jj) * Pz + kk];
   oct[t] = make_double2(v.x * scale, v.y * scale);
-}
-
-// g at integer offsets (i, j, k) in [0, D]^3 for the near-zone grid part
-__global__ void k_green_table(double2 *tab, int D, double k, double h) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int D1 = D + 1;
-  if (t >= D1 * D1 * D1) return;
-  const int i = t / (D1 * D1), j = (t / D1) % D1, l = t % D1;
-  tab[t] = green(k, h * sqrt((double)i * i + (double)j * j + (double)l * l));
-}
-
-// Z^near_mn = Z^MOM_mn - Z^grid_mn for the near pairs of row m = blockIdx.x
-// (one thread per nonzero); diagonal Z^MOM_mm is also stored.
-__global__ void __launch_bounds__(128)
-    k_near_fill(const int32_t *rwg, const double *len, const double *area, const int32_t *tris,
-                const double *verts, const int32_t *anchor3, const int32_t *rowptr,
-                const int32_t *cols, const double *lam, const double *curl, double alpha,
-                const double2 *gtab, int D, int M, double k, double eta, int64_t row0,
-                double2 *nearv, double2 *zdiag) {
-  extern __shared__ double lam_m[];  // 4 K projection weights, then 3 K curl weights (CFIE)
-  const int K = (M + 1) * (M + 1) * (M + 1);
-  const int64_t m = row0 + blockIdx.x;
-  for (int i = threadIdx.x; i < 4 * K; i += blockDim.x) lam_m[i] = lam[m * 4 * K + i];
-  double *w_m = lam_m + 4 * K;
-  if (curl)
-    for (int i = threadIdx.x; i < 3 * K; i += blockDim.x) w_m[i] = curl[m * 3 * K + i];
-  __syncthreads();
-  const double pref = k * eta;  // real factor of j k eta
-  D3 Tm[2][3], pm[2];
-  double Am[2], sm[2], lm = 0;
-  int tm_id[2];
-  for (int side = 0; side < 2; ++side) {
-    basis_side(rwg, len, area, tris, verts, m, side, Tm[side], &Am[side], &pm[side], &sm[side], &lm);
-    tm_id[side] = rwg[4 * m + side];
-  }
-  const int am[3] = {anchor3[3 * m], anchor3[3 * m + 1], anchor3[3 * m + 2]};
-  const int D1 = D + 1;
-  const int M1 = M + 1;
-  for (int64_t e = rowptr[m] + threadIdx.x; e < rowptr[m + 1]; e += blockDim.x) {
-    const int64_t n = cols[e];
-    // ---- Z^MOM_mn from the four triangle pairs
-    double zr = 0.0, zi = 0.0;
-    for (int sn_ = 0; sn_ < 2; ++sn_) {
-      D3 Tn[3], pn;
-      double An, sn, ln;
-      basis_side(rwg, len, area, tris, verts, n, sn_, Tn, &An, &pn, &sn, &ln);
-      const int tn = rwg[4 * n + sn_];
-      const int32_t *vn = &tris[3 * (int64_t)tn];
-      for (int sm_ = 0; sm_ < 2; ++sm_) {
-        const int32_t *vm = &tris[3 * (int64_t)tm_id[sm_]];
-        bool touch = false;
-        for (int a = 0; a < 3; ++a)
-          for (int c = 0; c < 3; ++c) touch |= (vm[a] == vn[c]);
-        const C2 I = efie_pair(Tm[sm_], Am[sm_], pm[sm_], Tn, An, pn, k, touch);
-        const double f = sm[sm_] * sn * lm * ln / (4.0 * Am[sm_] * An);
-        zr += f * I.re;
-        zi += f * I.im;
-      }
-    }
-    // j k eta (zr + j zi)
-    double mom_re = -pref * zi, mom_im = pref * zr;
-    if (curl) {
-      // combined field: alpha Z^E + (1 - alpha) eta (G/2 - K) over the four
-      // triangle pairs (coplanar pairs, the same triangle included, have K = 0)
-      double hr = 0.0, hi = 0.0;
-      for (int sn_ = 0; sn_ < 2; ++sn_) {
-        D3 Tn[3], pn;
-        double An, sn, ln;
-        basis_side(rwg, len, area, tris, verts, n, sn_, Tn, &An, &pn, &sn, &ln);
-        const int tn = rwg[4 * n + sn_];
-        const int32_t *vn = &tris[3 * (int64_t)tn];
-        for (int sm_ = 0; sm_ < 2; ++sm_) {
-          const double f = sm[sm_] * sn * lm * ln / (4.0 * Am[sm_] * An);
-          if (tm_id[sm_] == tn) {
-            hr += f * 0.5 * gram_pair(Tm[sm_], Am[sm_], pm[sm_], pn);
-            continue;
-          }
-          if (coplanar(Tm[sm_], Tn)) continue;
-          const int32_t *vm = &tris[3 * (int64_t)tm_id[sm_]];
-          bool touch = false;
-          for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 3; ++c) touch |= (vm[a] == vn[c]);
-          const C2 I = mfie_pair(Tm[sm_], Am[sm_], pm[sm_], tri_normal(Tm[sm_]), Tn, An, pn, k, touch);
-          hr -= f * I.re;
-          hi -= f * I.im;
-        }
-      }
-      mom_re = alpha * mom_re + (1.0 - alpha) * eta * hr;
-      mom_im = alpha * mom_im + (1.0 - alpha) * eta * hi;
-    }
-    // ---- Z^grid_mn = j k eta [sum_{q<3} L_mq^T G L_nq - k^-2 L_md^T G L_nd]
-    const int dn[3] = {am[0] - anchor3[3 * n], am[1] - anchor3[3 * n + 1], am[2] - anchor3[3 * n + 2]};
-    const double *lam_n = lam + n * 4 * K;
-    double gr = 0.0, gi = 0.0, wr = 0.0, wi = 0.0;
-    for (int v = 0; v < K; ++v) {
-      const int vi = v / (M1 * M1), vj = (v / M1) % M1, vk = v % M1;
-      const double ln0 = lam_n[v], ln1 = lam_n[K + v], ln2 = lam_n[2 * K + v], ln3 = lam_n[3 * K + v];
-      double tr0 = 0, ti0 = 0, tr1 = 0, ti1 = 0;  // vector and scalar parts
-      double tr2 = 0, ti2 = 0;                    // curl-weight part (combined field)
-      for (int u = 0; u < K; ++u) {
-        const int ui = u / (M1 * M1), uj = (u / M1) % M1, uk = u % M1;
-        const int oi = abs(dn[0] + ui - vi), oj = abs(dn[1] + uj - vj), ok = abs(dn[2] + uk - vk);
-        const double2 g = gtab[(oi * D1 + oj) * D1 + ok];
-        const double vec = lam_m[u] * ln0 + lam_m[K + u] * ln1 + lam_m[2 * K + u] * ln2;
-        const double sca = lam_m[3 * K + u] * ln3;
-        tr0 += g.x * vec;
-        ti0 += g.y * vec;
-        tr1 += g.x * sca;
-        ti1 += g.y * sca;
-        if (curl) {
-          const double cw = w_m[u] * ln0 + w_m[K + u] * ln1 + w_m[2 * K + u] * ln2;
-          tr2 += g.x * cw;
-          ti2 += g.y * cw;
-        }
-      }
-      gr += tr0 - tr1 / (k * k);
-      gi += ti0 - ti1 / (k * k);
-      wr += tr2;
-      wi += ti2;
-    }
-    double grid_re = -pref * gi, grid_im = pref * gr;
-    if (curl) {  // alpha j k eta [..] - (1 - alpha) eta W^T g Lambda
-      grid_re = alpha * grid_re - (1.0 - alpha) * eta * wr;
-      grid_im = alpha * grid_im - (1.0 - alpha) * eta * wi;
-    }
-    nearv[e] = make_double2(mom_re - grid_re, mom_im - grid_im);
-    if (n == m) zdiag[m] = make_double2(mom_re, mom_im);
-  }
 }
 
 __global__ void k_excitation(const int32_t *rwg, const double *len, const double *area,
@@ -693,39 +539,8 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
   }
   phase_done(AIM_SETUP_GREEN);
 
-  // near zone: offsets table size from the largest anchor difference
-  int D = 0;
-  for (int64_t i = 0; i < n; ++i)
-    for (int64_t e = h.rowptr[i]; e < h.rowptr[i + 1]; ++e) {
-      const int64_t j = h.cols[e];
-      for (int c = 0; c < 3; ++c) D = std::max(D, std::abs(h.anchor[3 * i + c] - h.anchor[3 * j + c]));
-    }
-  D += M;
-  const int D1 = D + 1;
-  double2 *gtab = (double2 *)dev_alloc(pl, sizeof(double2) * D1 * D1 * D1);
-  hipLaunchKernelGGL(k_green_table, dim3(blocks_for((int64_t)D1 * D1 * D1, 256)), dim3(256), 0, s,
-                     gtab, D, h.k, h.h);
-  LAUNCHCHECK();
-  md.near64 = (double2 *)dev_alloc(pl, sizeof(double2) * std::max<int64_t>(h.nnz, 1));
-  md.zdiag = (double2 *)dev_alloc(pl, sizeof(double2) * n);
-  const int64_t chunk = 1 << 20;  // rows per launch
-  for (int64_t r0 = 0; r0 < n; r0 += chunk) {
-    const int64_t rows = std::min(chunk, n - r0);
-    hipLaunchKernelGGL(k_near_fill, dim3((unsigned)rows), dim3(128),
-                       sizeof(double) * (h.cfie ? 7 : 4) * K, s, md.rwg, md.len, area, md.tris,
-                       md.verts, anchor3, md.rowptr, md.cols, md.lam64, md.curl64, h.alpha, gtab,
-                       D, M, h.k, kEta0, r0, md.near64, md.zdiag);
-    LAUNCHCHECK();
-  }
-  if (pl->mixed) {
-    md.near32 = (float2 *)dev_alloc(pl, sizeof(float2) * std::max<int64_t>(h.nnz, 1));
-    hipLaunchKernelGGL(k_to_float, dim3(blocks_for(2 * h.nnz, 256)), dim3(256), 0, s,
-                       (const double *)md.near64, (float *)md.near32, 2 * h.nnz);
-    LAUNCHCHECK();
-  }
-  HIPCHECK(hipStreamSynchronize(s));
+  near_fill_mesh(pl, md, area, anchor3, s);
   phase_done(AIM_SETUP_NEAR_FILL);
-  dev_free(pl, gtab);
   dev_free(pl, anchor3);
   md.area = area;  // kept for excitation and RCS
   rcs_prepare_mesh(pl, md, s);
