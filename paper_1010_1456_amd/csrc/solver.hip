@@ -17,6 +17,7 @@
 #include <complex>
 #include <map>
 #include <tuple>
+#include <type_traits>
 
 #include "aim_internal.h"
 
@@ -47,55 +48,146 @@ __device__ inline double2 block_sum2(double a, double b) {
   return make_double2(ra, rb);
 }
 
-// All nv dot products of one Gram-Schmidt pass in one launch: every thread
-// keeps its kRows entries of w in registers and walks a group of kGroup basis
-// vectors (blockIdx.z); each wave writes its partial sum of conj(V[i][r][row])
-// w[r][row] to part[(i S + s) np_stride + p], p = the wave's index, and
-// k_part_reduce adds the partials in a fixed order: no atomics, bitwise
-// reproducible.
-constexpr int kRows = 8;
-constexpr int kGroup = 8;
-constexpr int kDotWaves = 4;  // waves per work-group of k_dots_part
-__global__ void __launch_bounds__(64 * kDotWaves)
-    k_dots_part(const double2 *V, const double2 *w, int64_t ld, int64_t vstride, int64_t lo,
-                int64_t hi, int nv, int sys0, int S, int64_t np_stride, double2 *part) {
-  const int r = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int64_t p = (int64_t)blockIdx.x * kDotWaves + (threadIdx.x >> 6);
-  double2 wv[kRows];
-  int64_t idx[kRows];
-#pragma unroll
-  for (int k = 0; k < kRows; ++k) {
-    idx[k] = lo + ((int64_t)blockIdx.x * kRows + k) * blockDim.x + threadIdx.x;
-    wv[k] = idx[k] < hi ? w[(int64_t)r * ld + idx[k]] : make_double2(0.0, 0.0);
+// One pass over the Krylov basis of the Gram-Schmidt step: with SUB, w -= V h
+// (h[i S + s]); with DOTS, the partial dot products V_i^H w of the (new) w into
+// part[(i S + s) np_stride + blockIdx.x]; with NORM, the partial |w|^2 of the new
+// w into npart[s kNormParts + blockIdx.x]. Classical Gram-Schmidt twice is then
+// three passes over V instead of four, the middle one (SUB and DOTS) keeping its
+// tile of V in registers between the two uses.
+//
+// Bound by the read of V (N nv 16 bytes, from HBM or the last-level cache). A
+// work-group's 256 threads are 16 rows x 16 vector groups: thread (lr, g) holds
+// rows lr + 16 k (k < RP) of vectors g + 16 t (t < SLOTS), all loads of a tile
+// in flight at once, so that also a basis of a few thousand rows fills the chip.
+// With a thread per row (subtraction) or per 8 rows and 8 vectors (dots) the
+// 16-lambda plate's steps (N = 61 920, 50 vectors on average) had 242 and 217
+// work-groups on 256 CUs and took 16 and 22 us a pass, at 3.1 and 2.3 TB/s.
+constexpr int kTileLanes = 16;  // row lanes, and vector groups, of a work-group
+constexpr int kNormParts = 1024;  // upper bound of the grid's x extent
+template <int SLOTS, int RP, bool SUB, bool DOTS, bool NORM>
+__global__ void __launch_bounds__(256)
+    k_basis_pass(const double2 *__restrict__ V, double2 *__restrict__ w, int64_t ld,
+                 int64_t vstride, int64_t lo, int64_t n, int nv, int sys0, int S,
+                 const double2 *__restrict__ h, int64_t np_stride, double2 *__restrict__ part,
+                 double *__restrict__ npart) {
+  constexpr int ROWS = kTileLanes * RP;
+  __shared__ double2 hs[SUB ? SLOTS * 16 : 1];
+  __shared__ double2 red[SUB ? 2 : 1][4][ROWS];
+  const int r = blockIdx.y, s = sys0 + r;
+  const int lr = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int wave = threadIdx.x >> 6;
+  V += (int64_t)r * ld + lo;
+  w += (int64_t)r * ld + lo;
+  if (SUB) {
+    for (int i = threadIdx.x; i < SLOTS * 16; i += 256)
+      hs[i] = i < nv ? h[(int64_t)i * S + s] : make_double2(0.0, 0.0);
+    __syncthreads();
   }
-  const int i1 = min(nv, (int)(blockIdx.z + 1) * kGroup);
-  for (int i = blockIdx.z * kGroup; i < i1; ++i) {
-    const double2 *v = V + (int64_t)i * vstride + (int64_t)r * ld;
-    double a = 0, b = 0;
+  double2 acc[DOTS ? SLOTS : 1];
+  double nrm = 0.0;
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
-      if (idx[k] < hi) {
-        const double2 q = v[idx[k]];
-        a += q.x * wv[k].x + q.y * wv[k].y;
-        b += q.x * wv[k].y - q.y * wv[k].x;
+  for (int t = 0; t < (DOTS ? SLOTS : 1); ++t) acc[t] = make_double2(0.0, 0.0);
+  int par = 0;
+  for (int64_t row0 = (int64_t)blockIdx.x * ROWS; row0 < n; row0 += (int64_t)gridDim.x * ROWS) {
+    double2 v[SLOTS][RP], wv[RP];
+#pragma unroll
+    for (int t = 0; t < SLOTS; ++t)
+#pragma unroll
+      for (int k = 0; k < RP; ++k) {
+        const int64_t row = row0 + lr + 16 * k;
+        const int i = g + 16 * t;
+        v[t][k] = (i < nv && row < n) ? V[(int64_t)i * vstride + row] : make_double2(0.0, 0.0);
       }
+#pragma unroll
+    for (int k = 0; k < RP; ++k) {
+      const int64_t row = row0 + lr + 16 * k;
+      wv[k] = row < n ? w[row] : make_double2(0.0, 0.0);
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      a += __shfl_xor(a, off, 64);
-      b += __shfl_xor(b, off, 64);
+    if (SUB) {
+      double2 p[RP];
+#pragma unroll
+      for (int k = 0; k < RP; ++k) p[k] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int t = 0; t < SLOTS; ++t) {
+        const double2 c = hs[g + 16 * t];
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+          p[k].x += c.x * v[t][k].x - c.y * v[t][k].y;
+          p[k].y += c.x * v[t][k].y + c.y * v[t][k].x;
+        }
+      }
+      // over the 16 vector groups: 4 in each wave, then the 4 waves (the buffer
+      // of the tile before last is free: every thread has passed its barrier)
+#pragma unroll
+      for (int off = 16; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+          p[k].x += __shfl_xor(p[k].x, off, 64);
+          p[k].y += __shfl_xor(p[k].y, off, 64);
+        }
+      if ((g & 3) == 0)
+#pragma unroll
+        for (int k = 0; k < RP; ++k) red[par][wave][lr + 16 * k] = p[k];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < RP; ++k) {
+        double2 q = red[par][0][lr + 16 * k];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) {
+          q.x += red[par][u][lr + 16 * k].x;
+          q.y += red[par][u][lr + 16 * k].y;
+        }
+        wv[k].x -= q.x;
+        wv[k].y -= q.y;
+        const int64_t row = row0 + lr + 16 * k;
+        if (g == 0 && row < n) w[row] = wv[k];
+      }
+      par ^= 1;
     }
-    if (lane == 0) part[((int64_t)i * S + sys0 + r) * np_stride + p] = make_double2(a, b);
+    if (NORM)
+#pragma unroll
+      for (int k = 0; k < RP; ++k) nrm += wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+    if (DOTS)
+#pragma unroll
+      for (int t = 0; t < SLOTS; ++t)
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+          acc[t].x += v[t][k].x * wv[k].x + v[t][k].y * wv[k].y;
+          acc[t].y += v[t][k].x * wv[k].y - v[t][k].y * wv[k].x;
+        }
   }
+  for (int off = 1; off < 16; off <<= 1) {  // over the 16 row lanes
+    if (NORM) nrm += __shfl_xor(nrm, off, 64);
+    if (DOTS)
+#pragma unroll
+      for (int t = 0; t < SLOTS; ++t) {
+        acc[t].x += __shfl_xor(acc[t].x, off, 64);
+        acc[t].y += __shfl_xor(acc[t].y, off, 64);
+      }
+  }
+  if (NORM && threadIdx.x == 0) npart[(int64_t)s * kNormParts + blockIdx.x] = nrm;
+  if (DOTS && lr == 0)
+#pragma unroll
+    for (int t = 0; t < SLOTS; ++t) {
+      const int i = g + 16 * t;
+      if (i < nv) part[((int64_t)i * S + s) * np_stride + blockIdx.x] = acc[t];
+    }
 }
-// partials per work-group of k_dots_part over n rows
-int64_t dot_parts(int64_t n) { return (n + 64 * kDotWaves * kRows - 1) / (64 * kDotWaves * kRows) * kDotWaves; }
+// work-groups per system of a pass over n rows with R right-hand sides: one per
+// 64-row tile up to about 8 per CU over all systems
+int64_t basis_groups(int64_t n, int R) {
+  const int64_t most = std::min<int64_t>(kNormParts, std::max<int64_t>(64, 2048 / R));
+  return std::max<int64_t>(1, std::min<int64_t>(most, (n + 63) / 64));
+}
 
 // out[i S + s] = sum_{p < np} part[(i S + s) np_stride + p], fixed order;
-// one wave per (i, s): blockIdx.x = i, blockIdx.y = s - sys0
+// one wave per (i, s): blockIdx.x = i, blockIdx.y = s - sys0. With add (the
+// second pass), the sum of both passes goes to column j of H as well.
 __global__ void __launch_bounds__(64)
-    k_part_reduce(const double2 *part, int64_t np_stride, int np, int sys0, int S, double2 *out) {
-  const int64_t row = (int64_t)blockIdx.x * S + sys0 + blockIdx.y;
+    k_part_reduce(const double2 *part, int64_t np_stride, int np, int sys0, int S, double2 *out,
+                  const double2 *add, double2 *H, int m, int j) {
+  const int s = sys0 + blockIdx.y;
+  const int64_t row = (int64_t)blockIdx.x * S + s;
   const double2 *pp = part + row * np_stride;
   double a = 0, b = 0;
   for (int q = threadIdx.x; q < np; q += 64) {
@@ -106,28 +198,15 @@ __global__ void __launch_bounds__(64)
     a += __shfl_xor(a, off, 64);
     b += __shfl_xor(b, off, 64);
   }
-  if (threadIdx.x == 0) out[row] = make_double2(a, b);
-}
-
-// w[r][row] -= sum_{i<nv} h[i*S + s] V[i][r][row]
-__global__ void k_sub_basis(const double2 *V, double2 *w, int64_t ld, int64_t vstride, int64_t lo,
-                            int64_t hi, int nv, int sys0, int S, const double2 *h) {
-  const int r = blockIdx.y;
-  const int64_t n = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= hi) return;
-  double2 acc = w[(int64_t)r * ld + n];
-  for (int i = 0; i < nv; ++i) {
-    const double2 c = h[(int64_t)i * S + sys0 + r];
-    const double2 p = V[(int64_t)i * vstride + (int64_t)r * ld + n];
-    acc.x -= c.x * p.x - c.y * p.y;
-    acc.y -= c.x * p.y + c.y * p.x;
+  if (threadIdx.x == 0) {
+    out[row] = make_double2(a, b);
+    if (add)
+      H[((int64_t)s * (m + 1) + blockIdx.x) * m + j] = make_double2(add[row].x + a, add[row].y + b);
   }
-  w[(int64_t)r * ld + n] = acc;
 }
 
 // part[s kNormParts + blockIdx.x] = sum |w|^2 over the block's rows of system
 // s (grid-stride); k_norm_reduce adds the partials in a fixed order
-constexpr int kNormParts = 1024;  // upper bound of the grid's x extent
 __global__ void __launch_bounds__(kRed)
     k_norm2_part(const double2 *w, int64_t ld, int64_t lo, int64_t hi, int sys0, double *part) {
   const int r = blockIdx.y;
@@ -161,9 +240,9 @@ __global__ void k_normalize(const double2 *w, double2 *out, int64_t ld, int64_t 
   out[(int64_t)r * ld + n] = make_double2(p.x * inv, p.y * inv);
 }
 
-// The end of an Arnoldi step in one launch: the squared norm of w from the
-// k_norm2_part partials (every work-group adds them in the order of
-// k_norm_reduce; work-group 0 stores it for the Givens kernel), v_{j+1} =
+// The end of an Arnoldi step in one launch: the squared norm of w from the last
+// basis pass' partials (every work-group adds them in the same order;
+// work-group 0 stores it for the Givens kernel), v_{j+1} =
 // w / |w| into out, and the next step's preconditioned vector
 // z = dinv v_{j+1} (what k_precond would compute from out).
 __global__ void __launch_bounds__(256)
@@ -314,65 +393,82 @@ struct GmresDev {
   double *tol_abs;  // [S] stop when |g_{j+1}| <= tol_abs
 };
 
-// New Hessenberg column j of every active system (one 64-lane work-group per
-// system): sum of the two Gram-Schmidt passes and the norm; apply the
-// previous rotations, form the new one, update the residual estimate
-// |g_{j+1}|. The column and the rotations are staged in LDS by all lanes; the
-// rotation chain itself is sequential. LDS: (3m + 1) complex values.
+// The new Hessenberg columns j0 .. j1-1 (at most kCheckEvery) of every active
+// system, in H as the Gram-Schmidt passes left them, with nrm[j S + s] = |w|^2
+// of each: one 64-lane work-group per system and lane c on column j0 + c. The
+// rotations known before j0 are applied to all columns at once, then each column
+// in turn forms its own, which the later ones apply; the system stops at the
+// first column whose residual estimate |g_{j+1}| meets the tolerance, or breaks
+// down. The chain of dependent rotations, about 60 ns each, bounds it: one column
+// at a time it took 8.1 us per step of the 16-lambda plate's solve, after which
+// the next product had to wait. LDS: (kCheckEvery (m + 2) + 2m) complex values.
+constexpr int kCheckEvery = 8;  // iterations between convergence checks on the host
+__device__ inline void rotate(double2 c, double2 s, double2 &hi, double2 &hn) {
+  // [hi; hn] <- [conj(c) hi + conj(s) hn; -s hi + c hn]
+  const double2 t0 = cconjmul_(c, hi), t1 = cconjmul_(s, hn);
+  const double2 u0 = cmul_(s, hi), u1 = cmul_(c, hn);
+  hi = make_double2(t0.x + t1.x, t0.y + t1.y);
+  hn = make_double2(u1.x - u0.x, u1.y - u0.y);
+}
 __global__ void __launch_bounds__(64)
-    k_givens(GmresDev d, const double2 *h1, const double2 *h2, const double *nrm, int j, int m,
-             int S) {
+    k_givens(GmresDev d, const double *nrm, int j0, int j1, int m, int S) {
   const int s = blockIdx.x;
   if (!d.active[s]) return;  // uniform over the work-group
   extern __shared__ double2 gsh[];
-  double2 *col = gsh, *cl = gsh + (m + 1), *sl = cl + m;
+  __shared__ int stop;
+  const int nc = j1 - j0, L = m + 2;  // rows of a column in LDS (odd stride for even m)
+  double2 *cl = gsh + kCheckEvery * L, *sl = cl + m;
   double2 *Hs = d.H + (int64_t)s * (m + 1) * m;
   double2 *cs = d.cs + (int64_t)s * m, *sn = d.sn + (int64_t)s * m;
-  for (int i = threadIdx.x; i <= j; i += 64) {
-    const double2 a = h1[(int64_t)i * S + s], b = h2[(int64_t)i * S + s];
-    col[i] = make_double2(a.x + b.x, a.y + b.y);
+  for (int c = 0; c < nc; ++c) {
+    for (int i = threadIdx.x; i <= j0 + c; i += 64) gsh[c * L + i] = Hs[i * m + j0 + c];
+    if (threadIdx.x == 0)
+      gsh[c * L + j0 + c + 1] = make_double2(sqrt(nrm[(int64_t)(j0 + c) * S + s]), 0.0);
   }
-  for (int i = threadIdx.x; i < j; i += 64) {
+  for (int i = threadIdx.x; i < j0; i += 64) {
     cl[i] = cs[i];
     sl[i] = sn[i];
   }
+  if (threadIdx.x == 0) stop = 0;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double2 *g = d.g + (int64_t)s * (m + 1);
-    const double2 hj1 = make_double2(sqrt(nrm[s]), 0.0);
-    for (int i = 0; i < j; ++i) {
-      const double2 hi = col[i], hn = col[i + 1];
-      // [hi; hn] <- [conj(c) hi + conj(s) hn; -s hi + c hn]
-      const double2 t0 = cconjmul_(cl[i], hi), t1 = cconjmul_(sl[i], hn);
-      const double2 u0 = cmul_(sl[i], hi), u1 = cmul_(cl[i], hn);
-      col[i] = make_double2(t0.x + t1.x, t0.y + t1.y);
-      col[i + 1] = make_double2(u1.x - u0.x, u1.y - u0.y);
+  const int c = threadIdx.x;
+  double2 *col = gsh + c * L;
+  if (c < nc)
+    for (int i = 0; i < j0; ++i) rotate(cl[i], sl[i], col[i], col[i + 1]);
+  int last = 0;  // columns completed
+  for (int t = 0; t < nc; ++t) {
+    const int j = j0 + t;
+    if (c == t) {
+      double2 *g = d.g + (int64_t)s * (m + 1);
+      const double2 a = col[j];
+      const double h1 = col[j + 1].x;  // |w|, untouched by the rotations before j
+      const double den = sqrt(a.x * a.x + a.y * a.y + h1 * h1);
+      const double2 rc = den == 0.0 ? make_double2(1.0, 0.0) : make_double2(a.x / den, a.y / den);
+      const double2 rs = den == 0.0 ? make_double2(0.0, 0.0) : make_double2(h1 / den, 0.0);
+      cs[j] = cl[j] = rc;
+      sn[j] = sl[j] = rs;
+      col[j] = make_double2(den, 0.0);
+      col[j + 1] = make_double2(0.0, 0.0);
+      const double2 gj = g[j];
+      const double2 gn = cmul_(rs, gj);
+      g[j + 1] = make_double2(-gn.x, -gn.y);
+      g[j] = cconjmul_(rc, gj);
+      d.its[s] += 1;
+      d.jend[s] = j + 1;
+      const double res = sqrt(gn.x * gn.x + gn.y * gn.y);
+      if (res <= d.tol_abs[s] || den == 0.0) {
+        d.active[s] = 0;
+        stop = 1;
+      }
     }
-    const double2 a = col[j];
-    const double den = sqrt(a.x * a.x + a.y * a.y + hj1.x * hj1.x);
-    double2 c, sv;
-    if (den == 0.0) {
-      c = make_double2(1.0, 0.0);
-      sv = make_double2(0.0, 0.0);
-    } else {
-      c = make_double2(a.x / den, a.y / den);
-      sv = make_double2(hj1.x / den, 0.0);
-    }
-    cs[j] = c;
-    sn[j] = sv;
-    col[j] = make_double2(den, 0.0);
-    col[j + 1] = make_double2(0.0, 0.0);
-    const double2 gj = g[j];
-    const double2 gn = cmul_(sv, gj);
-    g[j + 1] = make_double2(-gn.x, -gn.y);
-    g[j] = cconjmul_(c, gj);
-    d.its[s] += 1;
-    d.jend[s] = j + 1;
-    const double res = sqrt(gn.x * gn.x + gn.y * gn.y);
-    if (res <= d.tol_abs[s] || den == 0.0) d.active[s] = 0;
+    __syncthreads();
+    last = t + 1;
+    if (stop) break;
+    if (c > t && c < nc) rotate(cl[j], sl[j], col[j], col[j + 1]);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i <= j + 1; i += 64) Hs[i * m + j] = col[i];
+  for (int q = 0; q < last; ++q)
+    for (int i = threadIdx.x; i <= j0 + q + 1; i += 64) Hs[i * m + j0 + q] = gsh[q * L + i];
 }
 
 // y = H^-1 g on the jend x jend upper triangle (y stored [i][s] like h); one
@@ -413,14 +509,13 @@ struct Work {
   double2 *V = nullptr;  // (m+1) x R x ld
   double2 *z = nullptr, *w = nullptr;
   double2 *h1 = nullptr, *h2 = nullptr, *y = nullptr;
-  double *nrm = nullptr;
+  double *nrm = nullptr;       // per system
+  double *step_nrm = nullptr;  // [m][S]: |w|^2 of each Arnoldi step
   double2 *part = nullptr;  // dot-product partials [(m+1) S][np_stride]
   int64_t np_stride = 0;
   double *npart = nullptr;  // norm partials [S][kNormParts]
   GmresDev dev{};
 };
-
-constexpr int kCheckEvery = 8;  // iterations between convergence checks on the host
 
 }  // namespace
 
@@ -475,8 +570,9 @@ SolverState &solver_state(Plan *pl, int R, int m) {
   wk.h2 = (double2 *)alloc(sizeof(double2) * (size_t)(m + 1) * S);
   wk.y = (double2 *)alloc(sizeof(double2) * (size_t)(m + 1) * S);
   wk.nrm = (double *)alloc(sizeof(double) * S);
+  wk.step_nrm = (double *)alloc(sizeof(double) * (size_t)m * S);
   wk.np_stride = 0;
-  for (auto &md : pl->mesh) wk.np_stride = std::max(wk.np_stride, dot_parts(md.hp.n));
+  for (auto &md : pl->mesh) wk.np_stride = std::max(wk.np_stride, basis_groups(md.hp.n, R));
   wk.part = (double2 *)alloc(sizeof(double2) * (size_t)(m + 1) * S * wk.np_stride);
   wk.npart = (double *)alloc(sizeof(double) * (size_t)S * kNormParts);
   wk.dev.H = (double2 *)alloc(sizeof(double2) * (size_t)S * (m + 1) * m);
@@ -499,7 +595,7 @@ SolverState &solver_state(Plan *pl, int R, int m) {
 }
 
 // One Arnoldi step j of every system: w = A D^-1 V[j], two classical
-// Gram-Schmidt passes, V[j+1] = w / |w|, Hessenberg column j and rotation.
+// Gram-Schmidt passes, V[j+1] = w / |w|, Hessenberg column j.
 void arnoldi_step(Ctx &c, aim_precision prec, Work &wk, int j, int m) {
   const int S = c.S, R = c.R;
   const int64_t ld = c.ld, vstride = (int64_t)R * ld;
@@ -509,46 +605,57 @@ void arnoldi_step(Ctx &c, aim_precision prec, Work &wk, int j, int m) {
     LAUNCHCHECK();
   }
   apply(c, prec, wk.z, wk.w);
-  for (int pass = 0; pass < 2; ++pass) {
-    double2 *h = pass == 0 ? wk.h1 : wk.h2;
-    int mi = 0;
-    for (auto &md : c.pl->mesh) {
-      if (!c.mesh_on(mi)) {
-        ++mi;
-        continue;
-      }
-      const int64_t nb = dot_parts(md.hp.n) / kDotWaves;
-      hipLaunchKernelGGL(k_dots_part, dim3((unsigned)nb, R, nblk(j + 1, kGroup)),
-                         dim3(64 * kDotWaves), 0, c.s, wk.V, wk.w, ld, vstride, md.offset,
-                         md.offset + md.hp.n, j + 1, mi * R, S, wk.np_stride, wk.part);
-      LAUNCHCHECK();
-      hipLaunchKernelGGL(k_part_reduce, dim3(j + 1, R), dim3(64), 0, c.s, wk.part, wk.np_stride,
-                         (int)(nb * kDotWaves), mi * R, S, h);
-      LAUNCHCHECK();
-      hipLaunchKernelGGL(k_sub_basis, dim3(nblk(md.hp.n, 256), R), dim3(256), 0, c.s, wk.V, wk.w,
-                         ld, vstride, md.offset, md.offset + md.hp.n, j + 1, mi * R, S, h);
-      LAUNCHCHECK();
-      ++mi;
-    }
-  }
   int mi = 0;
   for (auto &md : c.pl->mesh) {
     if (!c.mesh_on(mi)) {
       ++mi;
       continue;
     }
-    const unsigned nb = red_blocks(md.hp.n);
-    hipLaunchKernelGGL(k_norm2_part, dim3(nb, R), dim3(kRed), 0, c.s, wk.w, ld, md.offset,
-                       md.offset + md.hp.n, mi * R, wk.npart);
-    LAUNCHCHECK();
-    hipLaunchKernelGGL(k_normalize_next, dim3(nblk(md.hp.n, 256), R), dim3(256), 0, c.s, wk.w,
-                       wk.V + (j + 1) * vstride, wk.z, c.dinv, ld, md.offset, md.offset + md.hp.n,
-                       mi * R, wk.npart, (int)nb, wk.nrm);
+    const int64_t n = md.hp.n;
+    const int nb = (int)basis_groups(n, R), nv = j + 1, sys0 = mi * R;
+    auto pass = [&](auto kern, const double2 *h) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)nb, R), dim3(256), 0, c.s, wk.V, wk.w, ld, vstride,
+                         md.offset, n, nv, sys0, S, h, wk.np_stride, wk.part, wk.npart);
+      LAUNCHCHECK();
+    };
+    auto reduce = [&](double2 *h, const double2 *add) {
+      hipLaunchKernelGGL(k_part_reduce, dim3(nv, R), dim3(64), 0, c.s, wk.part, wk.np_stride, nb,
+                         sys0, S, h, add, wk.dev.H, m, j);
+      LAUNCHCHECK();
+    };
+    // slots: the smallest tile that holds the nv vectors
+    auto passes = [&](auto slots_, auto rp_) {
+      constexpr int SL = decltype(slots_)::value, RP = decltype(rp_)::value;
+      pass(k_basis_pass<SL, RP, false, true, false>, nullptr);
+      reduce(wk.h1, nullptr);
+      pass(k_basis_pass<SL, RP, true, true, false>, wk.h1);
+      reduce(wk.h2, wk.h1);
+      pass(k_basis_pass<SL, RP, true, false, true>, wk.h2);
+    };
+    if (nv <= 16)
+      passes(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+    else if (nv <= 32)
+      passes(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    else if (nv <= 64)
+      passes(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+    else if (nv <= 112)
+      passes(std::integral_constant<int, 7>{}, std::integral_constant<int, 4>{});
+    else
+      passes(std::integral_constant<int, 13>{}, std::integral_constant<int, 2>{});
+    hipLaunchKernelGGL(k_normalize_next, dim3(nblk(n, 256), R), dim3(256), 0, c.s, wk.w,
+                       wk.V + (j + 1) * vstride, wk.z, c.dinv, ld, md.offset, md.offset + n, sys0,
+                       wk.npart, nb, wk.step_nrm + (int64_t)j * S);
     LAUNCHCHECK();
     ++mi;
   }
-  hipLaunchKernelGGL(k_givens, dim3(S), dim3(64), sizeof(double2) * (3 * (size_t)m + 1), c.s,
-                     wk.dev, wk.h1, wk.h2, wk.nrm, j, m, S);
+}
+
+// Steps j0 .. j1-1 and their columns' rotations.
+void arnoldi_segment(Ctx &c, aim_precision prec, Work &wk, int j0, int j1, int m) {
+  for (int j = j0; j < j1; ++j) arnoldi_step(c, prec, wk, j, m);
+  hipLaunchKernelGGL(k_givens, dim3(c.S), dim3(64),
+                     sizeof(double2) * (kCheckEvery * ((size_t)m + 2) + 2 * (size_t)m), c.s, wk.dev,
+                     wk.step_nrm, j0, j1, m, c.S);
   LAUNCHCHECK();
 }
 
@@ -567,7 +674,7 @@ void run_segment_graph(Plan *pl, SolverState &st, Ctx &c, aim_precision prec, in
     HIPCHECK(hipStreamBeginCapture(c.s, hipStreamCaptureModeThreadLocal));
     hipGraph_t g = nullptr;
     try {
-      for (int j = j0; j < j1; ++j) arnoldi_step(c, prec, st.wk, j, st.m);
+      arnoldi_segment(c, prec, st.wk, j0, j1, st.m);
     } catch (...) {
       (void)hipStreamEndCapture(c.s, &g);
       if (g) (void)hipGraphDestroy(g);
@@ -675,7 +782,7 @@ int gmres_run(Ctx &c, SolverState &st, aim_precision prec, bool graphs, const do
       if (graphs && whole && st.warm[pi]) {
         run_segment_graph(c.pl, st, c, prec, j, j1);
       } else {
-        for (int jj = j; jj < j1; ++jj) arnoldi_step(c, prec, wk, jj, m);
+        arnoldi_segment(c, prec, wk, j, j1, m);
         st.warm[pi] = true;
       }
       nprod += j1 - j;
