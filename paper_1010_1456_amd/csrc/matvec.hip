@@ -8,6 +8,7 @@
 // wider type than the arithmetic (c128 Krylov vectors feeding the c64
 // operator): the narrowing happens in registers as x is read.
 #include <algorithm>
+#include <type_traits>
 
 #include "aim_internal.h"
 #include "fft_map.h"
@@ -153,54 +154,108 @@ __global__ void k_unblock(const cx<T> *__restrict__ in, cx<T> *__restrict__ out,
   out[t] = in[f * fstride + ((int64_t)(kz / blk) * Nx + x) * Py * blk + (int64_t)ky * blk + kz % blk];
 }
 
+// Sum over the 16 lanes of a row (every lane gets it), by lane permutations
+// within the row (DPP: quad swaps, then mirrors of 8 and 16 lanes).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
 template <typename V>
-__device__ __forceinline__ V half_wave_sum(V v) {
-#pragma unroll
-  for (int off = 16; off > 0; off >>= 1) {
-    v.x += __shfl_xor(v.x, off, 32);
-    v.y += __shfl_xor(v.y, off, 32);
-  }
+__device__ __forceinline__ V row_sum(V v) {
+  v.x += dpp<0xB1>(v.x), v.y += dpp<0xB1>(v.y);    // lane ^ 1
+  v.x += dpp<0x4E>(v.x), v.y += dpp<0x4E>(v.y);    // lane ^ 2
+  v.x += dpp<0x141>(v.x), v.y += dpp<0x141>(v.y);  // 7 - lane of 8
+  v.x += dpp<0x140>(v.x), v.y += dpp<0x140>(v.y);  // 15 - lane of 16
   return v;
 }
 
 // y_m = j k eta [sum_{q<3} Lambda_mq . phi_q - k^-2 Lambda_md . phi_d]
-//       + sum_n Z^near_mn x_n. One 32-lane half-wave per row m.
-constexpr int kNearUnroll = 4;
+//       + sum_n Z^near_mn x_n.
+//
+// 16 lanes per row m, four rows per wave. Bound by the latency of its chain of
+// loads, so the chain is kept short: row pointer, anchor and stencil offsets;
+// then the near entries' columns and values, the stencil weights and the fields,
+// all in flight together; then x at the columns. kNearUnroll entries per lane
+// cover rows of up to 96 entries (the benchmark meshes have 72 to 81) in one
+// pass, kStencilUnroll nodes per lane the 9 or 27 nodes of second order. With 32
+// lanes per row (a last pass mostly idle, two rows per wave) and the stencil's
+// chain before the near zone's, the 128-lambda plate took 1.21 ms (4.20 GB, 3.5
+// TB/s) and now takes 0.83 (5.1 TB/s, the rate of a copy); the 8-lambda CFIE
+// sphere 95 -> 87 us, third order with 3 right-hand sides in FP64 (2.7-lambda
+// sphere, formerly one at a time) 99 -> 55 us.
+constexpr int kRowLanes = 16;
+constexpr int kNearUnroll = 6;
+constexpr int kStencilUnroll = 2;
 
-// RB right-hand sides per grid row (blockIdx.y): the stencil weights, the
+// RB right-hand sides from r_first + RB blockIdx.y: the stencil weights, the
 // near-zone entries and their columns are loaded once for the RB products.
 // CF (combined field): y^far = keta j [sum_q Lambda_q^T phi_q - inv_k2
 // Lambda_d^T phi_d] - eta_h sum_e W_e^T phi_e, with keta = alpha k eta and
 // eta_h = (1 - alpha) eta; the curl weights W test the vector potential's curl.
 template <typename T, typename TX, typename TY, int RB, bool CF>
 __global__ void __launch_bounds__(256)
-    k_interp_near(const cx<T> *__restrict__ phi, int64_t nf, int nrhs, const T *__restrict__ lam,
-                  const T *__restrict__ curl, const int32_t *__restrict__ anchor_lin,
-                  const int32_t *__restrict__ soff, int K, const int32_t *__restrict__ rowptr,
-                  const int32_t *__restrict__ cols, const cx<T> *__restrict__ nearv,
-                  const cx<TX> *__restrict__ x, int64_t ldx, cx<TY> *__restrict__ y, int64_t ldy,
-                  int64_t n, T keta, T inv_k2, T eta_h) {
+    k_interp_near(const cx<T> *__restrict__ phi, int64_t nf, int r_first,
+                  const T *__restrict__ lam, const T *__restrict__ curl,
+                  const int32_t *__restrict__ anchor_lin, const int32_t *__restrict__ soff, int K,
+                  const int32_t *__restrict__ rowptr, const int32_t *__restrict__ cols,
+                  const cx<T> *__restrict__ nearv, const cx<TX> *__restrict__ x, int64_t ldx,
+                  cx<TY> *__restrict__ y, int64_t ldy, int64_t n, T keta, T inv_k2, T eta_h) {
   using V = cx<T>;
-  const int lane = threadIdx.x & 31;
-  const int64_t m = (int64_t)blockIdx.x * (blockDim.x >> 5) + (threadIdx.x >> 5);
-  if (m >= n) return;  // both rows of a wave exit together or each half runs alone
+  constexpr int NU = kNearUnroll, SU = kStencilUnroll;
+  const int lane = threadIdx.x & (kRowLanes - 1);
+  const int64_t m = (int64_t)blockIdx.x * (256 / kRowLanes) + threadIdx.x / kRowLanes;
+  if (m >= n) return;  // whole rows exit
+  int so[SU];
+#pragma unroll
+  for (int k = 0; k < SU; ++k) so[k] = lane + kRowLanes * k < K ? soff[lane + kRowLanes * k] : 0;
   const int64_t a = anchor_lin[m];
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
-  const int r0 = blockIdx.y * RB;  // first right-hand side of this row
+  const int r0 = r_first + blockIdx.y * RB;  // first right-hand side of this row
   V far[RB], nr[RB], fk[RB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
     far[rb].x = far[rb].y = nr[rb].x = nr[rb].y = fk[rb].x = fk[rb].y = 0;
-  for (int u = lane; u < K; u += 32) {
-    const int64_t o = a + soff[u];
-    const T l0 = lam[(m * 4 + 0) * K + u], l1 = lam[(m * 4 + 1) * K + u];
-    const T l2 = lam[(m * 4 + 2) * K + u], l3 = lam[(m * 4 + 3) * K + u];
-    T w0 = 0, w1 = 0, w2 = 0;
-    if (CF) {
-      w0 = curl[(m * 3 + 0) * K + u];
-      w1 = curl[(m * 3 + 1) * K + u];
-      w2 = curl[(m * 3 + 2) * K + u];
+  V z[NU];
+  int c[NU];
+  auto load_near = [&](int eb) {  // entries eb, eb + 16, ... of this lane
+#pragma unroll
+    for (int k = 0; k < NU; ++k) c[k] = eb + kRowLanes * k < e1 ? cols[eb + kRowLanes * k] : -1;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+      if (eb + kRowLanes * k < e1) {
+        z[k] = nearv[eb + kRowLanes * k];
+      } else {
+        z[k].x = 0;
+        z[k].y = 0;
+      }
     }
+  };
+  auto add_near = [&]() {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const cx<TX> *xr = x + (int64_t)(r0 + rb) * ldx;
+      cx<TX> xv[NU];
+#pragma unroll
+      for (int k = 0; k < NU; ++k) {
+        if (c[k] >= 0)
+          xv[k] = xr[c[k]];
+        else
+          xv[k].x = xv[k].y = 0;
+      }
+#pragma unroll
+      for (int k = 0; k < NU; ++k) {
+        const T xa = (T)xv[k].x, xb = (T)xv[k].y;
+        nr[rb].x += z[k].x * xa - z[k].y * xb;
+        nr[rb].y += z[k].x * xb + z[k].y * xa;
+      }
+    }
+  };
+  auto far_node = [&](int64_t o, T l0, T l1, T l2, T l3, T w0, T w1, T w2) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const V *ph = phi + o * nf + (r0 + rb) * 4;  // fields interleaved per node
@@ -212,35 +267,34 @@ __global__ void __launch_bounds__(256)
         fk[rb].y += w0 * p0.y + w1 * p1.y + w2 * p2.y;
       }
     }
+  };
+  const T *lm = lam + m * 4 * K, *wm = CF ? curl + m * 3 * K : nullptr;
+  load_near(e0 + lane);
+  for (int u0 = lane; u0 < K; u0 += kRowLanes * SU) {
+    T l[SU][4], w[SU][3];
+#pragma unroll
+    for (int k = 0; k < SU; ++k) {
+      const int u = u0 + kRowLanes * k;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) l[k][q] = u < K ? lm[q * K + u] : (T)0;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) w[k][q] = (CF && u < K) ? wm[q * K + u] : (T)0;
+    }
+#pragma unroll
+    for (int k = 0; k < SU; ++k)
+      if (u0 + kRowLanes * k < K)
+        far_node(a + so[k], l[k][0], l[k][1], l[k][2], l[k][3], w[k][0], w[k][1], w[k][2]);
+    if (u0 + kRowLanes * SU < K)  // the next nodes (orders above 2)
+#pragma unroll
+      for (int k = 0; k < SU; ++k) {
+        const int u = u0 + kRowLanes * (SU + k);
+        so[k] = u < K ? soff[u] : 0;
+      }
   }
-  // kNearUnroll entries per lane per pass, all gathers issued before any is
-  // used (rows hold ~80 entries: one pass of dependent loads, not three)
-  for (int eb = e0 + lane; eb < e1; eb += 32 * kNearUnroll) {
-    V z[kNearUnroll];
-    int c[kNearUnroll];
-#pragma unroll
-    for (int k = 0; k < kNearUnroll; ++k) {
-      const int e = eb + 32 * k;
-      const bool in = e < e1;
-      c[k] = in ? cols[e] : 0;
-      if (in) {
-        z[k] = nearv[e];
-      } else {
-        z[k].x = 0;
-        z[k].y = 0;
-      }
-    }
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const cx<TX> *xr = x + (int64_t)(r0 + rb) * ldx;
-#pragma unroll
-      for (int k = 0; k < kNearUnroll; ++k) {
-        const cx<TX> xv = xr[c[k]];
-        const T xa = (T)xv.x, xb = (T)xv.y;
-        nr[rb].x += z[k].x * xa - z[k].y * xb;
-        nr[rb].y += z[k].x * xb + z[k].y * xa;
-      }
-    }
+  add_near();
+  for (int eb = e0 + lane + kRowLanes * NU; eb < e1; eb += kRowLanes * NU) {
+    load_near(eb);
+    add_near();
   }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -251,7 +305,7 @@ __global__ void __launch_bounds__(256)
       acc.x -= eta_h * fk[rb].x;
       acc.y -= eta_h * fk[rb].y;
     }
-    acc = half_wave_sum(acc);
+    acc = row_sum(acc);
     if (lane == 0) {
       cx<TY> out;
       out.x = (decltype(out.x))acc.x;
@@ -657,35 +711,34 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
   const cx<T> *phi = (const cx<T> *)pl->work[md.lane][prec][0];
   const bool plane = md.planar_z >= 0;  // fields on the scatterer's grid plane only
   const int64_t nf = 4 * (int64_t)nrhs;  // fields per node of the interleaved grid
-  const int rows_per_block = 8;
-  const int64_t blocks = (h.n + rows_per_block - 1) / rows_per_block;
-  // right-hand sides per grid row: 4 or 2 when they divide nrhs
-  const int rb = nrhs % 4 == 0 ? 4 : (nrhs % 2 == 0 ? 2 : 1);
+  const int64_t blocks = (h.n + 256 / kRowLanes - 1) / (256 / kRowLanes);
   const bool cf = h.cfie;
   if (cf && (plane || !curl_of<T>(md))) throw Error(AIM_ERR_STATE, "combined field without curl weights");
-  auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, nrhs / rb), dim3(32 * rows_per_block), 0, s,
-                       phi, nf, nrhs, plane ? plane_lam_of<T>(md) : lam_of<T>(md),
-                       cf ? curl_of<T>(md) : nullptr, plane ? md.plane_anchor : md.anchor_lin,
+  // right-hand sides in groups of 4, then the 1 to 3 left over in one group
+  auto launch = [&](auto kern, int r_first, int groups) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, groups), dim3(256), 0, s, phi, nf, r_first,
+                       plane ? plane_lam_of<T>(md) : lam_of<T>(md), cf ? curl_of<T>(md) : nullptr,
+                       plane ? md.plane_anchor : md.anchor_lin,
                        plane ? md.plane_soff : md.stencil_off, plane ? md.plane_K : h.K,
                        md.rowptr, md.cols, near_of<T>(md), x, ldx, y, ldy, h.n,
                        (T)(h.alpha * h.k * kEta0), (T)(1.0 / (h.k * h.k)),
                        (T)((1.0 - h.alpha) * kEta0));
   };
-  if (cf) {
-    if (rb == 4)
-      launch(k_interp_near<T, TX, TY, 4, true>);
-    else if (rb == 2)
-      launch(k_interp_near<T, TX, TY, 2, true>);
-    else
-      launch(k_interp_near<T, TX, TY, 1, true>);
-  } else if (rb == 4) {
-    launch(k_interp_near<T, TX, TY, 4, false>);
-  } else if (rb == 2) {
-    launch(k_interp_near<T, TX, TY, 2, false>);
-  } else {
-    launch(k_interp_near<T, TX, TY, 1, false>);
-  }
+  auto groups = [&](auto cf_) {
+    constexpr bool CF = decltype(cf_)::value;
+    const int left = nrhs % 4, r_left = nrhs - left;
+    if (r_left > 0) launch(k_interp_near<T, TX, TY, 4, CF>, 0, r_left / 4);
+    if (left == 3)
+      launch(k_interp_near<T, TX, TY, 3, CF>, r_left, 1);
+    else if (left == 2)
+      launch(k_interp_near<T, TX, TY, 2, CF>, r_left, 1);
+    else if (left == 1)
+      launch(k_interp_near<T, TX, TY, 1, CF>, r_left, 1);
+  };
+  if (cf)
+    groups(std::true_type{});
+  else
+    groups(std::false_type{});
   LAUNCHCHECK();
   if (ev) HIPCHECK(hipEventRecord(ev[7], s));
 }

@@ -1,0 +1,61 @@
+"""The interpolation and near-zone kernel where its shapes change: right-hand
+sides in groups of 4 and the 1 to 3 left over, rows longer than one pass of 96
+entries, stencils of up to 216 nodes, row counts that are no multiple of a
+work-group's 16, in both arithmetics, against the oracle: relative 1e-12 in FP64,
+2e-5 in c64, and the c128-vector form of the c64 product equal to it bit for bit
+on c64-valued input."""
+
+import functools
+
+import numpy as np
+import pytest
+
+from oracle import aim as oaim
+from oracle.constants import wavenumber
+from oracle.rwg import build_rwg
+from workloads import plate_mesh, random_current, sphere_mesh
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FREQ = 0.3e9
+
+CASES = {
+    "plate": (lambda: plate_mesh(1.0, FREQ), 2, 0.3, None),
+    "sphere_long_rows": (lambda: sphere_mesh(0.5, FREQ, nf=4), 2, 0.5, 0.6),
+    "plate_long_rows": (lambda: plate_mesh(1.0, FREQ, jitter_seed=2), 1, 0.8, None),
+    "sphere_m3": (lambda: sphere_mesh(0.4, FREQ, nf=3), 3, 0.3, 0.6),
+    "sphere_m5": (lambda: sphere_mesh(0.4, FREQ, nf=3), 5, 0.3, None),
+}
+
+
+@functools.lru_cache(maxsize=None)
+def _problem(name):
+    from paper_1010_1456_amd import aim as A
+
+    make, order, radius, alpha = CASES[name]
+    m = make()
+    kw = {} if alpha is None else {"cfie_alpha": alpha}
+    op = oaim.build_operator(build_rwg(m.verts, m.tris), wavenumber(FREQ), 0.1 * m.lam, order,
+                             radius * m.lam, **kw)
+    return op, A.Plan([(m.verts, m.tris, FREQ)], order=order, near_radius_lambda=radius, **kw)
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("name", list(CASES))
+def test_product(name, nrhs):
+    from paper_1010_1456_amd import aim as A
+
+    op, plan = _problem(name)
+    x = random_current(plan.n_total, nrhs=nrhs, seed=nrhs).astype(np.complex64).astype(np.complex128)
+    ref = oaim.matvec_fft(op, x)
+    xt = torch.from_numpy(x).cuda()
+    y64 = plan.matvec(xt, A.AIM_FP64).cpu().numpy()
+    y32 = plan.matvec(xt.to(torch.complex64), A.AIM_MIXED)
+    yio = plan.matvec(xt, A.AIM_MIXED_IO64)
+    for r in range(nrhs):
+        nr = np.linalg.norm(ref[r])
+        assert np.linalg.norm(y64[r] - ref[r]) <= 1e-12 * nr, r
+        assert np.linalg.norm(y32[r].cpu().numpy() - ref[r]) <= 2e-5 * nr, r
+    assert torch.equal(yio.to(torch.complex64), y32)
