@@ -168,7 +168,6 @@ struct MeshDev {
   // the projection restricted to that plane (plane node p = x Ny + y):
   // node-ordered entries (ent_col, lamT shared), in-plane stencils of
   // (M+1)^2 weights, plane-linear anchors and stencil offsets
-  int32_t *plane_node_ptr = nullptr;  // Nx Ny + 1
   int64_t n_plane_occ = 0;            // occupied plane nodes and their entry ranges
   int32_t *plane_occ = nullptr;
   int32_t *plane_occ_ptr = nullptr;
@@ -220,6 +219,8 @@ struct Plan;
 // Device memory through the plan's allocator.
 void *dev_alloc(Plan *pl, size_t bytes);
 void dev_free(Plan *pl, void *p);
+// grid size of a launch of count threads, t per work-group
+inline unsigned launch_blocks(int64_t count, int t) { return (unsigned)((count + t - 1) / t); }
 
 struct Plan {
   int device = 0;  // HIP device the plan was set up on
@@ -253,6 +254,9 @@ void solver_release(Plan *pl);
 
 // set-up kernels (setup_kernels.hip)
 void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s);
+// node-ordered projection and the tables of occupied nodes and lines
+// (node_tables.hip), from Lambda, the curl weights and the anchors
+void node_tables_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 // near-zone matrix Z^MOM - Z^grid and the diagonal of Z^MOM (near_fill.hip);
 // area, anchor3: device, per triangle and 3 per basis
 void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *anchor3,

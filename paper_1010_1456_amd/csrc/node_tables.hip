@@ -1,0 +1,324 @@
+// Set-up tables by grid node: the transposed (node-ordered) projection that the
+// gather form of anterpolation walks, and the occupied nodes and z lines that the
+// product's passes are pruned to. All built on the GPU: a histogram of the
+// non-zero stencil weights by node, scans, and a counting sort whose lists are
+// then ordered, so that the tables do not depend on the order of the atomics. On
+// the host (one thread, after copying the weights' mask back) they took 53 ms on
+// the 8-lambda sphere and 345 ms on the 128-lambda plate.
+#include <algorithm>
+
+#include "aim_internal.h"
+
+namespace aim {
+
+namespace {
+
+__global__ void k_clear(int32_t *p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+// whether basis b has any non-zero weight at its stencil node u: projection or,
+// for the combined field, curl weight (the node is then read by the
+// interpolation even where its projection weights vanish, as off a flat face
+// lying in a grid plane)
+__device__ inline bool weighs(const double *lam, const double *curl, int64_t b, int u, int K) {
+  bool nz = false;
+  for (int q = 0; q < 4; ++q) nz |= lam[(b * 4 + q) * K + u] != 0.0;
+  if (curl)
+    for (int e = 0; e < 3; ++e) nz |= curl[(b * 3 + e) * K + u] != 0.0;
+  return nz;
+}
+
+// count[v]: non-zero (basis, stencil node) weights at grid node v
+__global__ void k_count(const double *lam, const double *curl, const int32_t *anchor_lin,
+                        const int32_t *soff, int64_t n, int K, int32_t *count) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n * K) return;
+  const int64_t b = t / K;
+  const int u = (int)(t - b * K);
+  if (weighs(lam, curl, b, u, K)) atomicAdd(&count[anchor_lin[b] + soff[u]], 1);
+}
+
+// the entries into their nodes' ranges, cursor[v] the next free place of node v
+__global__ void k_fill(const double *lam, const double *curl, const int32_t *anchor_lin,
+                       const int32_t *soff, int64_t n, int K, int32_t *cursor, int32_t *src) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n * K) return;
+  const int64_t b = t / K;
+  const int u = (int)(t - b * K);
+  if (weighs(lam, curl, b, u, K)) src[atomicAdd(&cursor[anchor_lin[b] + soff[u]], 1)] = (int32_t)t;
+}
+
+// each occupied node's entries in increasing order (basis, then stencil node):
+// lists of some tens, a thread each
+__global__ void k_order(const int32_t *occ_ptr, int64_t n_occ, int32_t *src) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n_occ) return;
+  const int e0 = occ_ptr[i], e1 = occ_ptr[i + 1];
+  for (int e = e0 + 1; e < e1; ++e) {
+    const int32_t v = src[e];
+    int p = e;
+    while (p > e0 && src[p - 1] > v) {
+      src[p] = src[p - 1];
+      --p;
+    }
+    src[p] = v;
+  }
+}
+
+// entry e with src[e] = b K + u: its basis b and lamT[e][q] = Lambda[b][q][u]
+__global__ void k_lam_transpose(const double *lam, const int32_t *src, int64_t ne, int K,
+                                int32_t *col, double *lamT64, float *lamT32) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= ne) return;
+  const int b = src[e] / K, u = src[e] - b * K;
+  col[e] = b;
+  for (int q = 0; q < 4; ++q) {
+    const double v = lam[((int64_t)b * 4 + q) * K + u];
+    lamT64[e * 4 + q] = v;
+    if (lamT32) lamT32[e * 4 + q] = (float)v;
+  }
+}
+
+// Exclusive scan of (value, 1 if value > 0) pairs, packed into 64 bits (sums in
+// the low word, occupied counts in the high one): per block of kScanItems items,
+// then the blocks' totals in one work-group, then written out by the callers.
+constexpr int kScanThreads = 256, kScanPer = 8, kScanItems = kScanThreads * kScanPer;
+__device__ inline uint64_t packed(int32_t v) {
+  return (uint64_t)(uint32_t)v | (v > 0 ? 1ull << 32 : 0);
+}
+__device__ inline uint64_t block_exclusive(uint64_t mine, uint64_t *total) {
+  __shared__ uint64_t ws[kScanThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t scan = mine;
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint64_t o = __shfl_up((unsigned long long)scan, off, 64);
+    if (lane >= off) scan += o;
+  }
+  __syncthreads();
+  if (lane == 63) ws[wave] = scan;
+  __syncthreads();
+  uint64_t before = 0, all = 0;
+  for (int w = 0; w < kScanThreads / 64; ++w) {
+    if (w < wave) before += ws[w];
+    all += ws[w];
+  }
+  *total = all;
+  return before + scan - mine;
+}
+__global__ void __launch_bounds__(kScanThreads)
+    k_scan_blocks(const int32_t *v, int64_t n, uint64_t *sums) {
+  const int64_t i0 = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
+  uint64_t mine = 0, total;
+  for (int k = 0; k < kScanPer; ++k)
+    if (i0 + k < n) mine += packed(v[i0 + k]);
+  (void)block_exclusive(mine, &total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+// sums[0 .. nb) to exclusive prefixes, sums[nb] the total
+__global__ void __launch_bounds__(kScanThreads) k_scan_sums(uint64_t *sums, int64_t nb) {
+  uint64_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += kScanThreads) {
+    const int64_t b = b0 + threadIdx.x;
+    uint64_t total;
+    const uint64_t ex = block_exclusive(b < nb ? sums[b] : 0, &total);
+    if (b < nb) sums[b] = carry + ex;
+    carry += total;
+  }
+  if (threadIdx.x == 0) sums[nb] = carry;
+}
+// applies f(i, value, exclusive sum, exclusive count of occupied items)
+template <class F>
+__device__ inline void scan_apply(const int32_t *v, int64_t n, const uint64_t *sums, F f) {
+  const int64_t i0 = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
+  int32_t x[kScanPer];
+  uint64_t mine = 0, total;
+  for (int k = 0; k < kScanPer; ++k) {
+    x[k] = i0 + k < n ? v[i0 + k] : 0;
+    mine += packed(x[k]);
+  }
+  uint64_t ex = sums[blockIdx.x] + block_exclusive(mine, &total);
+  for (int k = 0; k < kScanPer; ++k) {
+    if (i0 + k < n) f(i0 + k, x[k], (int32_t)(uint32_t)ex, (int32_t)(ex >> 32));
+    ex += packed(x[k]);
+  }
+}
+
+// node pointers, and the occupied nodes with their entry ranges; count becomes
+// the fill cursor
+__global__ void __launch_bounds__(kScanThreads)
+    k_nodes(int32_t *count, int64_t V0, const uint64_t *sums, int64_t nb, int32_t *node_ptr,
+            int32_t *occ, int32_t *occ_ptr) {
+  scan_apply(count, V0, sums, [&](int64_t v, int32_t c, int32_t e, int32_t i) {
+    node_ptr[v] = e;
+    count[v] = e;
+    if (c > 0) {
+      occ[i] = (int32_t)v;
+      occ_ptr[i] = e;
+    }
+  });
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    node_ptr[V0] = (int32_t)(uint32_t)sums[nb];
+    occ_ptr[sums[nb] >> 32] = (int32_t)(uint32_t)sums[nb];
+  }
+}
+
+// Per z line: whether it holds an occupied node, and {lo, g0, g1, hi}: its
+// occupied nodes lie in [lo, hi) outside the longest unoccupied run [g0, g1)
+// between them (a line through a closed surface crosses it twice)
+__global__ void k_line_ranges(const int32_t *node_ptr, int64_t lines, int Nz, int32_t *any,
+                              int32_t *range) {
+  const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (l >= lines) return;
+  int r0 = 0, r1 = 0, r2 = 0, r3 = 0;
+  bool some = false;
+  int e = node_ptr[l * Nz];
+  for (int z = 0; z < Nz; ++z) {
+    const int next = node_ptr[l * Nz + z + 1];
+    if (next > e) {
+      if (!some) {
+        r0 = z;
+        r1 = r2 = z + 1;
+        some = true;
+      } else if (z - r3 > r2 - r1) {  // a longer unoccupied run r3 .. z - 1
+        r1 = r3;
+        r2 = z;
+      }
+      r3 = z + 1;
+    }
+    e = next;
+  }
+  any[l] = some ? 1 : 0;
+  range[4 * l] = r0, range[4 * l + 1] = r1, range[4 * l + 2] = r2, range[4 * l + 3] = r3;
+}
+__global__ void __launch_bounds__(kScanThreads)
+    k_lines(const int32_t *any, int64_t lines, const uint64_t *sums, const int32_t *range,
+            int32_t *occ_lines, int32_t *zrange) {
+  scan_apply(any, lines, sums, [&](int64_t l, int32_t c, int32_t, int32_t i) {
+    if (c > 0) {
+      occ_lines[i] = (int32_t)l;
+      for (int q = 0; q < 4; ++q) zrange[4 * i + q] = range[4 * l + q];
+    }
+  });
+}
+// per x: the y range [lo, hi) of its occupied lines ([0, 0) if none); one wave
+__global__ void __launch_bounds__(64) k_yrange(const int32_t *any, int Ny, int32_t *yr) {
+  const int64_t x = blockIdx.x;
+  int lo = Ny, hi = 0;
+  for (int y = threadIdx.x; y < Ny; y += 64)
+    if (any[x * Ny + y]) {
+      lo = min(lo, y);
+      hi = max(hi, y + 1);
+    }
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off, 64));
+    hi = max(hi, __shfl_xor(hi, off, 64));
+  }
+  if (threadIdx.x == 0) {
+    yr[2 * x] = lo < hi ? lo : 0;
+    yr[2 * x + 1] = lo < hi ? hi : 0;
+  }
+}
+
+// the plane's occupied nodes x Ny + y from the grid's (all on one plane)
+__global__ void k_plane(const int32_t *occ, int64_t n_occ, int Nz, int32_t *plane_occ) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_occ) plane_occ[i] = occ[i] / Nz;
+}
+
+}  // namespace
+
+void node_tables_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
+  const HostPlan &h = md.hp;
+  const int64_t n = h.n, NK = n * h.K;
+  const int Nx = h.grid[0], Ny = h.grid[1], Nz = h.grid[2];
+  const int64_t A = (int64_t)Nx * Ny, V0 = A * Nz;
+  if (NK > INT32_MAX) throw Error(AIM_ERR_ARG, "projection too large for 32-bit indexing");
+  std::vector<void *> tmp;
+  auto scratch = [&](size_t bytes) {
+    void *p = dev_alloc(pl, bytes);
+    tmp.push_back(p);
+    return p;
+  };
+  auto scan_blocks = [](int64_t count) { return (count + kScanItems - 1) / kScanItems; };
+  uint64_t *sums = (uint64_t *)scratch(sizeof(uint64_t) * (scan_blocks(std::max(V0, A)) + 1));
+  // scans v[0 .. count); returns (sum, occupied items)
+  auto scan = [&](const int32_t *v, int64_t count) {
+    const int64_t nb = scan_blocks(count);
+    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kScanThreads), 0, s, v, count, sums);
+    LAUNCHCHECK();
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, sums, nb);
+    LAUNCHCHECK();
+    uint64_t total = 0;
+    HIPCHECK(hipMemcpyAsync(&total, sums + nb, sizeof(total), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipStreamSynchronize(s));
+    return std::make_pair((int64_t)(uint32_t)total, (int64_t)(total >> 32));
+  };
+  auto ints = [&](int64_t count) {
+    return (int32_t *)dev_alloc(pl, sizeof(int32_t) * (size_t)std::max<int64_t>(count, 1));
+  };
+
+  int32_t *count = (int32_t *)scratch(sizeof(int32_t) * V0);
+  hipLaunchKernelGGL(k_clear, dim3(launch_blocks(V0, 256)), dim3(256), 0, s, count, V0);
+  LAUNCHCHECK();
+  hipLaunchKernelGGL(k_count, dim3(launch_blocks(NK, 256)), dim3(256), 0, s, md.lam64, md.curl64,
+                     md.anchor_lin, md.stencil_off, n, h.K, count);
+  LAUNCHCHECK();
+  const auto nodes = scan(count, V0);
+  const int64_t ne = nodes.first;
+  md.n_entries = ne;
+  md.n_occ = nodes.second;
+  md.node_ptr = ints(V0 + 1);
+  md.occ = ints(md.n_occ);
+  md.occ_ptr = ints(md.n_occ + 1);
+  const int64_t vb = scan_blocks(V0);
+  hipLaunchKernelGGL(k_nodes, dim3((unsigned)vb), dim3(kScanThreads), 0, s, count, V0, sums, vb,
+                     md.node_ptr, md.occ, md.occ_ptr);
+  LAUNCHCHECK();
+  int32_t *src = (int32_t *)scratch(sizeof(int32_t) * std::max<int64_t>(ne, 1));
+  hipLaunchKernelGGL(k_fill, dim3(launch_blocks(NK, 256)), dim3(256), 0, s, md.lam64, md.curl64,
+                     md.anchor_lin, md.stencil_off, n, h.K, count, src);
+  LAUNCHCHECK();
+  md.ent_col = ints(ne);
+  md.lamT64 = (double *)dev_alloc(pl, sizeof(double) * 4 * std::max<int64_t>(ne, 1));
+  if (pl->mixed) md.lamT32 = (float *)dev_alloc(pl, sizeof(float) * 4 * std::max<int64_t>(ne, 1));
+  if (ne > 0) {
+    hipLaunchKernelGGL(k_order, dim3(launch_blocks(md.n_occ, 64)), dim3(64), 0, s, md.occ_ptr,
+                       md.n_occ, src);
+    LAUNCHCHECK();
+    hipLaunchKernelGGL(k_lam_transpose, dim3(launch_blocks(ne, 256)), dim3(256), 0, s, md.lam64,
+                       src, ne, h.K, md.ent_col, md.lamT64, md.lamT32);
+    LAUNCHCHECK();
+  }
+
+  int32_t *any = (int32_t *)scratch(sizeof(int32_t) * A);
+  int32_t *range = (int32_t *)scratch(sizeof(int32_t) * 4 * A);
+  hipLaunchKernelGGL(k_line_ranges, dim3(launch_blocks(A, 64)), dim3(64), 0, s, md.node_ptr, A, Nz,
+                     any, range);
+  LAUNCHCHECK();
+  md.n_occ_lines = scan(any, A).second;
+  md.occ_lines = ints(md.n_occ_lines);
+  md.occ_zrange = ints(4 * md.n_occ_lines);
+  hipLaunchKernelGGL(k_lines, dim3((unsigned)scan_blocks(A)), dim3(kScanThreads), 0, s, any, A,
+                     sums, range, md.occ_lines, md.occ_zrange);
+  LAUNCHCHECK();
+  md.occ_yrange = ints(2 * (int64_t)Nx);
+  hipLaunchKernelGGL(k_yrange, dim3((unsigned)Nx), dim3(64), 0, s, any, Ny, md.occ_yrange);
+  LAUNCHCHECK();
+
+  if (md.planar_z >= 0) {
+    md.n_plane_occ = md.n_occ;
+    md.plane_occ = ints(md.n_occ);
+    md.plane_occ_ptr = md.occ_ptr;  // the same entry ranges
+    if (md.n_occ > 0) {
+      hipLaunchKernelGGL(k_plane, dim3(launch_blocks(md.n_occ, 256)), dim3(256), 0, s, md.occ,
+                         md.n_occ, Nz, md.plane_occ);
+      LAUNCHCHECK();
+    }
+  }
+  HIPCHECK(hipStreamSynchronize(s));
+  for (void *p : tmp) dev_free(pl, p);
+}
+
+}  // namespace aim

@@ -104,38 +104,6 @@ __global__ void k_curl_projection(const int32_t *rwg, const double *len, const d
   curl[(b * 3 + 2) * K + u] = acc.z;
 }
 
-// 1 where a (basis, stencil node) pair has any non-zero weight: projection
-// or, for the combined field, curl weight (the node is then read by the
-// interpolation even where its projection weights vanish, as off a flat face
-// lying in a grid plane)
-__global__ void k_lam_mask(const double *lam, const double *curl, int64_t n, int K,
-                           uint8_t *mask) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * K) return;
-  const int64_t b = t / K;
-  const int u = (int)(t - b * K);
-  bool nz = false;
-  for (int q = 0; q < 4; ++q) nz |= lam[(b * 4 + q) * K + u] != 0.0;
-  if (curl)
-    for (int e = 0; e < 3; ++e) nz |= curl[(b * 3 + e) * K + u] != 0.0;
-  mask[t] = nz ? 1 : 0;
-}
-
-// lamT[e][q] = Lambda[src / K][q][src % K] for entry e with src = ent_src[e]
-__global__ void k_lam_transpose(const double *lam, const int32_t *ent_src, int64_t ne, int K,
-                                double *lamT64, float *lamT32) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= ne) return;
-  const int64_t src = ent_src[e];
-  const int64_t b = src / K;
-  const int u = (int)(src - b * K);
-  for (int q = 0; q < 4; ++q) {
-    const double v = lam[(b * 4 + q) * K + u];
-    lamT64[e * 4 + q] = v;
-    if (lamT32) lamT32[e * 4 + q] = (float)v;
-  }
-}
-
 __global__ void k_to_float(const double *in, float *out, int64_t n) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = (float)in[i];
@@ -159,20 +127,32 @@ __global__ void k_embed_green(double2 *out, int Px, int Py, int Pz, int Nx, int 
   out[t] = v;
 }
 
-// z range of the grid planes holding a non-zero projection weight
+// z range of the grid planes holding a non-zero projection weight (one atomic
+// per wave: one per weight, 1.5 M of them on the 4-lambda sphere, queued on the
+// two addresses for 0.54 ms)
 __global__ void k_lam_zrange(const double *lam, const int32_t *anchor3, int64_t n, int M,
                              int *zr) {
   const int K = (M + 1) * (M + 1) * (M + 1);
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * K) return;
-  const int64_t b = t / K;
-  const int u = (int)(t - b * K);
-  bool nz = false;
-  for (int q = 0; q < 4; ++q) nz |= lam[(b * 4 + q) * K + u] != 0.0;
-  if (!nz) return;
-  const int z = anchor3[3 * b + 2] + u % (M + 1);
-  atomicMin(&zr[0], z);
-  atomicMax(&zr[1], z);
+  int lo = INT32_MAX, hi = INT32_MIN;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n * K;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t b = t / K;
+    const int u = (int)(t - b * K);
+    bool nz = false;
+    for (int q = 0; q < 4; ++q) nz |= lam[(b * 4 + q) * K + u] != 0.0;
+    if (!nz) continue;
+    const int z = anchor3[3 * b + 2] + u % (M + 1);
+    lo = min(lo, z);
+    hi = max(hi, z);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off, 64));
+    hi = max(hi, __shfl_xor(hi, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0 && lo <= hi) {
+    atomicMin(&zr[0], lo);
+    atomicMax(&zr[1], hi);
+  }
 }
 
 // in-plane weights: plane_lam[b][q][ui (M+1) + uj] = lam[b][q][u] with u's
@@ -347,7 +327,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
   {
     int zr_h[2] = {INT32_MAX, INT32_MIN};
     int *zr = upload(pl, zr_h, 2, s);
-    hipLaunchKernelGGL(k_lam_zrange, dim3(blocks_for(n * K, 256)), dim3(256), 0, s, md.lam64,
+    hipLaunchKernelGGL(k_lam_zrange, dim3(std::min(blocks_for(n * K, 256), 2048)), dim3(256), 0, s, md.lam64,
                        anchor3, n, M, zr);
     LAUNCHCHECK();
     HIPCHECK(hipMemcpyAsync(zr_h, zr, sizeof(zr_h), hipMemcpyDeviceToHost, s));
@@ -376,115 +356,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     md.plane_K = K2;
   }
 
-  // node-ordered (transposed) projection for the gather form of anterpolation
-  {
-    const int64_t NK = n * K;
-    uint8_t *dmask = (uint8_t *)dev_alloc(pl, NK);
-    hipLaunchKernelGGL(k_lam_mask, dim3(blocks_for(NK, 256)), dim3(256), 0, s, md.lam64, md.curl64,
-                       n, K, dmask);
-    LAUNCHCHECK();
-    std::vector<uint8_t> mask(NK);
-    HIPCHECK(hipMemcpyAsync(mask.data(), dmask, NK, hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
-    dev_free(pl, dmask);
-    const int64_t V0 = (int64_t)h.grid[0] * h.grid[1] * h.grid[2];
-    std::vector<int32_t> ptr(V0 + 1, 0);
-    for (int64_t b = 0; b < n; ++b)
-      for (int u = 0; u < K; ++u)
-        if (mask[b * K + u]) ptr[alin[b] + soff[u] + 1]++;
-    for (int64_t v = 0; v < V0; ++v) ptr[v + 1] += ptr[v];
-    const int64_t ne = ptr[V0];
-    if (ne > INT32_MAX) throw Error(AIM_ERR_ARG, "projection too large for 32-bit indexing");
-    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1), col(std::max<int64_t>(ne, 1)),
-        src(std::max<int64_t>(ne, 1));
-    for (int64_t b = 0; b < n; ++b)  // entries of a node in (basis, node) order
-      for (int u = 0; u < K; ++u)
-        if (mask[b * K + u]) {
-          const int32_t e = fill[alin[b] + soff[u]]++;
-          col[e] = (int32_t)b;
-          src[e] = (int32_t)(b * K + u);
-        }
-    md.n_entries = ne;
-    md.node_ptr = upload(pl, ptr.data(), ptr.size(), s);
-    {
-      std::vector<int32_t> occ, optr;
-      for (int64_t v = 0; v < V0; ++v)
-        if (ptr[v + 1] > ptr[v]) {
-          occ.push_back((int32_t)v);
-          optr.push_back(ptr[v]);
-        }
-      optr.push_back(ptr[V0]);
-      std::vector<int32_t> lines;
-      for (int32_t v : occ)
-        if (lines.empty() || lines.back() != v / h.grid[2]) lines.push_back(v / h.grid[2]);
-      md.n_occ = (int64_t)occ.size();
-      md.n_occ_lines = (int64_t)lines.size();
-      if (occ.empty()) occ.push_back(0);
-      if (lines.empty()) lines.push_back(0);
-      md.occ = upload(pl, occ.data(), occ.size(), s);
-      md.occ_ptr = upload(pl, optr.data(), optr.size(), s);
-      md.occ_lines = upload(pl, lines.data(), lines.size(), s);
-      std::vector<int32_t> yr(2 * (size_t)h.grid[0], 0);
-      for (int64_t x = 0; x < h.grid[0]; ++x) yr[2 * x] = h.grid[1];
-      for (int64_t i = 0; i < md.n_occ_lines; ++i) {
-        const int64_t x = lines[i] / h.grid[1], y = lines[i] % h.grid[1];
-        yr[2 * x] = std::min<int32_t>(yr[2 * x], (int32_t)y);
-        yr[2 * x + 1] = std::max<int32_t>(yr[2 * x + 1], (int32_t)y + 1);
-      }
-      for (int64_t x = 0; x < h.grid[0]; ++x)
-        if (yr[2 * x] > yr[2 * x + 1]) yr[2 * x] = yr[2 * x + 1] = 0;
-      md.occ_yrange = upload(pl, yr.data(), yr.size(), s);
-      // per occupied line {lo, g0, g1, hi}: its occupied nodes lie in
-      // [lo, hi) outside the longest unoccupied run [g0, g1) between them (a
-      // line through a closed surface crosses it twice); occupied nodes are
-      // increasing, so lines come in order
-      std::vector<int32_t> zr;
-      for (int64_t i = 0; i < md.n_occ; ++i) {
-        const int32_t line = occ[i] / h.grid[2], z = occ[i] % h.grid[2];
-        if (zr.empty() || line != occ[i - 1] / h.grid[2]) {
-          zr.insert(zr.end(), {z, z + 1, z + 1, z + 1});
-        } else {
-          int32_t *r = &zr[zr.size() - 4];
-          if (z - r[3] > r[2] - r[1]) {  // a longer unoccupied run r[3] .. z - 1
-            r[1] = r[3];
-            r[2] = z;
-          }
-          r[3] = z + 1;
-        }
-      }
-      if (zr.empty()) zr.assign(4, 0);
-      md.occ_zrange = upload(pl, zr.data(), zr.size(), s);
-      HIPCHECK(hipStreamSynchronize(s));  // host vectors go out of scope
-    }
-    if (md.planar_z >= 0) {  // all entries sit on the plane: plane node p = x Ny + y
-      const int64_t A = (int64_t)h.grid[0] * h.grid[1];
-      std::vector<int32_t> p2(A + 1);
-      for (int64_t p = 0; p < A; ++p) p2[p] = ptr[p * h.grid[2] + md.planar_z];
-      p2[A] = ptr[V0];
-      md.plane_node_ptr = upload(pl, p2.data(), p2.size(), s);
-      std::vector<int32_t> occ, optr;
-      for (int64_t p = 0; p < A; ++p)
-        if (p2[p + 1] > p2[p]) {
-          occ.push_back((int32_t)p);
-          optr.push_back(p2[p]);
-        }
-      optr.push_back(p2[A]);
-      md.n_plane_occ = (int64_t)occ.size();
-      if (occ.empty()) occ.push_back(0);
-      md.plane_occ = upload(pl, occ.data(), occ.size(), s);
-      md.plane_occ_ptr = upload(pl, optr.data(), optr.size(), s);
-      HIPCHECK(hipStreamSynchronize(s));  // host vectors go out of scope
-    }
-    md.ent_col = upload(pl, col.data(), col.size(), s);
-    int32_t *dsrc = upload(pl, src.data(), src.size(), s);
-    md.lamT64 = (double *)dev_alloc(pl, sizeof(double) * 4 * std::max<int64_t>(ne, 1));
-    if (pl->mixed) md.lamT32 = (float *)dev_alloc(pl, sizeof(float) * 4 * std::max<int64_t>(ne, 1));
-    hipLaunchKernelGGL(k_lam_transpose, dim3(blocks_for(std::max<int64_t>(ne, 1), 256)), dim3(256), 0,
-                       s, md.lam64, dsrc, ne, K, md.lamT64, md.lamT32);
-    LAUNCHCHECK();
-    HIPCHECK(hipStreamSynchronize(s));
-    dev_free(pl, dsrc);
-  }
+  node_tables_mesh(pl, md, s);
   phase_done(AIM_SETUP_PROJECTION);
 
   // FFT plans, twiddles, Green's spectrum octant
