@@ -61,7 +61,8 @@ def log(msg):
 # the operator data they read (the solver, RCS, ABI glue, host planning and
 # near-field quadrature do not change a product kernel's memory traffic)
 MATVEC_SOURCES_EXCLUDED = ("api.hip", "solver.hip", "rcs.hip", "host_plan.cpp", "geom_device.h",
-                           "turns.h", "near_fill.hip")
+                           "turns.h", "scan.h", "node_tables.hip", "near_pattern.hip",
+                           "near_fill.hip")
 
 
 def sources_digest():

@@ -193,9 +193,9 @@ typedef struct {
                                            on that plane alone with the 2-D spectrum */
   double device_bytes;                  /* device memory held by the plan */
   double setup_ms[AIM_MAX_MESH][AIM_NSETUP]; /* wall time of each set-up phase, ms: host plan
-                                               (mesh checks, RWG table, grid, anchors, near-zone
-                                               pattern), projection weights, Green's spectrum,
-                                               near-zone fill (FP64 quadrature of Z^MOM - Z^grid),
+                                               (mesh checks, RWG table, grid, anchors), projection
+                                               weights and node tables, Green's spectrum, near-zone
+                                               pattern and fill (FP64 quadrature of Z^MOM - Z^grid),
                                                variant tuning (paper Section 2.4, Fig. 4, times
                                                the matrix fill) */
   double cfie_alpha[AIM_MAX_MESH];      /* combined-field parameter of each mesh, or -1 where

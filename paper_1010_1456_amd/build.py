@@ -22,7 +22,8 @@ OUT = os.path.join(HERE, "libaim.so")
 BUILD = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
-SOURCES = ["host_plan.cpp", "api.hip", "setup_kernels.hip", "node_tables.hip", "near_fill.hip", "matvec.hip", "solver.hip", "rcs.hip",
+SOURCES = ["host_plan.cpp", "api.hip", "setup_kernels.hip", "node_tables.hip", "near_pattern.hip",
+           "near_fill.hip", "matvec.hip", "solver.hip", "rcs.hip",
            "fft_contig_f32.hip", "fft_contig_f64.hip", "fft_strided_f32.hip", "fft_strided_f64.hip",
            "fft_mid_f32.hip", "fft_mid_f64.hip", "fft_anterp_f32.hip", "fft_anterp_f64.hip",
            "fft_xy_f32.hip", "fft_xy_f64.hip"]

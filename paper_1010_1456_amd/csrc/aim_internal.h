@@ -73,7 +73,16 @@ struct HostPlan {
   std::vector<int32_t> cols;     // nnz
 };
 
-void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp);
+// pattern: with the near-zone CSR (a plan on the GPU builds it there,
+// near_pattern_mesh)
+void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp, bool pattern = true);
+// cells the near pairs are searched with: pairs within r_near lie at most reach
+// cells apart per axis
+struct NearCells {
+  double lo[3], size;
+  int nc[3], reach;
+};
+NearCells near_cells(const HostPlan &h);
 
 // ---------------------------------------------------------------------------
 // Device-side data of one mesh.
@@ -257,6 +266,8 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s);
 // node-ordered projection and the tables of occupied nodes and lines
 // (node_tables.hip), from Lambda, the curl weights and the anchors
 void node_tables_mesh(Plan *pl, MeshDev &md, hipStream_t s);
+// near-zone CSR pattern (near_pattern.hip): md.rowptr, md.cols and hp.nnz
+void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 // near-zone matrix Z^MOM - Z^grid and the diagonal of Z^MOM (near_fill.hip);
 // area, anchor3: device, per triangle and 3 per basis
 void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *anchor3,

@@ -196,7 +196,7 @@ aim_status aim_setup(const aim_mesh *meshes, int32_t nmesh, const aim_params *p,
     int64_t off = 0;
     for (int i = 0; i < nmesh; ++i) {
       const double t0 = wall_ms();
-      host_plan_build(meshes[i], *p, &pl->mesh[i].hp);
+      host_plan_build(meshes[i], *p, &pl->mesh[i].hp, false);
       pl->mesh[i].setup_ms[AIM_SETUP_HOST_PLAN] = wall_ms() - t0;
       pl->mesh[i].offset = off;
       off += pl->mesh[i].hp.n;

@@ -53,7 +53,9 @@ int fft_length_at_least(int lo) {
 static void fail_mesh(const std::string &m) { throw Error(AIM_ERR_MESH, m); }
 static void fail_arg(const std::string &m) { throw Error(AIM_ERR_ARG, m); }
 
-void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp) {
+static void near_pattern_host(HostPlan &h);
+
+void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp, bool pattern) {
   if (!(m.freq_hz > 0)) fail_arg("freq_hz must be > 0");
   if (m.nv <= 0 || m.nt <= 0 || !m.verts || !m.tris) fail_arg("empty mesh");
   if (!(p.h_lambda > 0)) fail_arg("h_lambda must be > 0");
@@ -202,20 +204,33 @@ void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp) {
       h.anchor[3 * i + c] = (int32_t)a;
     }
 
-  // near zone: |c_m - c_n|^2 <= r^2 with a uniform cell hash
-  const double r = h.r_near, r2 = r * r;
-  double bmin[3], bmax[3];
-  for (int c = 0; c < 3; ++c) {
-    bmin[c] = bmax[c] = h.centre[c];
-    for (int64_t i = 0; i < n; ++i) {
-      bmin[c] = std::min(bmin[c], h.centre[3 * i + c]);
-      bmax[c] = std::max(bmax[c], h.centre[3 * i + c]);
+  if (pattern) near_pattern_host(h);
+}
+
+NearCells near_cells(const HostPlan &h) {
+  NearCells c;
+  double hi[3];
+  for (int d = 0; d < 3; ++d) {
+    c.lo[d] = hi[d] = h.centre[d];
+    for (int64_t i = 0; i < h.n; ++i) {
+      c.lo[d] = std::min(c.lo[d], h.centre[3 * i + d]);
+      hi[d] = std::max(hi[d], h.centre[3 * i + d]);
     }
   }
-  double span = std::max({bmax[0] - bmin[0], bmax[1] - bmin[1], bmax[2] - bmin[2], 1e-30});
-  double cs = std::max(r, span / 256.0);
-  int nc[3];
-  for (int c = 0; c < 3; ++c) nc[c] = std::max(1, (int)std::floor((bmax[c] - bmin[c]) / cs) + 1);
+  const double span = std::max({hi[0] - c.lo[0], hi[1] - c.lo[1], hi[2] - c.lo[2], 1e-30});
+  c.size = std::max(h.r_near, span / 256.0);
+  for (int d = 0; d < 3; ++d) c.nc[d] = std::max(1, (int)std::floor((hi[d] - c.lo[d]) / c.size) + 1);
+  c.reach = (int)std::ceil(h.r_near / c.size);
+  return c;
+}
+
+// near zone: |c_m - c_n|^2 <= r^2 with a uniform cell hash
+static void near_pattern_host(HostPlan &h) {
+  const int64_t n = h.n;
+  const NearCells cells = near_cells(h);
+  const double r2 = h.r_near * h.r_near, cs = cells.size;
+  const double *bmin = cells.lo;
+  const int *nc = cells.nc, reach = cells.reach;
   const int64_t ncell = (int64_t)nc[0] * nc[1] * nc[2];
   std::vector<int32_t> cell_of(n);
   std::vector<int64_t> cstart(ncell + 1, 0);
@@ -233,7 +248,6 @@ void host_plan_build(const aim_mesh &m, const aim_params &p, HostPlan *hp) {
     std::vector<int64_t> fill(cstart.begin(), cstart.end() - 1);
     for (int64_t i = 0; i < n; ++i) members[fill[cell_of[i]]++] = (int32_t)i;
   }
-  const int reach = (int)std::ceil(r / cs);
   unsigned nthr = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   std::vector<std::vector<int32_t>> part_cols(nthr);
   std::vector<int64_t> count(n, 0);

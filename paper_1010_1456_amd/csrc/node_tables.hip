@@ -8,6 +8,7 @@
 #include <algorithm>
 
 #include "aim_internal.h"
+#include "scan.h"
 
 namespace aim {
 
@@ -81,76 +82,13 @@ __global__ void k_lam_transpose(const double *lam, const int32_t *src, int64_t n
   }
 }
 
-// Exclusive scan of (value, 1 if value > 0) pairs, packed into 64 bits (sums in
-// the low word, occupied counts in the high one): per block of kScanItems items,
-// then the blocks' totals in one work-group, then written out by the callers.
-constexpr int kScanThreads = 256, kScanPer = 8, kScanItems = kScanThreads * kScanPer;
-__device__ inline uint64_t packed(int32_t v) {
-  return (uint64_t)(uint32_t)v | (v > 0 ? 1ull << 32 : 0);
-}
-__device__ inline uint64_t block_exclusive(uint64_t mine, uint64_t *total) {
-  __shared__ uint64_t ws[kScanThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint64_t scan = mine;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint64_t o = __shfl_up((unsigned long long)scan, off, 64);
-    if (lane >= off) scan += o;
-  }
-  __syncthreads();
-  if (lane == 63) ws[wave] = scan;
-  __syncthreads();
-  uint64_t before = 0, all = 0;
-  for (int w = 0; w < kScanThreads / 64; ++w) {
-    if (w < wave) before += ws[w];
-    all += ws[w];
-  }
-  *total = all;
-  return before + scan - mine;
-}
-__global__ void __launch_bounds__(kScanThreads)
-    k_scan_blocks(const int32_t *v, int64_t n, uint64_t *sums) {
-  const int64_t i0 = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
-  uint64_t mine = 0, total;
-  for (int k = 0; k < kScanPer; ++k)
-    if (i0 + k < n) mine += packed(v[i0 + k]);
-  (void)block_exclusive(mine, &total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-// sums[0 .. nb) to exclusive prefixes, sums[nb] the total
-__global__ void __launch_bounds__(kScanThreads) k_scan_sums(uint64_t *sums, int64_t nb) {
-  uint64_t carry = 0;
-  for (int64_t b0 = 0; b0 < nb; b0 += kScanThreads) {
-    const int64_t b = b0 + threadIdx.x;
-    uint64_t total;
-    const uint64_t ex = block_exclusive(b < nb ? sums[b] : 0, &total);
-    if (b < nb) sums[b] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) sums[nb] = carry;
-}
-// applies f(i, value, exclusive sum, exclusive count of occupied items)
-template <class F>
-__device__ inline void scan_apply(const int32_t *v, int64_t n, const uint64_t *sums, F f) {
-  const int64_t i0 = (int64_t)blockIdx.x * kScanItems + (int64_t)threadIdx.x * kScanPer;
-  int32_t x[kScanPer];
-  uint64_t mine = 0, total;
-  for (int k = 0; k < kScanPer; ++k) {
-    x[k] = i0 + k < n ? v[i0 + k] : 0;
-    mine += packed(x[k]);
-  }
-  uint64_t ex = sums[blockIdx.x] + block_exclusive(mine, &total);
-  for (int k = 0; k < kScanPer; ++k) {
-    if (i0 + k < n) f(i0 + k, x[k], (int32_t)(uint32_t)ex, (int32_t)(ex >> 32));
-    ex += packed(x[k]);
-  }
-}
-
 // node pointers, and the occupied nodes with their entry ranges; count becomes
 // the fill cursor
 __global__ void __launch_bounds__(kScanThreads)
     k_nodes(int32_t *count, int64_t V0, const uint64_t *sums, int64_t nb, int32_t *node_ptr,
             int32_t *occ, int32_t *occ_ptr) {
-  scan_apply(count, V0, sums, [&](int64_t v, int32_t c, int32_t e, int32_t i) {
+  scan_apply<true>(count, V0, sums, [&](int64_t v, int32_t c, uint64_t ex) {
+    const int32_t e = (int32_t)(uint32_t)ex, i = (int32_t)(ex >> 32);
     node_ptr[v] = e;
     count[v] = e;
     if (c > 0) {
@@ -195,7 +133,8 @@ __global__ void k_line_ranges(const int32_t *node_ptr, int64_t lines, int Nz, in
 __global__ void __launch_bounds__(kScanThreads)
     k_lines(const int32_t *any, int64_t lines, const uint64_t *sums, const int32_t *range,
             int32_t *occ_lines, int32_t *zrange) {
-  scan_apply(any, lines, sums, [&](int64_t l, int32_t c, int32_t, int32_t i) {
+  scan_apply<true>(any, lines, sums, [&](int64_t l, int32_t c, uint64_t ex) {
+    const int32_t i = (int32_t)(ex >> 32);
     if (c > 0) {
       occ_lines[i] = (int32_t)l;
       for (int q = 0; q < 4; ++q) zrange[4 * i + q] = range[4 * l + q];
@@ -241,18 +180,10 @@ void node_tables_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
     tmp.push_back(p);
     return p;
   };
-  auto scan_blocks = [](int64_t count) { return (count + kScanItems - 1) / kScanItems; };
   uint64_t *sums = (uint64_t *)scratch(sizeof(uint64_t) * (scan_blocks(std::max(V0, A)) + 1));
   // scans v[0 .. count); returns (sum, occupied items)
   auto scan = [&](const int32_t *v, int64_t count) {
-    const int64_t nb = scan_blocks(count);
-    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kScanThreads), 0, s, v, count, sums);
-    LAUNCHCHECK();
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, sums, nb);
-    LAUNCHCHECK();
-    uint64_t total = 0;
-    HIPCHECK(hipMemcpyAsync(&total, sums + nb, sizeof(total), hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
+    const uint64_t total = scan_sums<true>(v, count, sums, s);
     return std::make_pair((int64_t)(uint32_t)total, (int64_t)(total >> 32));
   };
   auto ints = [&](int64_t count) {

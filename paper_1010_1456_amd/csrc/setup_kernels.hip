@@ -289,10 +289,6 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     soff[u] = (ui * h.grid[1] + uj) * h.grid[2] + uk;
   }
   md.stencil_off = upload(pl, soff.data(), soff.size(), s);
-  std::vector<int32_t> rp32(n + 1);
-  for (int64_t i = 0; i <= n; ++i) rp32[i] = (int32_t)h.rowptr[i];
-  md.rowptr = upload(pl, rp32.data(), rp32.size(), s);
-  md.cols = upload(pl, h.cols.data(), h.cols.size(), s);
   HIPCHECK(hipStreamSynchronize(s));
 
   // projection weights
@@ -411,6 +407,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
   }
   phase_done(AIM_SETUP_GREEN);
 
+  near_pattern_mesh(pl, md, s);
   near_fill_mesh(pl, md, area, anchor3, s);
   phase_done(AIM_SETUP_NEAR_FILL);
   dev_free(pl, anchor3);
