@@ -87,7 +87,7 @@ typedef struct {
  *                     timing (for tests and measurements; 0 = pick all):
  *                     bits 0-7  field groups the forward y, x and inverse y
  *                               passes are pipelined over (aim_info.xy_groups):
- *                               0 (pick), 1, 2 or 4;
+ *                               0 (= 1), 1, 2 or 4;
  *                     bits 8-15 tile rows of the x and strided y passes
  *                               (aim_info.tile_bytes): 0 (pick), 1 (128-byte
  *                               rows), 2 (64-byte rows);
@@ -210,8 +210,8 @@ typedef struct {
   int32_t xy_groups[AIM_MAX_MESH][2];   /* [mesh][0 FP64, 1 mixed]: field groups over which the
                                            forward y, x and inverse y passes run pipelined, the
                                            x pass of one group beside the y passes of others in
-                                           one launch (1: one pass after the other; chosen by
-                                           timing at set-up) */
+                                           one launch (1: one pass after the other, unless
+                                           aim_params.tuning asks for groups) */
   int32_t tile_bytes[AIM_MAX_MESH][2][2]; /* [mesh][0 FP64, 1 mixed][0 x pass, 1 strided y
                                            passes]: bytes of consecutive grid lines (128 or 64)
                                            in one work-group's tile (chosen by timing at

@@ -338,11 +338,11 @@ struct StageView {
 // each stage: ev[0] .. ev[AIM_NSTAGE]. `full3d` (inspection): the 3-D passes
 // also for a scatterer in one grid plane. `views` (optional, AIM_NSTAGE
 // entries, index = stage): where the product's own passes left each stage's
-// output.
+// output. `first` (set-up timings): stages before it are not launched.
 template <typename T, typename TX>
 void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, int stop_stage,
                 hipStream_t s, hipEvent_t *ev = nullptr, bool full3d = false,
-                StageView *views = nullptr);
+                StageView *views = nullptr, int first = 1);
 // copies a stage's output as recorded in `v` to out in the plain [F][A][Z] layout
 template <typename T>
 void copy_stage_view(const StageView &v, void *out, hipStream_t s);

@@ -468,7 +468,7 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
 
 template <typename T, typename TX>
 void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, int stop,
-                hipStream_t s, hipEvent_t *ev, bool full3d, StageView *views) {
+                hipStream_t s, hipEvent_t *ev, bool full3d, StageView *views, int first) {
   auto mark = [&](int i) {
     if (ev) HIPCHECK(hipEventRecord(ev[i], s));
   };
@@ -510,7 +510,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * A1, 2, s);
     mark(0);
     const int64_t no = md.n_plane_occ;
-    if (no > 0) {
+    if (no > 0 && first <= 1) {
       hipLaunchKernelGGL((k_anterp_gather<T, TX>),
                          dim3((unsigned)((no + 4 * npw - 1) / (4 * npw)), nrhs),
                          dim3(256), 0, s, x, ldx, nrhs, md.plane_occ_ptr, md.plane_occ,
@@ -521,8 +521,9 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     view(1, gs, Nx, Ny, A1, Ny, 1);
     if (stop <= 1) return;
     mark(2);
-    fft_pass_contig(gs, g2, md.plan[1], Ny, Py, F * Nx, fftk::contig_map(Ny), fftk::contig_map(Py),
-                    false, tw_of<T>(md, 1), s);
+    if (first <= 3)
+      fft_pass_contig(gs, g2, md.plan[1], Ny, Py, F * Nx, fftk::contig_map(Ny),
+                      fftk::contig_map(Py), false, tw_of<T>(md, 1), s);
     mark(3);
     view(3, g2, Nx, Py, V2, Py, 1);
     if (stop <= 3) return;
@@ -549,7 +550,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
     mark(0);
-    if (md.n_occ > 0) {
+    if (md.n_occ > 0 && first <= 1) {
       hipLaunchKernelGGL((k_anterp_gather<T, TX>),
                          dim3((unsigned)((md.n_occ + 4 * npw - 1) / (4 * npw)), nrhs),
                          dim3(256), 0, s, x, ldx, nrhs, md.occ_ptr, md.occ, md.ent_col,
@@ -559,13 +560,15 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     mark(1);
     view(1, gs, A1, Nz, V0, Nz, 1);
     if (stop <= 1) return;
-    fft_pass_contig(gs, g1, md.plan[2], Nz, Pz, F * A1, fftk::contig_map(Nz),
-                    fftk::contig_map(A1, V1, 1, A1), false, tw_of<T>(md, 2), s);
+    if (first <= 2)
+      fft_pass_contig(gs, g1, md.plan[2], Nz, Pz, F * A1, fftk::contig_map(Nz),
+                      fftk::contig_map(A1, V1, 1, A1), false, tw_of<T>(md, 2), s);
     mark(2);
     view(2, g1, A1, Pz, V1, 1, A1);
     if (stop <= 2) return;
-    fft_pass_contig(g1, g2, md.plan[1], Ny, Py, F * Pz * Nx, fftk::contig_map(Ny),
-                    fftk::contig_map(Py), false, tw_of<T>(md, 1), s);
+    if (first <= 3)
+      fft_pass_contig(g1, g2, md.plan[1], Ny, Py, F * Pz * Nx, fftk::contig_map(Ny),
+                      fftk::contig_map(Py), false, tw_of<T>(md, 1), s);
     mark(3);
     view(3, g2, (int64_t)Nx * Py, Pz, V2, 1, (int64_t)Nx * Py);
     if (stop <= 3) return;
@@ -609,7 +612,9 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   // The variant is tuned on one right-hand side and walks the right-hand
   // sides in turn, so several take the two-launch form (right-hand sides in
   // parallel).
-  if (stop <= 1 || !md.fuse_proj[prec] || nrhs > 1 ||
+  if (first > 2) {  // (set-up) the passes after the forward z pass alone
+    gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
+  } else if (stop <= 1 || !md.fuse_proj[prec] || nrhs > 1 ||
       !anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, (int64_t)Nx * Ny, g1,
                    Pzs, (int64_t)Nx * Ny * Pzs, tw_of<T>(md, 2), md.plan[2], s)) {
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
@@ -670,13 +675,15 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     blocked_view(4);
     mark(5);
   } else {
-    fft_pass_strided(gz, g2, md.plan[1], Ny, Py, F * Nx, Pz, m1y, m2, false, tw_of<T>(md, 1),
-                     md.y_row[prec], s);
+    if (first <= 3)
+      fft_pass_strided(gz, g2, md.plan[1], Ny, Py, F * Nx, Pz, m1y, m2, false, tw_of<T>(md, 1),
+                       md.y_row[prec], s);
     mark(3);
     blocked_view(3);
     if (stop <= 3) return;
-    fft_mid_pass(g2, md.plan[0], Nx, (int)F, Py, Pz, md.H[0], md.H[1], md.H[2], ghat_of<T>(md),
-                 tw_of<T>(md, 0), blk, V2, md.x_row[prec], s);
+    if (first <= 4)
+      fft_mid_pass(g2, md.plan[0], Nx, (int)F, Py, Pz, md.H[0], md.H[1], md.H[2], ghat_of<T>(md),
+                   tw_of<T>(md, 0), blk, V2, md.x_row[prec], s);
     mark(4);
     blocked_view(4);
     if (stop <= 4) return;
@@ -894,13 +901,16 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
   try {
     x = dev_alloc(pl, sizeof(double2) * n * nr);
     HIPCHECK(hipMemsetAsync(x, 0, sizeof(double2) * n * nr, s));
-    auto time_stages = [&](int prec, int stop) {
+    // the stages first .. stop alone (zero grids stay zero)
+    auto time_stages = [&](int prec, int first, int stop) {
       for (int rep = 0; rep < 4; ++rep) {  // first repetition is a warm-up
         if (rep == 1) HIPCHECK(hipEventRecord(e0, s));
         if (prec == 0)
-          far_stages<double, double>(pl, md, nr, (const double2 *)x, n, stop, s);
+          far_stages<double, double>(pl, md, nr, (const double2 *)x, n, stop, s, nullptr, false,
+                                     nullptr, first);
         else
-          far_stages<float, double>(pl, md, nr, (const double2 *)x, n, stop, s);
+          far_stages<float, double>(pl, md, nr, (const double2 *)x, n, stop, s, nullptr, false,
+                                    nullptr, first);
       }
       HIPCHECK(hipEventRecord(e1, s));
       HIPCHECK(hipEventSynchronize(e1));
@@ -915,7 +925,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       int choice = kGatherNpwCand[1];
       for (int c = 0; c < 3; ++c) {
         md.gather_npw[prec] = kGatherNpwCand[c];
-        const float ms = time_stages(prec, 1);
+        const float ms = time_stages(prec, 1, 1);
         if (c == 0 || ms < best) {
           best = ms;
           choice = kGatherNpwCand[c];
@@ -934,7 +944,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       int choice = 0;
       for (int v = 0; v < 2; ++v) {
         md.fuse_proj[prec] = v;
-        const float ms = time_stages(prec, 2);
+        const float ms = time_stages(prec, 1, 2);
         if (v == 0 || ms < best) {
           best = ms;
           choice = v;
@@ -942,66 +952,38 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       }
       md.fuse_proj[prec] = choice;
     }
-    // tile rows of the x pass and of the strided y passes (the whole far part
-    // timed; 64-byte rows halve a work-group's LDS tile, so more work-groups
-    // fit a CU, at the cost of half-cache-line accesses)
+    // tile rows of the x pass and of the strided y passes, each pass timed alone
+    // (timing the whole far part for all four combinations, and for the pipelined
+    // y / x / y passes, took 107 ms of the 8-lambda sphere's set-up): 64-byte rows
+    // halve a work-group's LDS tile, so more work-groups fit a CU, at the cost of
+    // half-cache-line accesses. A variant must beat 128-byte rows by 3%, the
+    // timing spread of products of one right-hand side; by 1% where several are
+    // timed. The passes are pipelined over field groups only where the caller
+    // asks for it: sequential passes were faster everywhere that was measured
+    // (8-lambda sphere: 0.676 ms against 0.688 and 0.738 in 2 and 4 groups).
+    const int rows = (pl->params.tuning >> 8) & 0xff;   // 1: 128-byte, 2: 64-byte rows everywhere
+    const int groups = pl->params.tuning & 0xff;
+    const float margin = nr > 1 ? 0.99f : 0.97f;
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
-      const int forced = (pl->params.tuning >> 8) & 0xff;
-      md.x_row[prec] = md.y_row[prec] = 128;
-      if (forced == 1 || forced == 2) {  // 1: 128-byte rows, 2: 64-byte rows everywhere
-        md.x_row[prec] = md.y_row[prec] = forced == 2 ? 64 : 128;
-        continue;
-      }
-      // (a variant must beat 128-byte rows by 3%, the timing spread of
-      // products of one right-hand side; by 1% where several are timed)
-      const float margin = nr > 1 ? 0.99f : 0.97f;
-      float best = 0, base = 0;
-      int bx = 128, by = 128;
-      for (int xr : {128, 64})
-        for (int yr : {128, 64}) {
-          md.x_row[prec] = xr;
-          md.y_row[prec] = yr;
-          const float ms = time_stages(prec, 6);
-          if (xr == 128 && yr == 128) {
-            best = base = ms;
-          } else if (ms < best && ms < margin * base) {
-            best = ms;
-            bx = xr;
-            by = yr;
-          }
-        }
-      md.x_row[prec] = bx;
-      md.y_row[prec] = by;
-    }
-    // field groups of the pipelined y / x / y passes (kz-blocked grids with
-    // equal x and y lengths)
-    for (int prec = 0; prec < 2; ++prec) {
-      if (prec == 1 && !pl->mixed) break;
+      const bool thin =
+          md.planar_z >= 0 ||
+          (prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]));
       md.xy_groups[prec] = 1;
-      const bool thin = prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]);
-      if (thin || md.planar_z >= 0 || !xy_pipeline_available(md.plan[0], md.plan[1])) continue;
-      const int forced = pl->params.tuning & 0xff;
-      if (forced > 0) {
-        md.xy_groups[prec] = forced;
-        continue;
-      }
-      // the pipeline must beat the sequential passes by a clear margin: the
-      // set-up times a few products of one right-hand side, and differences
-      // of a few percent there are within run-to-run spread
-      float best = 0, sequential = 0;
-      int choice = 1;
-      for (int g : {1, 2, 4}) {
-        md.xy_groups[prec] = g;
-        const float ms = time_stages(prec, 6);
-        if (g == 1) {
-          best = sequential = ms;
-        } else if (ms < best && ms < 0.97f * sequential) {
-          best = ms;
-          choice = g;
+      md.x_row[prec] = md.y_row[prec] = rows == 2 ? 64 : 128;
+      if (rows == 0) {
+        const float x128 = time_stages(prec, 4, 4);
+        md.x_row[prec] = 64;
+        if (time_stages(prec, 4, 4) >= margin * x128) md.x_row[prec] = 128;
+        if (!thin) {  // (the y lines of the thin layouts are contiguous)
+          const float y128 = time_stages(prec, 3, 3) + time_stages(prec, 5, 5);
+          md.y_row[prec] = 64;
+          if (time_stages(prec, 3, 3) + time_stages(prec, 5, 5) >= margin * y128)
+            md.y_row[prec] = 128;
         }
       }
-      md.xy_groups[prec] = choice;
+      if (groups > 0 && !thin && xy_pipeline_available(md.plan[0], md.plan[1]))
+        md.xy_groups[prec] = groups;
     }
   } catch (...) {
     (void)hipEventDestroy(e0);
@@ -1015,11 +997,11 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
 }
 
 template void far_stages<double, double>(Plan *, MeshDev &, int, const double2 *, int64_t, int,
-                                         hipStream_t, hipEvent_t *, bool, StageView *);
+                                         hipStream_t, hipEvent_t *, bool, StageView *, int);
 template void far_stages<float, float>(Plan *, MeshDev &, int, const float2 *, int64_t, int,
-                                       hipStream_t, hipEvent_t *, bool, StageView *);
+                                       hipStream_t, hipEvent_t *, bool, StageView *, int);
 template void far_stages<float, double>(Plan *, MeshDev &, int, const double2 *, int64_t, int,
-                                        hipStream_t, hipEvent_t *, bool, StageView *);
+                                        hipStream_t, hipEvent_t *, bool, StageView *, int);
 template void matvec_mesh<double, double, double>(Plan *, MeshDev &, int, const double2 *, int64_t,
                                                   double2 *, int64_t, hipStream_t, hipEvent_t *);
 template void matvec_mesh<float, float, float>(Plan *, MeshDev &, int, const float2 *, int64_t,
