@@ -243,9 +243,10 @@ struct Plan {
   std::vector<MeshDev> mesh;
   std::vector<std::pair<void *, size_t>> live;  // allocations (for destroy/info)
   double device_bytes = 0;
-  // grid work buffers per lane and precision, grown on demand
-  void *work[kMaxLanes][2][3] = {};
-  size_t work_bytes[kMaxLanes][2][3] = {};
+  // work buffers per lane and precision, grown on demand: the grids g0, g1, g2,
+  // and x transposed for several right-hand sides
+  void *work[kMaxLanes][2][4] = {};
+  size_t work_bytes[kMaxLanes][2][4] = {};
   // lanes of a multi-mesh product: the meshes are dealt to nlanes streams
   // (lane 0 is the caller's stream, lanes 1.. the plan's own, default
   // priority), each with its own work buffers, so that the members' products

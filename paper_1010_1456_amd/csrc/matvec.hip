@@ -12,6 +12,7 @@
 
 #include "aim_internal.h"
 #include "fft_map.h"
+#include "multi_rhs.h"
 
 namespace aim {
 
@@ -438,8 +439,8 @@ static cx<T> *src_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStr
 }
 
 void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStream_t s) {
-  void *(&work)[3] = pl->work[lane][prec];
-  size_t(&have)[3] = pl->work_bytes[lane][prec];
+  void *(&work)[4] = pl->work[lane][prec];
+  size_t(&have)[4] = pl->work_bytes[lane][prec];
   if (have[which] < bytes) {
     if (work[which]) dev_free(pl, work[which]);
     work[which] = nullptr;
@@ -464,6 +465,56 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
     }
   }
   return work[which];
+}
+
+// Lanes per node (row) of the several-right-hand-sides kernels (multi_rhs.h), 0:
+// the others. From 6 on they are faster on every mesh measured (projection and
+// interpolation together, 4-lambda CFIE sphere: 8 right-hand sides 145 -> 119 us
+// in c64 and 276 -> 209 in FP64, 16: 248 -> 170 and 528 -> 306); with 3 or 4 their
+// short runs lose (4: 85 -> 99 and 164 -> 170), at 5 the two are equal.
+static int multi_lanes(int nrhs) { return nrhs < 6 ? 0 : (nrhs <= 8 ? 8 : 16); }
+
+// x of one mesh transposed to [n][nrhs] in T
+template <typename T, typename TX>
+static cx<T> *transposed_x(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx,
+                           bool fill, hipStream_t s) {
+  const int prec = sizeof(T) == 8 ? 0 : 1;
+  const int64_t n = md.hp.n;
+  cx<T> *xt = (cx<T> *)work_buffer(pl, md.lane, prec, 3, sizeof(cx<T>) * n * nrhs, s);
+  if (fill) {
+    hipLaunchKernelGGL((k_transpose_x<T, TX>), dim3(launch_blocks(n, 64), (nrhs + 15) / 16),
+                       dim3(kMultiThreads), 0, s, x, ldx, nrhs, n, xt);
+    LAUNCHCHECK();
+  }
+  return xt;
+}
+
+// projection of x onto the occupied nodes occ of grids of Vg nodes
+template <typename T, typename TX>
+static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx,
+                    const int32_t *occ_ptr, const int32_t *occ, int64_t n_occ, cx<T> *grid,
+                    int64_t Vg, hipStream_t s) {
+  const int npw = md.gather_npw[sizeof(T) == 8 ? 0 : 1];
+  const int LR = multi_lanes(nrhs);
+  if (LR > 0) {
+    const cx<T> *xt = transposed_x<T, TX>(pl, md, nrhs, x, ldx, true, s);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(launch_blocks(n_occ, kMultiRows), (nrhs + LR - 1) / LR),
+                         dim3(kMultiThreads), 0, s, xt, nrhs, occ_ptr, occ, md.ent_col,
+                         lamT_of<T>(md), grid, n_occ, Vg);
+    };
+    if (n_occ > 0) {
+      if (LR == 8)
+        go(k_anterp_multi<T, 8>);
+      else
+        go(k_anterp_multi<T, 16>);
+    }
+  } else if (n_occ > 0) {
+    hipLaunchKernelGGL((k_anterp_gather<T, TX>),
+                       dim3((unsigned)((n_occ + 4 * npw - 1) / (4 * npw)), nrhs), dim3(256), 0, s,
+                       x, ldx, nrhs, occ_ptr, occ, md.ent_col, lamT_of<T>(md), grid, n_occ, Vg, npw);
+  }
+  LAUNCHCHECK();
 }
 
 template <typename T, typename TX>
@@ -509,14 +560,8 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * A1, 2, s);
     mark(0);
-    const int64_t no = md.n_plane_occ;
-    if (no > 0 && first <= 1) {
-      hipLaunchKernelGGL((k_anterp_gather<T, TX>),
-                         dim3((unsigned)((no + 4 * npw - 1) / (4 * npw)), nrhs),
-                         dim3(256), 0, s, x, ldx, nrhs, md.plane_occ_ptr, md.plane_occ,
-                         md.ent_col, lamT_of<T>(md), gs, no, A1, npw);
-      LAUNCHCHECK();
-    }
+    if (first <= 1)
+      project<T, TX>(pl, md, nrhs, x, ldx, md.plane_occ_ptr, md.plane_occ, md.n_plane_occ, gs, A1, s);
     mark(1);
     view(1, gs, Nx, Ny, A1, Ny, 1);
     if (stop <= 1) return;
@@ -550,13 +595,8 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
     mark(0);
-    if (md.n_occ > 0 && first <= 1) {
-      hipLaunchKernelGGL((k_anterp_gather<T, TX>),
-                         dim3((unsigned)((md.n_occ + 4 * npw - 1) / (4 * npw)), nrhs),
-                         dim3(256), 0, s, x, ldx, nrhs, md.occ_ptr, md.occ, md.ent_col,
-                         lamT_of<T>(md), gs, md.n_occ, V0, npw);
-      LAUNCHCHECK();
-    }
+    if (first <= 1)
+      project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
     mark(1);
     view(1, gs, A1, Nz, V0, Nz, 1);
     if (stop <= 1) return;
@@ -618,13 +658,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
       !anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, (int64_t)Nx * Ny, g1,
                    Pzs, (int64_t)Nx * Ny * Pzs, tw_of<T>(md, 2), md.plan[2], s)) {
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
-    if (md.n_occ > 0) {
-      hipLaunchKernelGGL((k_anterp_gather<T, TX>),
-                         dim3((unsigned)((md.n_occ + 4 * npw - 1) / (4 * npw)), nrhs),
-                         dim3(256), 0, s, x, ldx, nrhs, md.occ_ptr, md.occ, md.ent_col,
-                         lamT_of<T>(md), gs, md.n_occ, V0, npw);
-      LAUNCHCHECK();
-    }
+    project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
     mark(1);
     view(1, gs, (int64_t)Nx * Ny, Nz, V0, Nz, 1);
     if (stop <= 1) return;
@@ -742,10 +776,33 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
     else if (left == 1)
       launch(k_interp_near<T, TX, TY, 1, CF>, r_left, 1);
   };
+  // several right-hand sides: x transposed by the projection
+  auto multi = [&](auto cf_, auto lr_) {
+    constexpr bool CF = decltype(cf_)::value;
+    constexpr int LR = decltype(lr_)::value;
+    const cx<T> *xt = transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);
+    hipLaunchKernelGGL((k_interp_multi<T, TY, LR, CF>),
+                       dim3(launch_blocks(h.n, kMultiRows), (nrhs + LR - 1) / LR),
+                       dim3(kMultiThreads), 0, s, phi, nrhs,
+                       plane ? plane_lam_of<T>(md) : lam_of<T>(md), cf ? curl_of<T>(md) : nullptr,
+                       plane ? md.plane_anchor : md.anchor_lin,
+                       plane ? md.plane_soff : md.stencil_off, plane ? md.plane_K : h.K, md.rowptr,
+                       md.cols, near_of<T>(md), xt, y, ldy, h.n, (T)(h.alpha * h.k * kEta0),
+                       (T)(1.0 / (h.k * h.k)), (T)((1.0 - h.alpha) * kEta0));
+  };
+  auto all = [&](auto cf_) {
+    const int LR = multi_lanes(nrhs);
+    if (LR == 16)
+      multi(cf_, std::integral_constant<int, 16>{});
+    else if (LR == 8)
+      multi(cf_, std::integral_constant<int, 8>{});
+    else
+      groups(cf_);
+  };
   if (cf)
-    groups(std::true_type{});
+    all(std::true_type{});
   else
-    groups(std::false_type{});
+    all(std::false_type{});
   LAUNCHCHECK();
   if (ev) HIPCHECK(hipEventRecord(ev[7], s));
 }

@@ -1,5 +1,6 @@
 """The interpolation and near-zone kernel where its shapes change: right-hand
-sides in groups of 4 and the 1 to 3 left over, rows longer than one pass of 96
+sides in groups of 4 and the 1 to 3 left over, a lane each from 6 on (8 or 16 lanes,
+one or more groups of them), rows longer than one pass of 96
 entries, stencils of up to 216 nodes, row counts that are no multiple of a
 work-group's 16, in both arithmetics, against the oracle: relative 1e-12 in FP64,
 2e-5 in c64, and the c128-vector form of the c64 product equal to it bit for bit
@@ -42,7 +43,7 @@ def _problem(name):
     return op, A.Plan([(m.verts, m.tris, FREQ)], order=order, near_radius_lambda=radius, **kw)
 
 
-@pytest.mark.parametrize("nrhs", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 4, 5, 6, 8, 9, 16, 17])
 @pytest.mark.parametrize("name", list(CASES))
 def test_product(name, nrhs):
     from paper_1010_1456_amd import aim as A
