@@ -155,8 +155,8 @@ __global__ void k_unblock(const cx<T> *__restrict__ in, cx<T> *__restrict__ out,
   out[t] = in[f * fstride + ((int64_t)(kz / blk) * Nx + x) * Py * blk + (int64_t)ky * blk + kz % blk];
 }
 
-// Sum over the 16 lanes of a row (every lane gets it), by lane permutations
-// within the row (DPP: quad swaps, then mirrors of 8 and 16 lanes).
+// Sum over the 16 or 32 lanes of a row (every lane gets it), by lane permutations
+// (DPP: quad swaps, then mirrors of 8 and 16 lanes).
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
@@ -166,12 +166,13 @@ __device__ __forceinline__ double dpp(double v) {
   return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
                           __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
 }
-template <typename V>
+template <int LANES, typename V>
 __device__ __forceinline__ V row_sum(V v) {
   v.x += dpp<0xB1>(v.x), v.y += dpp<0xB1>(v.y);    // lane ^ 1
   v.x += dpp<0x4E>(v.x), v.y += dpp<0x4E>(v.y);    // lane ^ 2
   v.x += dpp<0x141>(v.x), v.y += dpp<0x141>(v.y);  // 7 - lane of 8
   v.x += dpp<0x140>(v.x), v.y += dpp<0x140>(v.y);  // 15 - lane of 16
+  if (LANES == 32) v.x += __shfl_xor(v.x, 16, 64), v.y += __shfl_xor(v.y, 16, 64);
   return v;
 }
 
@@ -192,13 +193,18 @@ __device__ __forceinline__ V row_sum(V v) {
 constexpr int kRowLanes = 16;
 constexpr int kNearUnroll = 6;
 constexpr int kStencilUnroll = 2;
+// 32 lanes per row, a half and the same number of these, where higher orders
+// (64 nodes and more) meet fewer rows than 16 lanes each fill the chip with: the
+// time is then one wave's chain (third order, 1-lambda sphere, 3 630 rows, c64:
+// 7.9 -> 6.8 us; 25 230 rows: 16 lanes are faster)
+constexpr int64_t kFewRows = 8192;
 
 // RB right-hand sides from r_first + RB blockIdx.y: the stencil weights, the
 // near-zone entries and their columns are loaded once for the RB products.
 // CF (combined field): y^far = keta j [sum_q Lambda_q^T phi_q - inv_k2
 // Lambda_d^T phi_d] - eta_h sum_e W_e^T phi_e, with keta = alpha k eta and
 // eta_h = (1 - alpha) eta; the curl weights W test the vector potential's curl.
-template <typename T, typename TX, typename TY, int RB, bool CF>
+template <typename T, typename TX, typename TY, int RB, bool CF, int LANES = kRowLanes>
 __global__ void __launch_bounds__(256)
     k_interp_near(const cx<T> *__restrict__ phi, int64_t nf, int r_first,
                   const T *__restrict__ lam, const T *__restrict__ curl,
@@ -207,13 +213,13 @@ __global__ void __launch_bounds__(256)
                   const cx<T> *__restrict__ nearv, const cx<TX> *__restrict__ x, int64_t ldx,
                   cx<TY> *__restrict__ y, int64_t ldy, int64_t n, T keta, T inv_k2, T eta_h) {
   using V = cx<T>;
-  constexpr int NU = kNearUnroll, SU = kStencilUnroll;
-  const int lane = threadIdx.x & (kRowLanes - 1);
-  const int64_t m = (int64_t)blockIdx.x * (256 / kRowLanes) + threadIdx.x / kRowLanes;
+  constexpr int NU = kNearUnroll * kRowLanes / LANES, SU = kStencilUnroll;
+  const int lane = threadIdx.x & (LANES - 1);
+  const int64_t m = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   if (m >= n) return;  // whole rows exit
   int so[SU];
 #pragma unroll
-  for (int k = 0; k < SU; ++k) so[k] = lane + kRowLanes * k < K ? soff[lane + kRowLanes * k] : 0;
+  for (int k = 0; k < SU; ++k) so[k] = lane + LANES * k < K ? soff[lane + LANES * k] : 0;
   const int64_t a = anchor_lin[m];
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
   const int r0 = r_first + blockIdx.y * RB;  // first right-hand side of this row
@@ -225,11 +231,11 @@ __global__ void __launch_bounds__(256)
   int c[NU];
   auto load_near = [&](int eb) {  // entries eb, eb + 16, ... of this lane
 #pragma unroll
-    for (int k = 0; k < NU; ++k) c[k] = eb + kRowLanes * k < e1 ? cols[eb + kRowLanes * k] : -1;
+    for (int k = 0; k < NU; ++k) c[k] = eb + LANES * k < e1 ? cols[eb + LANES * k] : -1;
 #pragma unroll
     for (int k = 0; k < NU; ++k) {
-      if (eb + kRowLanes * k < e1) {
-        z[k] = nearv[eb + kRowLanes * k];
+      if (eb + LANES * k < e1) {
+        z[k] = nearv[eb + LANES * k];
       } else {
         z[k].x = 0;
         z[k].y = 0;
@@ -271,11 +277,11 @@ __global__ void __launch_bounds__(256)
   };
   const T *lm = lam + m * 4 * K, *wm = CF ? curl + m * 3 * K : nullptr;
   load_near(e0 + lane);
-  for (int u0 = lane; u0 < K; u0 += kRowLanes * SU) {
+  for (int u0 = lane; u0 < K; u0 += LANES * SU) {
     T l[SU][4], w[SU][3];
 #pragma unroll
     for (int k = 0; k < SU; ++k) {
-      const int u = u0 + kRowLanes * k;
+      const int u = u0 + LANES * k;
 #pragma unroll
       for (int q = 0; q < 4; ++q) l[k][q] = u < K ? lm[q * K + u] : (T)0;
 #pragma unroll
@@ -283,17 +289,17 @@ __global__ void __launch_bounds__(256)
     }
 #pragma unroll
     for (int k = 0; k < SU; ++k)
-      if (u0 + kRowLanes * k < K)
+      if (u0 + LANES * k < K)
         far_node(a + so[k], l[k][0], l[k][1], l[k][2], l[k][3], w[k][0], w[k][1], w[k][2]);
-    if (u0 + kRowLanes * SU < K)  // the next nodes (orders above 2)
+    if (u0 + LANES * SU < K)  // the next nodes (orders above 2)
 #pragma unroll
       for (int k = 0; k < SU; ++k) {
-        const int u = u0 + kRowLanes * (SU + k);
+        const int u = u0 + LANES * (SU + k);
         so[k] = u < K ? soff[u] : 0;
       }
   }
   add_near();
-  for (int eb = e0 + lane + kRowLanes * NU; eb < e1; eb += kRowLanes * NU) {
+  for (int eb = e0 + lane + LANES * NU; eb < e1; eb += LANES * NU) {
     load_near(eb);
     add_near();
   }
@@ -306,7 +312,7 @@ __global__ void __launch_bounds__(256)
       acc.x -= eta_h * fk[rb].x;
       acc.y -= eta_h * fk[rb].y;
     }
-    acc = row_sum(acc);
+    acc = row_sum<LANES>(acc);
     if (lane == 0) {
       cx<TY> out;
       out.x = (decltype(out.x))acc.x;
@@ -752,12 +758,11 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
   const cx<T> *phi = (const cx<T> *)pl->work[md.lane][prec][0];
   const bool plane = md.planar_z >= 0;  // fields on the scatterer's grid plane only
   const int64_t nf = 4 * (int64_t)nrhs;  // fields per node of the interleaved grid
-  const int64_t blocks = (h.n + 256 / kRowLanes - 1) / (256 / kRowLanes);
   const bool cf = h.cfie;
   if (cf && (plane || !curl_of<T>(md))) throw Error(AIM_ERR_STATE, "combined field without curl weights");
   // right-hand sides in groups of 4, then the 1 to 3 left over in one group
-  auto launch = [&](auto kern, int r_first, int groups) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks, groups), dim3(256), 0, s, phi, nf, r_first,
+  auto launch = [&](auto kern, int r_first, int groups, int lanes = kRowLanes) {
+    hipLaunchKernelGGL(kern, dim3(launch_blocks(h.n, 256 / lanes), groups), dim3(256), 0, s, phi, nf, r_first,
                        plane ? plane_lam_of<T>(md) : lam_of<T>(md), cf ? curl_of<T>(md) : nullptr,
                        plane ? md.plane_anchor : md.anchor_lin,
                        plane ? md.plane_soff : md.stencil_off, plane ? md.plane_K : h.K,
@@ -773,6 +778,8 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
       launch(k_interp_near<T, TX, TY, 3, CF>, r_left, 1);
     else if (left == 2)
       launch(k_interp_near<T, TX, TY, 2, CF>, r_left, 1);
+    else if (left == 1 && !plane && h.K >= 64 && h.n <= kFewRows)
+      launch(k_interp_near<T, TX, TY, 1, CF, 32>, r_left, 1, 32);
     else if (left == 1)
       launch(k_interp_near<T, TX, TY, 1, CF>, r_left, 1);
   };
