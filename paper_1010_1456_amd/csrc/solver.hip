@@ -49,8 +49,9 @@ __device__ inline double2 block_sum2(double a, double b) {
 }
 
 // One pass over the Krylov basis of the Gram-Schmidt step: with SUB, w -= V h
-// (h[i S + s]); with DOTS, the partial dot products V_i^H w of the (new) w into
-// part[(i S + s) np_stride + blockIdx.x]; with NORM, the partial |w|^2 of the new
+// (h[i S + s], or the sum of the np partials of an earlier pass in hpart, then also
+// put into, or with `second` added to, column j of H); with DOTS, the partial dot
+// products V_i^H w of the (new) w into part[(i S + s) np_stride + blockIdx.x]; with NORM, the partial |w|^2 of the new
 // w into npart[s kNormParts + blockIdx.x]. Classical Gram-Schmidt twice is then
 // three passes over V instead of four, the middle one (SUB and DOTS) keeping its
 // tile of V in registers between the two uses.
@@ -68,8 +69,9 @@ template <int SLOTS, int RP, bool SUB, bool DOTS, bool NORM>
 __global__ void __launch_bounds__(256)
     k_basis_pass(const double2 *__restrict__ V, double2 *__restrict__ w, int64_t ld,
                  int64_t vstride, int64_t lo, int64_t n, int nv, int sys0, int S,
-                 const double2 *__restrict__ h, int64_t np_stride, double2 *__restrict__ part,
-                 double *__restrict__ npart) {
+                 const double2 *__restrict__ h, const double2 *__restrict__ hpart, int np,
+                 bool second, double2 *__restrict__ H, int m, int j, int64_t np_stride,
+                 double2 *__restrict__ part, double *__restrict__ npart) {
   constexpr int ROWS = kTileLanes * RP;
   __shared__ double2 hs[SUB ? SLOTS * 16 : 1];
   __shared__ double2 red[SUB ? 2 : 1][4][ROWS];
@@ -79,8 +81,23 @@ __global__ void __launch_bounds__(256)
   V += (int64_t)r * ld + lo;
   w += (int64_t)r * ld + lo;
   if (SUB) {
-    for (int i = threadIdx.x; i < SLOTS * 16; i += 256)
-      hs[i] = i < nv ? h[(int64_t)i * S + s] : make_double2(0.0, 0.0);
+    for (int i = threadIdx.x; i < SLOTS * 16; i += 256) {
+      double2 c = make_double2(0.0, 0.0);
+      if (i < nv && np > 0) {
+        for (int p = 0; p < np; ++p) {
+          const double2 q = hpart[((int64_t)i * S + s) * np_stride + p];
+          c.x += q.x;
+          c.y += q.y;
+        }
+        if (blockIdx.x == 0) {
+          double2 *hc = &H[((int64_t)s * (m + 1) + i) * m + j];
+          *hc = second ? make_double2(hc->x + c.x, hc->y + c.y) : c;
+        }
+      } else if (i < nv) {
+        c = h[(int64_t)i * S + s];
+      }
+      hs[i] = c;
+    }
     __syncthreads();
   }
   double2 acc[DOTS ? SLOTS : 1];
@@ -173,6 +190,10 @@ __global__ void __launch_bounds__(256)
       if (i < nv) part[((int64_t)i * S + s) * np_stride + blockIdx.x] = acc[t];
     }
 }
+// Up to this many partials per sum are added by the next pass itself: a launch of
+// its own for them costs more where the basis is short (1-lambda plate, 4 partials:
+// 40 -> 35 us per step and product; the passes then write alternate halves of part)
+constexpr int kInlineParts = 16;
 // work-groups per system of a pass over n rows with R right-hand sides: one per
 // 64-row tile up to about 8 per CU over all systems
 int64_t basis_groups(int64_t n, int R) {
@@ -181,27 +202,25 @@ int64_t basis_groups(int64_t n, int R) {
 }
 
 // out[i S + s] = sum_{p < np} part[(i S + s) np_stride + p], fixed order;
-// one wave per (i, s): blockIdx.x = i, blockIdx.y = s - sys0. With add (the
-// second pass), the sum of both passes goes to column j of H as well.
-__global__ void __launch_bounds__(64)
+// blockIdx.x = i, blockIdx.y = s - sys0. With add (the second pass), the sum of
+// both passes goes to column j of H as well. (A work-group per sum: with a wave the
+// up to 1024 partials came 16 loads deep, 5.8 us on the 16-lambda plate, now 3.6.)
+__global__ void __launch_bounds__(kRed)
     k_part_reduce(const double2 *part, int64_t np_stride, int np, int sys0, int S, double2 *out,
                   const double2 *add, double2 *H, int m, int j) {
   const int s = sys0 + blockIdx.y;
   const int64_t row = (int64_t)blockIdx.x * S + s;
   const double2 *pp = part + row * np_stride;
   double a = 0, b = 0;
-  for (int q = threadIdx.x; q < np; q += 64) {
+  for (int q = threadIdx.x; q < np; q += kRed) {
     a += pp[q].x;
     b += pp[q].y;
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    a += __shfl_xor(a, off, 64);
-    b += __shfl_xor(b, off, 64);
-  }
+  const double2 t = block_sum2(a, b);
   if (threadIdx.x == 0) {
-    out[row] = make_double2(a, b);
+    out[row] = t;
     if (add)
-      H[((int64_t)s * (m + 1) + blockIdx.x) * m + j] = make_double2(add[row].x + a, add[row].y + b);
+      H[((int64_t)s * (m + 1) + blockIdx.x) * m + j] = make_double2(add[row].x + t.x, add[row].y + t.y);
   }
 }
 
@@ -245,31 +264,145 @@ __global__ void k_normalize(const double2 *w, double2 *out, int64_t ld, int64_t 
 // work-group 0 stores it for the Givens kernel), v_{j+1} =
 // w / |w| into out, and the next step's preconditioned vector
 // z = dinv v_{j+1} (what k_precond would compute from out).
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kRed)
     k_normalize_next(const double2 *w, double2 *out, double2 *z, const double2 *dinv, int64_t ld,
                      int64_t lo, int64_t hi, int sys0, const double *part, int np, double *nrm) {
   __shared__ double snrm;
   const int r = blockIdx.y;
   const int s = sys0 + r;
-  if (threadIdx.x < 64) {
-    double a = 0;
-    for (int q = threadIdx.x; q < np; q += 64) a += part[(int64_t)s * kNormParts + q];
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (threadIdx.x == 0) {
-      snrm = a;
-      if (blockIdx.x == 0) nrm[s] = a;
-    }
+  const int64_t n = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double2 p = make_double2(0.0, 0.0), d = p;
+  if (n < hi) {  // in flight with the partials
+    p = w[(int64_t)r * ld + n];
+    d = dinv[n];
+  }
+  double a = 0;
+  for (int q = threadIdx.x; q < np; q += kRed) a += part[(int64_t)s * kNormParts + q];
+  const double2 t = block_sum2(a, 0.0);
+  if (threadIdx.x == 0) {
+    snrm = t.x;
+    if (blockIdx.x == 0) nrm[s] = t.x;
   }
   __syncthreads();
-  const int64_t n = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= hi) return;
   const double sv = snrm;
   const double inv = sv > 0 ? 1.0 / sqrt(sv) : 0.0;
-  const double2 p = w[(int64_t)r * ld + n];
   const double2 v = make_double2(p.x * inv, p.y * inv);
   out[(int64_t)r * ld + n] = v;
-  const double2 d = dinv[n];
   z[(int64_t)r * ld + n] = make_double2(v.x * d.x - v.y * d.y, v.x * d.y + v.y * d.x);
+}
+
+// Sum over a wave, the same in every lane: lane permutations within rows of 16
+// (DPP: quad swaps, mirrors of 8 and 16 lanes), then the four rows' sums.
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v) {
+  return v + __hiloint2double(
+                 __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                 __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = add_dpp<0xB1>(v);
+  v = add_dpp<0x4E>(v);
+  v = add_dpp<0x141>(v);
+  v = add_dpp<0x140>(v);
+  auto row = [&](int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+  };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
+// The whole Gram-Schmidt step of a small mesh (n <= 256 rows, at most 16 T
+// vectors) in one launch: both passes, the norm, v_{j+1} and the next z, by one
+// work-group of 16 waves per system. A wave holds vectors wave + 16 t in registers
+// (lane + 64 k the rows), so the basis is read once and the dot products stay
+// within the wave; the subtraction's sums over vectors go through LDS. The launches
+// are what a step costs here (about 4 us each, whatever they do): 4 to 6 of them
+// become one.
+constexpr int kSmallRows = 256, kSmallWaves = 16;
+constexpr int kSmallVectors = 64;  // (96 need 128 registers and spill: 21 us, the six launches 20)
+template <int T>
+__global__ void __launch_bounds__(64 * kSmallWaves)
+    k_arnoldi_small(double2 *V, const double2 *w, double2 *z, const double2 *dinv, int64_t ld,
+                    int64_t vstride, int64_t lo, int n, int j, int sys0, int S, double2 *H, int m,
+                    double *nrm) {
+  constexpr int NK = kSmallRows / 64;
+  __shared__ double2 ws[kSmallRows], red[kSmallWaves][kSmallRows];
+  const int r = blockIdx.x, s = sys0 + r, nv = j + 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double2 *Vr = V + (int64_t)r * ld + lo;
+  const int64_t base = (int64_t)r * ld + lo;
+  double2 v[T][NK], h[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int i = wave + kSmallWaves * t;
+    h[t] = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const int row = lane + 64 * k;
+      v[t][k] = (i < nv && row < n) ? Vr[(int64_t)i * vstride + row] : make_double2(0.0, 0.0);
+    }
+  }
+  if (tid < kSmallRows) ws[tid] = tid < n ? w[base + tid] : make_double2(0.0, 0.0);
+  __syncthreads();
+  for (int pass = 0; pass < 2; ++pass) {
+    double2 y[NK], p[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      y[k] = ws[lane + 64 * k];
+      p[k] = make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      double a = 0, b = 0;
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        a += v[t][k].x * y[k].x + v[t][k].y * y[k].y;
+        b += v[t][k].x * y[k].y - v[t][k].y * y[k].x;
+      }
+      const double2 c = make_double2(wave_sum(a), wave_sum(b));
+      h[t].x += c.x;
+      h[t].y += c.y;
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        p[k].x += c.x * v[t][k].x - c.y * v[t][k].y;
+        p[k].y += c.x * v[t][k].y + c.y * v[t][k].x;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NK; ++k) red[wave][lane + 64 * k] = p[k];
+    __syncthreads();
+    if (tid < kSmallRows) {
+      double2 a = ws[tid];
+#pragma unroll
+      for (int q = 0; q < kSmallWaves; ++q) {
+        a.x -= red[q][tid].x;
+        a.y -= red[q][tid].y;
+      }
+      ws[tid] = a;
+    }
+    __syncthreads();
+  }
+  if (lane == 0)
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int i = wave + kSmallWaves * t;
+      if (i < nv) H[((int64_t)s * (m + 1) + i) * m + j] = h[t];
+    }
+  double a = 0;  // |w|^2, by every wave in the same order
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    const double2 y = ws[lane + 64 * k];
+    a += y.x * y.x + y.y * y.y;
+  }
+  a = wave_sum(a);
+  if (tid == 0) nrm[s] = a;
+  const double inv = a > 0 ? 1.0 / sqrt(a) : 0.0;
+  if (tid < n) {
+    const double2 u = make_double2(ws[tid].x * inv, ws[tid].y * inv), d = dinv[lo + tid];
+    Vr[(int64_t)nv * vstride + tid] = u;
+    z[base + tid] = make_double2(u.x * d.x - u.y * d.y, u.x * d.y + u.y * d.x);
+  }
 }
 
 // z[r][row] = v[r][row] / d[row]
@@ -388,6 +521,7 @@ struct GmresDev {
   double2 *cs, *sn;  // [S][m]
   double2 *g;      // [S][m+1]
   int *active;     // [S]
+  int *poll;       // [S] the same for the host (pinned), which polls it
   int *its;        // [S] iterations counted
   int *jend;       // [S] columns of the current cycle
   double *tol_abs;  // [S] stop when |g_{j+1}| <= tol_abs
@@ -458,6 +592,7 @@ __global__ void __launch_bounds__(64)
       const double res = sqrt(gn.x * gn.x + gn.y * gn.y);
       if (res <= d.tol_abs[s] || den == 0.0) {
         d.active[s] = 0;
+        d.poll[s] = 0;
         stop = 1;
       }
     }
@@ -471,38 +606,61 @@ __global__ void __launch_bounds__(64)
     for (int i = threadIdx.x; i <= j0 + q + 1; i += 64) Hs[i * m + j0 + q] = gsh[q * L + i];
 }
 
-// y = H^-1 g on the jend x jend upper triangle (y stored [i][s] like h); one
-// 64-lane work-group per system: rows bottom-up, each row's sum over the
-// known y_k split over the lanes (fixed order). LDS: m complex values.
+// y = H^-1 g on the jend x jend upper triangle (y stored [i][s] like h); one wave
+// per system, lane l with rows l + 64 q. Columns are taken from the last: the lane
+// that holds row i has y_i, which all lanes take off their rows above it, so the
+// chain per column is a division and a lane broadcast, and eight columns are loaded
+// ahead of it. (Row by row, with a sum over the lanes and a barrier each, 100
+// columns took 72 us.)
+constexpr int kBackRows = 4;  // 64 rows each: restart <= 200
 __global__ void __launch_bounds__(64) k_backsub(GmresDev d, double2 *y, int m, int S) {
-  const int s = blockIdx.x;
-  extern __shared__ double2 ysh[];
+  const int s = blockIdx.x, lane = threadIdx.x;
   const int n = d.jend[s];
   const double2 *Hs = d.H + (int64_t)s * (m + 1) * m;
-  const double2 *g = d.g + (int64_t)s * (m + 1);
-  for (int i = n - 1; i >= 0; --i) {
-    double ax = 0, ay = 0;
-    for (int k = i + 1 + threadIdx.x; k < n; k += 64) {
-      const double2 t = cmul_(Hs[i * m + k], ysh[k]);
-      ax += t.x;
-      ay += t.y;
+  const double2 *gs = d.g + (int64_t)s * (m + 1);
+  double2 g[kBackRows], inv[kBackRows];  // right-hand side; conj(h_kk) / |h_kk|^2
+#pragma unroll
+  for (int q = 0; q < kBackRows; ++q) {
+    const int k = lane + 64 * q;
+    g[q] = inv[q] = make_double2(0.0, 0.0);
+    if (k < n) {
+      g[q] = gs[k];
+      const double2 h = Hs[k * m + k];
+      const double dd = h.x * h.x + h.y * h.y;
+      if (dd != 0.0) inv[q] = make_double2(h.x / dd, -h.y / dd);  // else y_k = 0
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      ax += __shfl_xor(ax, off, 64);
-      ay += __shfl_xor(ay, off, 64);
-    }
-    if (threadIdx.x == 0) {
-      const double2 gi = g[i];
-      const double2 acc = make_double2(gi.x - ax, gi.y - ay);
-      const double2 hd = Hs[i * m + i];
-      const double dd = hd.x * hd.x + hd.y * hd.y;
-      ysh[i] = dd == 0.0 ? make_double2(0.0, 0.0)
-                         : make_double2((acc.x * hd.x + acc.y * hd.y) / dd,
-                                        (acc.y * hd.x - acc.x * hd.y) / dd);
-    }
-    __syncthreads();
   }
-  for (int i = threadIdx.x; i < n; i += 64) y[(int64_t)i * S + s] = ysh[i];
+#pragma unroll
+  for (int b = kBackRows - 1; b >= 0; --b) {  // columns 64 b .. 64 b + 63
+    for (int i1 = min(n, 64 * b + 64); i1 > 64 * b; i1 -= 8) {
+      double2 h[8][kBackRows];
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int q = 0; q <= b; ++q) {
+          const int i = i1 - 1 - c, k = lane + 64 * q;
+          h[c][q] = (i >= 64 * b && k < i) ? Hs[k * m + i] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int i = i1 - 1 - c;
+        if (i < 64 * b) break;
+        const double2 mine = cmul_(g[b], inv[b]);
+        auto at = [&](double v) {
+          return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i & 63),
+                                  __builtin_amdgcn_readlane(__double2loint(v), i & 63));
+        };
+        const double2 yi = make_double2(at(mine.x), at(mine.y));
+        if (lane == 0) y[(int64_t)i * S + s] = yi;
+#pragma unroll
+        for (int q = 0; q <= b; ++q) {
+          const double2 t = cmul_(h[c][q], yi);
+          g[q].x -= t.x;
+          g[q].y -= t.y;
+        }
+      }
+    }
+  }
 }
 
 struct Work {
@@ -526,6 +684,7 @@ struct SolverState {
   Work wk;
   double2 *dinv = nullptr;  // Jacobi: 1 / diag(Z^MOM)
   std::vector<void *> bufs;
+  int *poll = nullptr;  // pinned: the systems still active, written by k_givens
   hipStream_t stream = nullptr;
   hipEvent_t entry = nullptr;
   // (precision, j0, j1, meshes still iterating as bits)
@@ -553,6 +712,8 @@ SolverState &solver_state(Plan *pl, int R, int m) {
   drop_graphs(st);
   for (void *p : st.bufs) dev_free(pl, p);
   st.bufs.clear();
+  if (st.poll) HIPCHECK(hipHostFree(st.poll));
+  st.poll = nullptr;
   st.R = st.m = 0;
   st.warm[0] = st.warm[1] = false;
   auto alloc = [&](size_t bytes) {
@@ -571,7 +732,7 @@ SolverState &solver_state(Plan *pl, int R, int m) {
   wk.y = (double2 *)alloc(sizeof(double2) * (size_t)(m + 1) * S);
   wk.nrm = (double *)alloc(sizeof(double) * S);
   wk.step_nrm = (double *)alloc(sizeof(double) * (size_t)m * S);
-  wk.np_stride = 0;
+  wk.np_stride = 2 * kInlineParts;
   for (auto &md : pl->mesh) wk.np_stride = std::max(wk.np_stride, basis_groups(md.hp.n, R));
   wk.part = (double2 *)alloc(sizeof(double2) * (size_t)(m + 1) * S * wk.np_stride);
   wk.npart = (double *)alloc(sizeof(double) * (size_t)S * kNormParts);
@@ -580,6 +741,8 @@ SolverState &solver_state(Plan *pl, int R, int m) {
   wk.dev.sn = (double2 *)alloc(sizeof(double2) * (size_t)S * m);
   wk.dev.g = (double2 *)alloc(sizeof(double2) * (size_t)S * (m + 1));
   wk.dev.active = (int *)alloc(sizeof(int) * S);
+  HIPCHECK(hipHostMalloc((void **)&st.poll, sizeof(int) * S, hipHostMallocMapped));
+  HIPCHECK(hipHostGetDevicePointer((void **)&wk.dev.poll, st.poll, 0));
   wk.dev.its = (int *)alloc(sizeof(int) * S);
   wk.dev.jend = (int *)alloc(sizeof(int) * S);
   wk.dev.tol_abs = (double *)alloc(sizeof(double) * S);
@@ -613,24 +776,44 @@ void arnoldi_step(Ctx &c, aim_precision prec, Work &wk, int j, int m) {
     }
     const int64_t n = md.hp.n;
     const int nb = (int)basis_groups(n, R), nv = j + 1, sys0 = mi * R;
-    auto pass = [&](auto kern, const double2 *h) {
+    if (n <= kSmallRows && nv <= kSmallVectors) {
+      auto small = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(R), dim3(64 * kSmallWaves), 0, c.s, wk.V, wk.w, wk.z, c.dinv,
+                           ld, vstride, md.offset, (int)n, j, sys0, S, wk.dev.H, m,
+                           wk.step_nrm + (int64_t)j * S);
+        LAUNCHCHECK();
+      };
+      if (nv <= 16)
+        small(k_arnoldi_small<1>);
+      else if (nv <= 32)
+        small(k_arnoldi_small<2>);
+      else
+        small(k_arnoldi_small<4>);
+      ++mi;
+      continue;
+    }
+    const int np = nb <= kInlineParts ? nb : 0;
+    double2 *const part2 = np ? wk.part + kInlineParts : wk.part;
+    auto pass = [&](auto kern, const double2 *h, const double2 *from, double2 *to, bool second) {
       hipLaunchKernelGGL(kern, dim3((unsigned)nb, R), dim3(256), 0, c.s, wk.V, wk.w, ld, vstride,
-                         md.offset, n, nv, sys0, S, h, wk.np_stride, wk.part, wk.npart);
+                         md.offset, n, nv, sys0, S, h, from, np, second, wk.dev.H, m, j,
+                         wk.np_stride, to, wk.npart);
       LAUNCHCHECK();
     };
     auto reduce = [&](double2 *h, const double2 *add) {
-      hipLaunchKernelGGL(k_part_reduce, dim3(nv, R), dim3(64), 0, c.s, wk.part, wk.np_stride, nb,
+      if (np) return;
+      hipLaunchKernelGGL(k_part_reduce, dim3(nv, R), dim3(kRed), 0, c.s, wk.part, wk.np_stride, nb,
                          sys0, S, h, add, wk.dev.H, m, j);
       LAUNCHCHECK();
     };
     // slots: the smallest tile that holds the nv vectors
     auto passes = [&](auto slots_, auto rp_) {
       constexpr int SL = decltype(slots_)::value, RP = decltype(rp_)::value;
-      pass(k_basis_pass<SL, RP, false, true, false>, nullptr);
+      pass(k_basis_pass<SL, RP, false, true, false>, nullptr, nullptr, wk.part, false);
       reduce(wk.h1, nullptr);
-      pass(k_basis_pass<SL, RP, true, true, false>, wk.h1);
+      pass(k_basis_pass<SL, RP, true, true, false>, wk.h1, wk.part, part2, false);
       reduce(wk.h2, wk.h1);
-      pass(k_basis_pass<SL, RP, true, false, true>, wk.h2);
+      pass(k_basis_pass<SL, RP, true, false, true>, wk.h2, part2, nullptr, true);
     };
     if (nv <= 16)
       passes(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
@@ -763,7 +946,7 @@ int gmres_run(Ctx &c, SolverState &st, aim_precision prec, bool graphs, const do
     std::vector<double2> g0((size_t)S * (m + 1), make_double2(0, 0));
     std::vector<double> tabs(S);
     for (int s = 0; s < S; ++s) {
-      act[s] = !done[s];
+      st.poll[s] = act[s] = !done[s];  // (the stream is synchronised: no kernel writes it now)
       g0[(size_t)s * (m + 1)] = make_double2(std::sqrt(r2[s]), 0.0);
       tabs[s] = tol_s[s] * std::sqrt(rhs_norm2[s]);
     }
@@ -788,16 +971,14 @@ int gmres_run(Ctx &c, SolverState &st, aim_precision prec, bool graphs, const do
       nprod += j1 - j;
       total += j1 - j;
       j = j1;
-      HIPCHECK(hipMemcpyAsync(act.data(), wk.dev.active, sizeof(int) * S, hipMemcpyDeviceToHost, c.s));
       HIPCHECK(hipStreamSynchronize(c.s));
       bool any = false;
-      for (int s = 0; s < S; ++s) any |= (bool)act[s];
+      for (int s = 0; s < S; ++s) any |= (bool)(act[s] = st.poll[s]);
       if (!any) break;
       c.on = meshes_of(act);
     }
     // d += D^-1 V y, y = H^-1 g per system (systems done before the cycle: jend = 0)
-    hipLaunchKernelGGL(k_backsub, dim3(S), dim3(64), sizeof(double2) * (size_t)m, c.s, wk.dev,
-                       wk.y, m, S);
+    hipLaunchKernelGGL(k_backsub, dim3(S), dim3(64), 0, c.s, wk.dev, wk.y, m, S);
     LAUNCHCHECK();
     {
       int mi = 0;
@@ -827,6 +1008,7 @@ void solver_release(Plan *pl) {
   if (st.stream) (void)hipStreamSynchronize(st.stream);
   drop_graphs(st);
   for (void *p : st.bufs) dev_free(pl, p);
+  if (st.poll) (void)hipHostFree(st.poll);
   if (st.entry) (void)hipEventDestroy(st.entry);
   if (st.stream) (void)hipStreamDestroy(st.stream);
   delete pl->solver;

@@ -50,7 +50,8 @@ def _reference(side, wave, steps, restart):
 @pytest.mark.parametrize("side,nrhs,steps,restart", [
     (1.0, 1, 1, 5), (1.0, 3, 8, 8), (1.0, 1, 13, 40), (1.0, 2, 16, 16), (1.0, 1, 17, 17),
     (2.0, 1, 33, 40), (2.0, 3, 34, 34), (2.0, 1, 65, 80), (2.0, 1, 113, 200), (2.0, 3, 120, 130),
-    (2.0, 1, 30, 9), (1.0, 3, 29, 12), (4.5, 1, 20, 25), (4.5, 2, 66, 70),
+    (1.0, 2, 33, 33), (1.0, 1, 66, 90), (1.0, 1, 98, 100), (2.0, 1, 30, 9), (1.0, 3, 29, 12),
+    (4.5, 1, 20, 25), (4.5, 2, 66, 70), (2.0, 2, 129, 129), (2.0, 1, 196, 200),
 ])
 def test_iterate_after_k_steps(side, nrhs, steps, restart, graphs):
     from paper_1010_1456_amd import aim as A
