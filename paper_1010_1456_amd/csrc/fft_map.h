@@ -163,5 +163,12 @@ inline ContigMap select_lines(ContigMap m, const int32_t *sel, int64_t nsel, int
   return m;
 }
 
+// where the plane pass puts its output: element (f, kz, x, y) at
+// f fs + kz zs + x xs + y ys
+struct PlaneOut {
+  int64_t fs, zs;
+  int xs, ys;
+};
+
 }  // namespace fftk
 }  // namespace aim

@@ -1,0 +1,64 @@
+// Passes over kz-outer grids for double2: the run-time length selects the compiled
+// kernel set.
+#include "fft_plane.h"
+
+namespace aim {
+void fft_plane_pass(const double2 *in, double2 *out, const fftk::PlaneOut &om, const FftPlan &pl, int Nx,
+                    int Ny, int F, int Pz, int Hy, const double2 *ghat, const double2 *tw,
+                    const int32_t *yrange, hipStream_t s) {
+  if (F <= 0) return;
+  switch (pl.P) {
+#define AIM_X(P, a, b, c)                                                                      \
+  case P:                                                                                      \
+    fftk::launch_plane<double, fftk::PlanC<a, b, c>>(in, out, om, Nx, Ny, F, Pz, Hy, ghat, tw,  \
+                                                    yrange, s);                                \
+    return;
+    AIM_FOR_EACH_FFT_PLAN(AIM_X)
+#undef AIM_X
+    default:
+      break;
+  }
+  fftk::bad_length(pl.P);
+}
+
+void fft_zplane_pass(const double2 *in, double2 *out, const FftPlan &pl, int n_in, int n_out, int F,
+                     int64_t nl, const int32_t *sel, const int32_t *range, int64_t A1,
+                     bool inverse, const double2 *tw, hipStream_t s) {
+  if (F <= 0 || nl <= 0) return;
+  switch (pl.P) {
+#define AIM_X(P, a, b, c)                                                                      \
+  case P:                                                                                      \
+    fftk::launch_zplane<double, fftk::PlanC<a, b, c>>(in, out, n_in, n_out, F, nl, sel, range,  \
+                                                     A1, inverse, tw, s);                      \
+    return;
+    AIM_FOR_EACH_FFT_PLAN(AIM_X)
+#undef AIM_X
+    default:
+      break;
+  }
+  fftk::bad_length(pl.P);
+}
+
+bool fft_plane_available(const double2 *, const FftPlan &pl) {
+  switch (pl.P) {
+#define AIM_X(P, a, b, c) \
+  case P:                 \
+    return fftk::PlaneCfg<double, fftk::PlanC<a, b, c>>::ok;
+    AIM_FOR_EACH_FFT_PLAN(AIM_X)
+#undef AIM_X
+    default:
+      return false;
+  }
+}
+bool fft_zplane_available(const double2 *, const FftPlan &pl) {
+  switch (pl.P) {
+#define AIM_X(P, a, b, c) \
+  case P:                 \
+    return fftk::zplane_ok<fftk::PlanC<a, b, c>>();
+    AIM_FOR_EACH_FFT_PLAN(AIM_X)
+#undef AIM_X
+    default:
+      return false;
+  }
+}
+}  // namespace aim

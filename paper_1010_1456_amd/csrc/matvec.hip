@@ -393,6 +393,16 @@ const float2 *ghat2d_of<float>(const MeshDev &md) {
   return md.ghat2d32;
 }
 template <typename T>
+const cx<T> *ghatp_of(const MeshDev &md);
+template <>
+const double2 *ghatp_of<double>(const MeshDev &md) {
+  return md.ghatp64;
+}
+template <>
+const float2 *ghatp_of<float>(const MeshDev &md) {
+  return md.ghatp32;
+}
+template <typename T>
 const cx<T> *tw_of(const MeshDev &md, int d);
 template <>
 const double2 *tw_of<double>(const MeshDev &md, int d) {
@@ -425,23 +435,35 @@ static cx<T> *zeroed_buffer(Plan *pl, void *(&buf)[2], size_t (&have)[2], size_t
   }
   return (cx<T> *)buf[prec];
 }
-// the mesh's projected source grid in `layout` (1: 3-D grid [F][V0], 2: the
-// scatterer's plane [F][Nx Ny]), zero where no projection entry lands. The
-// projection writes the occupied nodes only, so a buffer last written in the
-// other layout (the full 3-D inspection of a planar scatterer, or the plane
-// after it) is cleared first.
+// a zeroed buffer in `layout`, cleared first if it was last written in another
+// one (whose zero nodes are others); a captured graph of the old layout is dropped
+template <typename T>
+static cx<T> *layout_buffer(Plan *pl, void *(&buf)[2], size_t (&have)[2], int (&in)[2],
+                            size_t bytes, int layout, hipStream_t s) {
+  const int prec = sizeof(T) == 8 ? 0 : 1;
+  const size_t had = have[prec];
+  cx<T> *p = zeroed_buffer<T>(pl, buf, have, bytes, s);
+  if (in[prec] != layout) {
+    ++pl->work_gen;
+    if (have[prec] == had) {  // not just zeroed
+      const int64_t n = (int64_t)(had / sizeof(cx<T>));
+      hipLaunchKernelGGL((k_zero<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
+      LAUNCHCHECK();
+    }
+  }
+  in[prec] = layout;
+  return p;
+}
+// the mesh's projected source grid (layouts as MeshDev::src_layout), zero where no
+// projection entry lands: the projection writes the occupied nodes only
 template <typename T>
 static cx<T> *src_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStream_t s) {
-  const int prec = sizeof(T) == 8 ? 0 : 1;
-  const size_t had = md.src_bytes[prec];
-  cx<T> *p = zeroed_buffer<T>(pl, md.src, md.src_bytes, bytes, s);
-  if (md.src_bytes[prec] == had && md.src_layout[prec] != layout) {  // not just zeroed
-    const int64_t n = (int64_t)(had / sizeof(cx<T>));
-    hipLaunchKernelGGL((k_zero<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-    LAUNCHCHECK();
-  }
-  md.src_layout[prec] = layout;
-  return p;
+  return layout_buffer<T>(pl, md.src, md.src_bytes, md.src_layout, bytes, layout, s);
+}
+// its forward z transforms, zero on the z lines without a source
+template <typename T>
+static cx<T> *fz_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStream_t s) {
+  return layout_buffer<T>(pl, md.fz, md.fz_bytes, md.fz_layout, bytes, layout, s);
 }
 
 void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStream_t s) {
@@ -523,6 +545,21 @@ static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int6
   LAUNCHCHECK();
 }
 
+// plane by plane where both lengths have the kernel; a flat scatterer's few planes only
+// up to 81 points, above which one work-group's chain takes longer than three launches
+// (c64, product: 3-lambda plate 17.5 -> 13.4 us at 63 points, 5-lambda plate 18.6 ->
+// 19.1 us at 108); a caller that asks for tile rows or field groups gets the passes
+// these belong to
+void choose_plane_fft(const Plan *pl, MeshDev &md) {
+  auto can = [&](auto *v) {
+    return (pl->params.tuning & 0xffff) == 0 && md.plan[0].P == md.plan[1].P &&
+           fft_plane_available(v, md.plan[0]) &&
+           (md.planar_z >= 0 ? md.plan[0].P <= 81 : fft_zplane_available(v, md.plan[2]));
+  };
+  md.plane_fft[0] = can((const double2 *)nullptr);
+  md.plane_fft[1] = pl->mixed && can((const float2 *)nullptr);
+}
+
 template <typename T, typename TX>
 void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, int stop,
                 hipStream_t s, hipEvent_t *ev, bool full3d, StageView *views, int first) {
@@ -557,13 +594,18 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   const int npw = md.gather_npw[prec];
   if (npw < 1 || npw > 64 || 64 % npw != 0)
     throw Error(AIM_ERR_ARG, "projection gather: nodes per wave must divide 64");
+  // the passes along y and x plane by plane, when the product runs through (the
+  // stage boundaries between them then fall together: the forward y step carries
+  // the time of all three)
+  const bool planes = md.plane_fft[prec] && stop >= 6 && first <= 1 && !full3d;
   if (md.planar_z >= 0 && !full3d) {
     // every source on the plane z = planar_z, and only that plane weighted by
     // the interpolation: the plane alone, g0 = [F][Nx][Ny], 2-D propagation
     // (y passes, x pass with the 2-D spectrum)
     const int64_t A1 = (int64_t)Nx * Ny, V2 = (int64_t)Nx * Py;
     cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * A1, s);
-    cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
+    cx<T> *g2 = planes ? nullptr
+                       : (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * A1, 2, s);
     mark(0);
     if (first <= 1)
@@ -572,6 +614,13 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     view(1, gs, Nx, Ny, A1, Ny, 1);
     if (stop <= 1) return;
     mark(2);
+    if (planes) {
+      fft_plane_pass(gs, g0, fftk::PlaneOut{1, 0, (int)(Ny * F), (int)F}, md.plan[0], Nx, Ny,
+                     (int)F, 1, md.H[1], ghat2d_of<T>(md), tw_of<T>(md, 0), nullptr, s);
+      for (int i = 3; i <= 6; ++i) mark(i);
+      view(6, g0, Nx, Ny, 1, (int64_t)Ny * F, F);
+      return;
+    }
     if (first <= 3)
       fft_pass_contig(gs, g2, md.plan[1], Ny, Py, F * Nx, fftk::contig_map(Ny),
                       fftk::contig_map(Py), false, tw_of<T>(md, 1), s);
@@ -589,6 +638,32 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     mark(5);
     mark(6);
     view(6, g0, Nx, Ny, 1, (int64_t)Ny * F, F);
+    return;
+  }
+  if (planes) {
+    // kz-outer grids gz and g1 [F][Pz][Nx][Ny] between the z passes
+    const int64_t A1 = (int64_t)Nx * Ny, nl = md.n_occ_lines;
+    const size_t bytes = sizeof(cx<T>) * F * Pz * A1;
+    cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * V0, s);
+    cx<T> *g1 = (cx<T> *)work_buffer(pl, md.lane, prec, 1, bytes, s);
+    cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
+    cx<T> *gz = fz_buffer<T>(pl, md, bytes, 2, s);
+    mark(0);
+    project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
+    mark(1);
+    view(1, gs, A1, Nz, V0, Nz, 1);
+    fft_zplane_pass(gs, gz, md.plan[2], Nz, Pz, (int)F, nl, md.occ_lines, md.occ_zrange, A1, false,
+                    tw_of<T>(md, 2), s);
+    mark(2);
+    view(2, gz, A1, Pz, Pz * A1, 1, A1);
+    fft_plane_pass(gz, g1, fftk::PlaneOut{Pz * A1, A1, Ny, 1}, md.plan[0], Nx, Ny, (int)F, Pz,
+                   md.H[1], ghatp_of<T>(md), tw_of<T>(md, 0), md.occ_yrange, s);
+    for (int i = 3; i <= 5; ++i) mark(i);
+    view(5, g1, A1, Pz, Pz * A1, 1, A1);
+    fft_zplane_pass(g1, g0, md.plan[2], Pz, Nz, (int)F, nl, md.occ_lines, md.occ_zrange, A1, true,
+                    tw_of<T>(md, 2), s);
+    view(6, g0, A1, Nz, 1, (int64_t)Nz * F, F);
+    mark(6);
     return;
   }
   if (thin_layout<T>(Pz)) {
@@ -659,7 +734,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   // sides in turn, so several take the two-launch form (right-hand sides in
   // parallel).
   if (first > 2) {  // (set-up) the passes after the forward z pass alone
-    gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
+    gz = fz_buffer<T>(pl, md, sizeof(cx<T>) * F * V1, 1, s);
   } else if (stop <= 1 || !md.fuse_proj[prec] || nrhs > 1 ||
       !anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, (int64_t)Nx * Ny, g1,
                    Pzs, (int64_t)Nx * Ny * Pzs, tw_of<T>(md, 2), md.plan[2], s)) {
@@ -673,7 +748,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
                       fftk::contig_map(Pzs), false, tw_of<T>(md, 2), s);
     } else {  // the occupied lines into the mesh's zeroed buffer (the others stay zero)
       const int64_t nl = md.n_occ_lines, A1 = (int64_t)Nx * Ny;
-      gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
+      gz = fz_buffer<T>(pl, md, sizeof(cx<T>) * F * V1, 1, s);
       fft_pass_contig(gs, gz, md.plan[2], Nz, Pz, F * nl,
                       fftk::select_lines(fftk::contig_map(Nz), md.occ_lines, nl, A1, md.occ_zrange),
                       fftk::select_lines(fftk::contig_map(Pzs), md.occ_lines, nl, A1), false,
@@ -1000,7 +1075,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       const bool thin = prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]);
-      if (thin || !fft_anterp_fused(md.plan[2])) {
+      if (thin || md.plane_fft[prec] || !fft_anterp_fused(md.plan[2])) {
         md.fuse_proj[prec] = 0;
         continue;
       }
@@ -1035,7 +1110,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
           (prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]));
       md.xy_groups[prec] = 1;
       md.x_row[prec] = md.y_row[prec] = rows == 2 ? 64 : 128;
-      if (rows == 0) {
+      if (rows == 0 && !md.plane_fft[prec]) {
         const float x128 = time_stages(prec, 4, 4);
         md.x_row[prec] = 64;
         if (time_stages(prec, 4, 4) >= margin * x128) md.x_row[prec] = 128;

@@ -186,6 +186,15 @@ __global__ void k_ghat_zsum(const double2 *oct, double2 *out, int Hx, int Hy, in
   out[t] = acc;
 }
 
+// the octant kz-outer: out[(kz Hx + kx) Hy + ky] = oct[(kx Hy + ky) Hz + kz]
+template <typename V>
+__global__ void k_octant_planes(const V *oct, V *out, int Hx, int Hy, int Hz) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t plane = (int64_t)Hx * Hy;
+  if (t >= plane * Hz) return;
+  out[t] = oct[(t % plane) * Hz + t / plane];
+}
+
 __global__ void k_extract_octant(const double2 *full, double2 *oct, int Py, int Pz, int Hx, int Hy,
                                  int Hz, double scale) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -352,12 +361,14 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     md.plane_K = K2;
   }
 
+  for (int d = 0; d < 3; ++d)
+    if (!fft_plan_for(h.pad[d], &md.plan[d])) throw Error(AIM_ERR_ARG, "unsupported FFT length");
+  choose_plane_fft(pl, md);
   node_tables_mesh(pl, md, s);
   phase_done(AIM_SETUP_PROJECTION);
 
-  // FFT plans, twiddles, Green's spectrum octant
+  // twiddles, Green's spectrum octant
   for (int d = 0; d < 3; ++d) {
-    if (!fft_plan_for(h.pad[d], &md.plan[d])) throw Error(AIM_ERR_ARG, "unsupported FFT length");
     md.H[d] = h.pad[d] / 2 + 1;
     twiddles(pl, h.pad[d], &md.tw64[d], &md.tw32[d], s);
   }
@@ -387,6 +398,15 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
                          (const double *)md.ghat64, (float *)md.ghat32, 2 * noct);
       LAUNCHCHECK();
     }
+    auto planes = [&](auto *oct, auto *&out) {
+      using V = std::remove_reference_t<decltype(*oct)>;
+      out = (V *)dev_alloc(pl, sizeof(V) * noct);
+      hipLaunchKernelGGL((k_octant_planes<V>), dim3(blocks_for(noct, 256)), dim3(256), 0, s, oct,
+                         out, md.H[0], md.H[1], md.H[2]);
+      LAUNCHCHECK();
+    };
+    if (md.planar_z < 0 && md.plane_fft[0]) planes(md.ghat64, md.ghatp64);
+    if (md.planar_z < 0 && md.plane_fft[1]) planes(md.ghat32, md.ghatp32);
     HIPCHECK(hipStreamSynchronize(s));
     dev_free(pl, e0);
     dev_free(pl, e1);
