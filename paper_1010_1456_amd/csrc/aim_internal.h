@@ -185,10 +185,10 @@ struct MeshDev {
   int32_t *plane_anchor = nullptr;    // n
   int32_t *plane_soff = nullptr;      // (M+1)^2
   int plane_K = 0;                    // (M+1)^2
-  // per precision: the passes along y and x run plane by plane in LDS
-  // (fft_plane.h), on kz-outer grids [F][Pz][Nx][Ny]; for a scatterer off one grid
-  // plane with the octant kz-outer too, [H2][H0][H1]
-  bool plane_fft[2] = {false, false};
+  // per precision: up to this many planes (fields times kz), the passes along y and
+  // x run plane by plane in LDS (fft_plane.h), on kz-outer grids [F][Pz][Nx][Ny]; for
+  // a scatterer off one grid plane with the octant kz-outer too, [H2][H0][H1]
+  int64_t plane_fft[2] = {0, 0};
   double2 *ghatp64 = nullptr;
   float2 *ghatp32 = nullptr;
   // occupied nodes per wave of the projection gather, per precision [FP64,
@@ -220,11 +220,13 @@ struct MeshDev {
   // are not those of the other, so a change of layout clears the buffer
   int src_layout[2] = {0, 0};
   // forward z transforms of those grids per precision [4 nrhs][Nx Ny][Pzs]
-  // (layout 1, kz-blocked grids only) or [4 nrhs][Pz][Nx Ny] (layout 2): zero
-  // once, after which the forward z pass writes the occupied z lines only
+  // (kz-blocked grids only), and kz-outer [4 nrhs][Pz][Nx Ny] (passes plane by
+  // plane): zero once, after which the forward z pass writes the occupied z lines
+  // only
   void *fz[2] = {nullptr, nullptr};
   size_t fz_bytes[2] = {0, 0};
-  int fz_layout[2] = {0, 0};
+  void *fzp[2] = {nullptr, nullptr};
+  size_t fzp_bytes[2] = {0, 0};
 };
 
 // milliseconds since an arbitrary epoch (steady clock)
@@ -280,8 +282,8 @@ void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 // area, anchor3: device, per triangle and 3 per basis
 void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *anchor3,
                     hipStream_t s);
-// whether the passes along y and x of one mesh run plane by plane (md.plane_fft),
-// from its FFT plans and planar_z
+// up to how many planes the passes along y and x of one mesh run plane by plane
+// (md.plane_fft), from its FFT plans and planar_z
 void choose_plane_fft(const Plan *pl, MeshDev &md);
 // times the alternative kernel variants of one mesh and keeps the faster
 void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s);
@@ -322,8 +324,9 @@ AIM_DECLARE_XY(double2)
 #undef AIM_DECLARE_XY
 
 // the y, x and y passes of kz-outer planes in one launch, and the z passes between
-// kz-outer grids (fft_plane_*.hip; see fft_plane.h). available: the length has the
-// kernel (the argument only names the precision)
+// kz-outer grids (fft_plane_*.hip; see fft_plane.h). plane_limit: the
+// planes up to which the length's kernel is the faster one (0: it has none); the first
+// argument only names the precision
 #define AIM_DECLARE_PLANE(V)                                                                      \
   void fft_plane_pass(const V *in, V *out, const fftk::PlaneOut &om, const FftPlan &pl, int Nx,   \
                       int Ny, int F, int Pz, int Hy, const V *ghat, const V *tw,                  \
@@ -331,7 +334,7 @@ AIM_DECLARE_XY(double2)
   void fft_zplane_pass(const V *in, V *out, const FftPlan &pl, int n_in, int n_out, int F,        \
                        int64_t nl, const int32_t *sel, const int32_t *range, int64_t A1,          \
                        bool inverse, const V *tw, hipStream_t s);                                 \
-  bool fft_plane_available(const V *, const FftPlan &pl);                                         \
+  int64_t fft_plane_limit(const V *, const FftPlan &pl);                                          \
   bool fft_zplane_available(const V *, const FftPlan &pl);
 AIM_DECLARE_PLANE(float2)
 AIM_DECLARE_PLANE(double2)

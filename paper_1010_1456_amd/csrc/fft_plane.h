@@ -65,6 +65,30 @@ struct PlaneCfg {
   static constexpr int NW = waves();
 };
 
+// planes (fields times kz) up to which the kernel is faster than the separate passes,
+// 0: never. Not all lengths divide well among the lanes of a wave: with P = R0 RM a
+// line takes R0 lanes, of which the outer stages use RM (96 = 12 x 8, 112 = 14 x 8, 126
+// = 14 x 9), and long lines leave one work-group per CU. Product on a 2-lambda sphere,
+// separate -> plane by plane, us, with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46
+// -> 37, 74 -> 59, 141 -> 114, 275 -> 185; 90 47 -> 40, 78 -> 74, 156 -> 151, 297 ->
+// 268; 96 47 -> 46, 78 -> 84, 157 -> 182, 312 -> 331; 108 53 -> 45, 91 -> 88, 197 ->
+// 177, 389 -> 333; 112 54 -> 52, with 8 206 -> 248; 120 56 -> 48, 100 -> 96, 243 -> 209,
+// 440 -> 391; 126 59 -> 53, 110 -> 107, 257 -> 236, 489 -> 456; 144 62 -> 68, with 8 308
+// -> 320; 162 84 -> 78, 180 -> 174, 492 -> 416, 935 -> 815. c128: 81 63 -> 53, 115 ->
+// 89, 263 -> 181, 485 -> 346; 90 66 -> 65, 124 -> 131, 304 -> 287, 550 -> 550; 96 66 ->
+// 70; 108 74 -> 70, 154 -> 159, 396 -> 355, 705 -> 692; 112 75 -> 120; 120 83 -> 72, 179
+// -> 167, 432 -> 410, 836 -> 777; 126 89 -> 84, 195 -> 202, 471 -> 505, 916 -> 983.
+// Lengths up to 72 are faster by 5 to 35% throughout.
+template <typename T, class PC>
+constexpr int64_t plane_limit() {
+  constexpr int P = PC::P;
+  constexpr bool f32 = sizeof(T) == 4;
+  if (!PlaneCfg<T, PC>::ok) return 0;
+  if (P == 144 || (!f32 && (P == 96 || P == 112))) return 0;
+  if (f32 ? (P == 96 || P == 112) : (P == 90 || P == 126)) return 512;  // one right-hand side
+  return INT64_MAX;
+}
+
 // Orders LDS accesses of a wave's lanes in the program (the hardware executes a
 // wave's LDS operations in order).
 __device__ __forceinline__ void wave_sync() {
@@ -434,7 +458,7 @@ void launch_plane(const cx<T> *in, cx<T> *out, const PlaneOut &om, int Nx, int N
                   int Hy, const cx<T> *ghat, const cx<T> *tw, const int32_t *yrange,
                   hipStream_t s) {
   using C = PlaneCfg<T, PC>;
-  if constexpr (C::ok) {
+  if constexpr (plane_limit<T, PC>() > 0) {
     if (Nx < 1 || Ny < 1 || 2 * Nx > PC::P + 1 || 2 * Ny > PC::P + 1 ||
         (PC::P % 2 == 0 && (2 * Nx > PC::P || 2 * Ny > PC::P)) || Hy != PC::P / 2 + 1)
       throw Error(AIM_ERR_ARG, "plane pass: more than P/2 sources on a line");

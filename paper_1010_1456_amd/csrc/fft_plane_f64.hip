@@ -39,15 +39,15 @@ void fft_zplane_pass(const double2 *in, double2 *out, const FftPlan &pl, int n_i
   fftk::bad_length(pl.P);
 }
 
-bool fft_plane_available(const double2 *, const FftPlan &pl) {
+int64_t fft_plane_limit(const double2 *, const FftPlan &pl) {
   switch (pl.P) {
 #define AIM_X(P, a, b, c) \
   case P:                 \
-    return fftk::PlaneCfg<double, fftk::PlanC<a, b, c>>::ok;
+    return fftk::plane_limit<double, fftk::PlanC<a, b, c>>();
     AIM_FOR_EACH_FFT_PLAN(AIM_X)
 #undef AIM_X
     default:
-      return false;
+      return 0;
   }
 }
 bool fft_zplane_available(const double2 *, const FftPlan &pl) {

@@ -1,7 +1,12 @@
 // FFT lengths with a compiled kernel set, and the radix of each Stockham
 // stage (non-increasing; 1 = no stage). Shared by the host planner, which
 // pads every grid dimension to the smallest listed length >= 2 N_d - 1, and
-// by the device passes, which are instantiated once per entry.
+// by the device passes, which are instantiated once per entry. A length is listed
+// where it is faster than the next longer one (product on a 2-lambda sphere padded to
+// it, one right-hand side, c64): 90 40 us against 46 at 96, 112 52 against 53 at 126
+// (c128, three: 155 against 195), 120 48 against 53 at 126, 224 119 against 182 at 252,
+// 252 182 against 222 at 288. 243 = 9 x 9 x 3 took 297 and is left out; 140 and 180 are
+// no faster than 144 and 192.
 #pragma once
 
 #define AIM_FOR_EACH_FFT_PLAN(X) \
@@ -25,14 +30,18 @@
   X(63, 9, 7, 1)                 \
   X(72, 9, 8, 1)                 \
   X(81, 9, 9, 1)                 \
+  X(90, 10, 9, 1)                \
   X(96, 12, 8, 1)                \
   X(108, 12, 9, 1)               \
+  X(112, 14, 8, 1)               \
+  X(120, 12, 10, 1)              \
   X(126, 14, 9, 1)               \
   X(144, 12, 12, 1)              \
   X(162, 18, 9, 1)               \
   X(192, 16, 12, 1)              \
   X(216, 18, 12, 1)              \
-  X(243, 9, 9, 3)                \
+  X(224, 16, 14, 1)              \
+  X(252, 18, 14, 1)              \
   X(288, 18, 16, 1)              \
   X(324, 18, 18, 1)              \
   X(384, 16, 8, 3)               \

@@ -435,35 +435,26 @@ static cx<T> *zeroed_buffer(Plan *pl, void *(&buf)[2], size_t (&have)[2], size_t
   }
   return (cx<T> *)buf[prec];
 }
-// a zeroed buffer in `layout`, cleared first if it was last written in another
-// one (whose zero nodes are others); a captured graph of the old layout is dropped
+// the mesh's projected source grid in `layout` (1: 3-D grid [F][V0], 2: the
+// scatterer's plane [F][Nx Ny]), zero where no projection entry lands. The
+// projection writes the occupied nodes only, so a buffer last written in the
+// other layout (the full 3-D inspection of a planar scatterer, or the plane
+// after it) is cleared first, and a captured graph of the other layout dropped.
 template <typename T>
-static cx<T> *layout_buffer(Plan *pl, void *(&buf)[2], size_t (&have)[2], int (&in)[2],
-                            size_t bytes, int layout, hipStream_t s) {
+static cx<T> *src_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStream_t s) {
   const int prec = sizeof(T) == 8 ? 0 : 1;
-  const size_t had = have[prec];
-  cx<T> *p = zeroed_buffer<T>(pl, buf, have, bytes, s);
-  if (in[prec] != layout) {
+  const size_t had = md.src_bytes[prec];
+  cx<T> *p = zeroed_buffer<T>(pl, md.src, md.src_bytes, bytes, s);
+  if (md.src_layout[prec] != layout) {
     ++pl->work_gen;
-    if (have[prec] == had) {  // not just zeroed
+    if (md.src_bytes[prec] == had) {  // not just zeroed
       const int64_t n = (int64_t)(had / sizeof(cx<T>));
       hipLaunchKernelGGL((k_zero<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
       LAUNCHCHECK();
     }
   }
-  in[prec] = layout;
+  md.src_layout[prec] = layout;
   return p;
-}
-// the mesh's projected source grid (layouts as MeshDev::src_layout), zero where no
-// projection entry lands: the projection writes the occupied nodes only
-template <typename T>
-static cx<T> *src_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStream_t s) {
-  return layout_buffer<T>(pl, md.src, md.src_bytes, md.src_layout, bytes, layout, s);
-}
-// its forward z transforms, zero on the z lines without a source
-template <typename T>
-static cx<T> *fz_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStream_t s) {
-  return layout_buffer<T>(pl, md.fz, md.fz_bytes, md.fz_layout, bytes, layout, s);
 }
 
 void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStream_t s) {
@@ -551,13 +542,13 @@ static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int6
 // 19.1 us at 108); a caller that asks for tile rows or field groups gets the passes
 // these belong to
 void choose_plane_fft(const Plan *pl, MeshDev &md) {
-  auto can = [&](auto *v) {
-    return (pl->params.tuning & 0xffff) == 0 && md.plan[0].P == md.plan[1].P &&
-           fft_plane_available(v, md.plan[0]) &&
-           (md.planar_z >= 0 ? md.plan[0].P <= 81 : fft_zplane_available(v, md.plan[2]));
+  auto limit = [&](auto *v) -> int64_t {
+    if ((pl->params.tuning & 0xffff) != 0 || md.plan[0].P != md.plan[1].P) return 0;
+    if (md.planar_z >= 0 ? md.plan[0].P > 81 : !fft_zplane_available(v, md.plan[2])) return 0;
+    return fft_plane_limit(v, md.plan[0]);
   };
-  md.plane_fft[0] = can((const double2 *)nullptr);
-  md.plane_fft[1] = pl->mixed && can((const float2 *)nullptr);
+  md.plane_fft[0] = limit((const double2 *)nullptr);
+  md.plane_fft[1] = pl->mixed ? limit((const float2 *)nullptr) : 0;
 }
 
 template <typename T, typename TX>
@@ -597,7 +588,8 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   // the passes along y and x plane by plane, when the product runs through (the
   // stage boundaries between them then fall together: the forward y step carries
   // the time of all three)
-  const bool planes = md.plane_fft[prec] && stop >= 6 && first <= 1 && !full3d;
+  const bool planes = F * (md.planar_z >= 0 ? 1 : Pz) <= md.plane_fft[prec] && stop >= 6 &&
+                      first <= 1 && !full3d;
   if (md.planar_z >= 0 && !full3d) {
     // every source on the plane z = planar_z, and only that plane weighted by
     // the interpolation: the plane alone, g0 = [F][Nx][Ny], 2-D propagation
@@ -647,7 +639,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * V0, s);
     cx<T> *g1 = (cx<T> *)work_buffer(pl, md.lane, prec, 1, bytes, s);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
-    cx<T> *gz = fz_buffer<T>(pl, md, bytes, 2, s);
+    cx<T> *gz = zeroed_buffer<T>(pl, md.fzp, md.fzp_bytes, bytes, s);
     mark(0);
     project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
     mark(1);
@@ -734,7 +726,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   // sides in turn, so several take the two-launch form (right-hand sides in
   // parallel).
   if (first > 2) {  // (set-up) the passes after the forward z pass alone
-    gz = fz_buffer<T>(pl, md, sizeof(cx<T>) * F * V1, 1, s);
+    gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
   } else if (stop <= 1 || !md.fuse_proj[prec] || nrhs > 1 ||
       !anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, (int64_t)Nx * Ny, g1,
                    Pzs, (int64_t)Nx * Ny * Pzs, tw_of<T>(md, 2), md.plan[2], s)) {
@@ -748,7 +740,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
                       fftk::contig_map(Pzs), false, tw_of<T>(md, 2), s);
     } else {  // the occupied lines into the mesh's zeroed buffer (the others stay zero)
       const int64_t nl = md.n_occ_lines, A1 = (int64_t)Nx * Ny;
-      gz = fz_buffer<T>(pl, md, sizeof(cx<T>) * F * V1, 1, s);
+      gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
       fft_pass_contig(gs, gz, md.plan[2], Nz, Pz, F * nl,
                       fftk::select_lines(fftk::contig_map(Nz), md.occ_lines, nl, A1, md.occ_zrange),
                       fftk::select_lines(fftk::contig_map(Pzs), md.occ_lines, nl, A1), false,
@@ -1075,7 +1067,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       const bool thin = prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]);
-      if (thin || md.plane_fft[prec] || !fft_anterp_fused(md.plan[2])) {
+      if (thin || md.plane_fft[prec] == INT64_MAX || !fft_anterp_fused(md.plan[2])) {
         md.fuse_proj[prec] = 0;
         continue;
       }
@@ -1110,7 +1102,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
           (prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]));
       md.xy_groups[prec] = 1;
       md.x_row[prec] = md.y_row[prec] = rows == 2 ? 64 : 128;
-      if (rows == 0 && !md.plane_fft[prec]) {
+      if (rows == 0 && md.plane_fft[prec] < INT64_MAX) {
         const float x128 = time_stages(prec, 4, 4);
         md.x_row[prec] = 64;
         if (time_stages(prec, 4, 4) >= margin * x128) md.x_row[prec] = 128;
