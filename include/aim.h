@@ -287,7 +287,8 @@ aim_status aim_matvec(aim_plan *plan, aim_precision prec, int32_t nrhs,
  * time of each step over all repetitions and meshes:
  *   0 projection (grid clear + anterpolation), 1 forward z pass,
  *   2 forward y pass, 3 x pass with the Green's spectrum multiply,
- *   4 inverse y pass, 5 inverse z pass, 6 interpolation + near correction;
+ *   4 inverse y pass, 5 inverse z pass, 6 interpolation + near correction
+ *   (where one kernel runs 2 to 4, plane by plane, 2 carries the time of the three);
  * total_ms (host, may be NULL) the event time from the first to the last
  * kernel. */
 #define AIM_NSTAGE 7
@@ -413,7 +414,9 @@ aim_status aim_debug_far_stage(aim_plan *plan, aim_precision prec, int32_t mesh,
  * occupied z range (3-D path), every element (plane path). A z line (x, y)
  * is occupied when it holds a node with a non-zero projection (or curl)
  * weight, and its occupied range runs from its first to its last such node.
- * Stages 1-3 stop after that stage; stages 4-6 run the whole far part. */
+ * Stages 1-3 stop after that stage; stages 4-6 run the whole far part. Where the
+ * product runs the passes along y and x plane by plane in one kernel, stages 1-4
+ * come from the separate passes, which give the same values up to rounding. */
 aim_status aim_debug_product_stage(aim_plan *plan, aim_precision prec, int32_t mesh,
                                    int32_t nrhs, const void *x, int32_t stage, void *grid_out,
                                    void *hip_stream);

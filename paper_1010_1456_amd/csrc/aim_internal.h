@@ -195,7 +195,7 @@ struct MeshDev {
   // FP32]: chosen by timing at set-up among 8, 16, 32
   int gather_npw[2] = {16, 16};
   // field groups of the pipelined y / x / y passes per precision (1: the
-  // three passes one after the other), chosen by timing at set-up
+  // three passes one after the other), where the caller asks for groups
   int xy_groups[2] = {1, 1};
   // bytes of consecutive lines per work-group tile (128 or 64) of the x pass
   // and of the strided y passes, per precision; chosen by timing at set-up
