@@ -741,7 +741,8 @@ SolverState &solver_state(Plan *pl, int R, int m) {
   wk.dev.sn = (double2 *)alloc(sizeof(double2) * (size_t)S * m);
   wk.dev.g = (double2 *)alloc(sizeof(double2) * (size_t)S * (m + 1));
   wk.dev.active = (int *)alloc(sizeof(int) * S);
-  HIPCHECK(hipHostMalloc((void **)&st.poll, sizeof(int) * S, hipHostMallocMapped));
+  HIPCHECK(hipHostMalloc((void **)&st.poll, sizeof(int) * S,
+                         hipHostMallocMapped | hipHostMallocCoherent));
   HIPCHECK(hipHostGetDevicePointer((void **)&wk.dev.poll, st.poll, 0));
   wk.dev.its = (int *)alloc(sizeof(int) * S);
   wk.dev.jend = (int *)alloc(sizeof(int) * S);
