@@ -50,42 +50,58 @@ struct PlaneCfg {
   static constexpr long bytes = (long)elems * (long)sizeof(cx<T>);
   static constexpr bool ok = PC::ns == 2 && P <= 162 && bytes <= 160 * 1024;
   static constexpr int groups_cu = (int)(160 * 1024 / (bytes > 0 ? bytes : 1));
-  // waves: the column tiles in the fewest equal rounds that keep a CU at no more
-  // than about 20 (c64) or 10 (c128) waves; FEW planes (each has a CU to itself and
-  // the time is one plane's chain): in the fewest rounds that the registers allow
-  static constexpr int col_tiles = (P + CB - 1) / CB;
+  // waves. Many planes: of 4, 8, 12 and 16, so that a work-group loads the 4 SIMDs of a
+  // CU alike (2-lambda sphere with 16 right-hand sides, c64, product: 90 points 5 waves
+  // 268 us, 8 waves 222; 81 points 6 waves 205 us, 4 waves 185), the count that keeps
+  // most waves busy, i.e. the waves resident (LDS, and registers for 16 to 20 in c64, 8
+  // to 10 in c128) times the share of the rounds over row and column tiles in which a
+  // wave has a tile. FEW planes: each has a CU to itself and the time is one plane's
+  // chain, so the fewest rounds that the registers allow.
+  static constexpr int col_tiles = (P + CB - 1) / CB, row_tiles = (N + CB - 1) / CB;
   static constexpr int waves() {
-    const int most = sizeof(T) == 4 ? 20 : 10, widest = sizeof(T) == 4 ? 16 : 8;
-    for (int m = 1; m <= col_tiles; ++m) {
-      const int w = (col_tiles + m - 1) / m;
-      if (FEW ? w <= widest : (w <= 16 && (w * groups_cu <= most || w <= 4))) return w;
+    const int widest = sizeof(T) == 4 ? 16 : 8;
+    const int most = sizeof(T) == 4 ? (P < 96 ? 20 : 16) : (P < 81 ? 10 : 8);
+    if (!FEW && col_tiles < 4) return col_tiles;
+    int best = 1, score = 0;
+    for (int w = FEW ? 1 : 4; w <= widest && (w <= col_tiles || !FEW); w += FEW ? 1 : 4) {
+      const int rounds = 2 * ((row_tiles + w - 1) / w) + (col_tiles + w - 1) / w;
+      const int fit = most / w > 0 ? most / w : 1, groups = groups_cu < fit ? groups_cu : fit;
+      // resident waves times busy share, in thousandths
+      const int sc = FEW ? 1000 - rounds
+                         : groups * 1000 * (2 * row_tiles + col_tiles) / rounds;
+      if (sc > score) {
+        best = w;
+        score = sc;
+      }
     }
-    return 1;
+    return best;
   }
   static constexpr int NW = waves();
 };
 
 // planes (fields times kz) up to which the kernel is faster than the separate passes,
 // 0: never. Not all lengths divide well among the lanes of a wave: with P = R0 RM a
-// line takes R0 lanes, of which the outer stages use RM (96 = 12 x 8, 112 = 14 x 8, 126
-// = 14 x 9), and long lines leave one work-group per CU. Product on a 2-lambda sphere,
-// separate -> plane by plane, us, with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46
-// -> 37, 74 -> 59, 141 -> 114, 275 -> 185; 90 47 -> 40, 78 -> 74, 156 -> 151, 297 ->
-// 268; 96 47 -> 46, 78 -> 84, 157 -> 182, 312 -> 331; 108 53 -> 45, 91 -> 88, 197 ->
-// 177, 389 -> 333; 112 54 -> 52, with 8 206 -> 248; 120 56 -> 48, 100 -> 96, 243 -> 209,
-// 440 -> 391; 126 59 -> 53, 110 -> 107, 257 -> 236, 489 -> 456; 144 62 -> 68, with 8 308
-// -> 320; 162 84 -> 78, 180 -> 174, 492 -> 416, 935 -> 815. c128: 81 63 -> 53, 115 ->
-// 89, 263 -> 181, 485 -> 346; 90 66 -> 65, 124 -> 131, 304 -> 287, 550 -> 550; 96 66 ->
-// 70; 108 74 -> 70, 154 -> 159, 396 -> 355, 705 -> 692; 112 75 -> 120; 120 83 -> 72, 179
-// -> 167, 432 -> 410, 836 -> 777; 126 89 -> 84, 195 -> 202, 471 -> 505, 916 -> 983.
-// Lengths up to 72 are faster by 5 to 35% throughout.
+// line takes R0 lanes, of which the outer stages use RM (112 = 14 x 8, 126 = 14 x 9),
+// and long lines leave one work-group per CU. Product on a 2-lambda sphere, separate ->
+// plane by plane, us, with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46 -> 37, 74 ->
+// 59, 137 -> 114, 272 -> 185; 90 47 -> 40, 77 -> 67, 149 -> 129, 300 -> 222; 96 47 -> 46,
+// 79 -> 78, 154 -> 152, 308 -> 262; 108 53 -> 45, 91 -> 88, 197 -> 177, 389 -> 333; 112
+// 53 -> 50, 94 -> 101, 208 -> 214, 407 -> 397; 120 56 -> 48, 100 -> 96, 243 -> 209, 440 ->
+// 391; 126 59 -> 52, 112 -> 107, 262 -> 239, 498 -> 454; 144 64 -> 67, 123 -> 134, 312 ->
+// 320, 576 -> 623; 162 84 -> 78, 180 -> 174, 492 -> 416, 935 -> 815. c128: 81 63 -> 53,
+// 115 -> 90, 262 -> 185, 487 -> 346; 90 67 -> 57, 125 -> 108, 305 -> 222, 572 -> 412; 96
+// 66 -> 61, 124 -> 120, 311 -> 263, 548 -> 489; 108 74 -> 70, 154 -> 159, 396 -> 355, 705
+// -> 692; 112 75 -> 76, 160 -> 178, 402 -> 420, 724 -> 798; 120 83 -> 72, 179 -> 167, 432
+// -> 410, 836 -> 777; 126 90 -> 84, 196 -> 204, 487 -> 505, 925 -> 984. Lengths up to 72
+// are faster by 5 to 35% throughout, but for 48 in c128 with 16 (71 -> 73).
 template <typename T, class PC>
 constexpr int64_t plane_limit() {
   constexpr int P = PC::P;
   constexpr bool f32 = sizeof(T) == 4;
   if (!PlaneCfg<T, PC>::ok) return 0;
-  if (P == 144 || (!f32 && (P == 96 || P == 112))) return 0;
-  if (f32 ? (P == 96 || P == 112) : (P == 90 || P == 126)) return 512;  // one right-hand side
+  if (P == 144 || (!f32 && P == 112)) return 0;
+  if (P == (f32 ? 112 : 126)) return 512;  // one right-hand side
+  if (!f32 && P == 48) return 2048;        // up to ten
   return INT64_MAX;
 }
 
