@@ -63,3 +63,44 @@ def test_occupied_nodes_and_projection(name):
     assert err <= 1e-13 * np.abs(ref).max()
     plan.close()
     again.close()
+
+
+@pytest.mark.parametrize("name", ["few_nodes", "fine_plate"])
+def test_many_entries_per_node(name):
+    """Meshes much finer than the grid: a sphere of 14 520 unknowns on a few nodes,
+    every node with up to all of them, and a lambda/50 plate with some hundreds.
+    The projection against the exported weights, to n roundings of its largest
+    value; the same from one set-up to the next; and a set-up whose time is linear
+    in the entries (ordered entry by entry, the sphere's lists alone take n^2 / 4
+    dependent steps, some tens of seconds)."""
+    from paper_1010_1456_amd import aim as A
+
+    m = (sphere_mesh(0.03, FREQ, nf=22, jitter_seed=5) if name == "few_nodes"
+         else plate_mesh(1.5, FREQ, squares_per_lambda=50, jitter_seed=6))
+    mesh = [(m.verts, m.tris, FREQ)]
+    plan = A.Plan(mesh, near_radius_lambda=0.0, mixed=False)
+    info = plan.info()
+    assert info["setup_ms"][0]["projection"] < 1000.0
+    n, grid = plan.n_total, np.array(info["grid"][0])
+    lam = plan.export(0, A.AIM_DATA_LAMBDA64)
+    anchor = A.host_plan(m.verts, m.tris, FREQ, near_radius_lambda=0.0)["anchors"]
+    u = np.stack(np.meshgrid(*[np.arange(3)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    node = anchor[:, None] + u
+    lin = (node[..., 0] * grid[1] + node[..., 1]) * grid[2] + node[..., 2]
+    assert np.bincount(lin[(lam != 0).any(1)]).max() > (n // 2 if name == "few_nodes" else 64)
+    x = random_current(n, nrhs=1, seed=8)
+    ref = np.zeros((4, grid.prod()), dtype=np.complex128)
+    for q in range(4):
+        np.add.at(ref[q], lin, lam[:, q] * x[0][:, None])
+    ref = ref.reshape(4, *grid)
+    if info["planar_z"][0] >= 0:
+        ref = ref[..., info["planar_z"][0]]
+    xt = torch.from_numpy(x).cuda()
+    got = plan.product_stage(0, xt, 1)
+    err = np.abs(got.cpu().numpy().reshape(ref.shape) - ref).max()
+    assert err <= n * 2.0 ** -53 * np.abs(ref).max()
+    again = A.Plan(mesh, near_radius_lambda=0.0, mixed=False)
+    if info["gather_npw"] == again.info()["gather_npw"]:
+        assert torch.equal(got, again.product_stage(0, xt, 1))
+    plan.close()
+    again.close()
