@@ -239,6 +239,14 @@ void *dev_alloc(Plan *pl, size_t bytes);
 void dev_free(Plan *pl, void *p);
 // grid size of a launch of count threads, t per work-group
 inline unsigned launch_blocks(int64_t count, int t) { return (unsigned)((count + t - 1) / t); }
+// A launch holds fewer than 2^32 threads: f(first, number) for runs of consecutive
+// work-groups, of up to 256 threads each, that add up to `groups`
+constexpr int64_t kLaunchGroups = int64_t(1) << 23;
+template <class F>
+void for_launches(int64_t groups, F f) {
+  for (int64_t g0 = 0; g0 < groups; g0 += kLaunchGroups)
+    f(g0, (unsigned)(groups - g0 < kLaunchGroups ? groups - g0 : kLaunchGroups));
+}
 
 struct Plan {
   int device = 0;  // HIP device the plan was set up on

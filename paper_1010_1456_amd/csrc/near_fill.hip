@@ -163,7 +163,7 @@ __device__ __forceinline__ void pair_point(const PairScale &sc, int p, const D3 
   }
 }
 
-// Z^MOM of row m = blockIdx.x into nearv, its diagonal entry also into zdiag.
+// Z^MOM of row m = row0 + blockIdx.x into nearv, its diagonal entry also into zdiag.
 // The triangles of a batch of entries are collected in a hash table in LDS; each
 // (triangle, side of m) pair is then integrated by 8 lanes, one outer point each
 // (the eighth idles), touching pairs first so that their long path shares few
@@ -184,14 +184,14 @@ __global__ void __launch_bounds__(kMomThreads)
     k_near_mom(const int32_t *__restrict__ rwg, const double *__restrict__ len,
                const double *__restrict__ area, const int32_t *__restrict__ tris,
                const double *__restrict__ verts, const int32_t *__restrict__ rowptr,
-               const int32_t *__restrict__ cols, PairScale sc, double2 *__restrict__ nearv,
-               double2 *__restrict__ zdiag) {
+               const int32_t *__restrict__ cols, PairScale sc, int64_t row0,
+               double2 *__restrict__ nearv, double2 *__restrict__ zdiag) {
   __shared__ int key[kMomSlots];
   __shared__ unsigned short dense[kMomSlots], ref[2 * kMomBatch], task[2 * kMomTris];
   __shared__ int ids[kMomTris];
   __shared__ double2 val[2 * kMomTris * 3];
   __shared__ int count, ntouch, nplain;
-  const int64_t m = blockIdx.x;
+  const int64_t m = row0 + blockIdx.x;
   const int tid = threadIdx.x;
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
   int tm[2], vm[2][3];
@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(kMomThreads)
   }
 }
 
-// Z^grid of row m = blockIdx.x subtracted from nearv. The grid nodes on the
+// Z^grid of row m = row0 + blockIdx.x subtracted from nearv. The grid nodes on the
 // stencils of the row's entries are marked in the box of nodes around m's
 // stencil (reach R per axis), numbered, and the four fields of basis m there,
 //   Phi_q(w) = sum_u c_q[u] g(|w - u|),  q = x, y, z, div,
@@ -313,7 +313,7 @@ struct GridNear {
 template <bool CF>
 __global__ void __launch_bounds__(kGridThreads)
     k_near_grid(GridNear gn, const int32_t *__restrict__ rowptr, const int32_t *__restrict__ cols,
-                double2 *__restrict__ nearv) {
+                int64_t row0, double2 *__restrict__ nearv) {
   extern __shared__ __align__(16) unsigned char grid_lds[];
   double2 *phi = reinterpret_cast<double2 *>(grid_lds);  // [kGridNodes][4]
   double2 *gt = phi + 4 * kGridNodes;                    // the table
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kGridThreads)
   unsigned short *node = reinterpret_cast<unsigned short *>(gt + ng);  // [kGridNodes] cells
   unsigned short *map = node + kGridNodes;                             // [ncell] number + 1
   __shared__ int wsum[kGridThreads / 64], total;
-  const int64_t m = blockIdx.x;
+  const int64_t m = row0 + blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
   const int K = gn.m1.x * gn.m1.y * gn.m1.z;
@@ -439,8 +439,9 @@ __global__ void __launch_bounds__(kGridThreads)
 template <bool CF>
 __global__ void __launch_bounds__(128)
     k_near_grid_direct(GridNear gn, const int32_t *__restrict__ rowptr,
-                       const int32_t *__restrict__ cols, double2 *__restrict__ nearv) {
-  const int64_t m = blockIdx.x;
+                       const int32_t *__restrict__ cols, int64_t row0,
+                       double2 *__restrict__ nearv) {
+  const int64_t m = row0 + blockIdx.x;
   const int K = gn.m1.x * gn.m1.y * gn.m1.z;
   const double *lm = gn.lam + m * 4 * K, *wm = CF ? gn.curl + m * 3 * K : nullptr;
   const int32_t *am = gn.anchor3 + 3 * m;
@@ -484,14 +485,16 @@ void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *an
   const bool cf = h.cfie;
   const PairScale sc{h.k, h.alpha * h.k * kEta0, (1.0 - h.alpha) * kEta0};
   auto mom = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kMomThreads), 0, s, md.rwg, md.len, area,
-                       md.tris, md.verts, md.rowptr, md.cols, sc, md.near64, md.zdiag);
+    for_launches(n, [&](int64_t row0, unsigned rows) {
+      hipLaunchKernelGGL(kern, dim3(rows), dim3(kMomThreads), 0, s, md.rwg, md.len, area, md.tris,
+                         md.verts, md.rowptr, md.cols, sc, row0, md.near64, md.zdiag);
+      LAUNCHCHECK();
+    });
   };
   if (cf)
     mom(k_near_mom<true>);
   else
     mom(k_near_mom<false>);
-  LAUNCHCHECK();
 
   const bool plane = md.planar_z >= 0;
   GridNear gn{};
@@ -529,8 +532,11 @@ void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *an
                      sizeof(unsigned short) * (kGridNodes + (size_t)ncell);
   if (ncell <= kGridCells && lds <= 96 * 1024) {
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kGridThreads), lds, s, gn, md.rowptr,
-                         md.cols, md.near64);
+      for_launches(n, [&](int64_t row0, unsigned rows) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(kGridThreads), lds, s, gn, md.rowptr, md.cols,
+                           row0, md.near64);
+        LAUNCHCHECK();
+      });
     };
     if (cf)
       go(k_near_grid<true>);
@@ -538,15 +544,17 @@ void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *an
       go(k_near_grid<false>);
   } else {
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(128), 0, s, gn, md.rowptr, md.cols,
-                         md.near64);
+      for_launches(n, [&](int64_t row0, unsigned rows) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(128), 0, s, gn, md.rowptr, md.cols, row0,
+                           md.near64);
+        LAUNCHCHECK();
+      });
     };
     if (cf)
       go(k_near_grid_direct<true>);
     else
       go(k_near_grid_direct<false>);
   }
-  LAUNCHCHECK();
   if (pl->mixed) {
     md.near32 = (float2 *)dev_alloc(pl, sizeof(float2) * std::max<int64_t>(h.nnz, 1));
     if (h.nnz > 0) {

@@ -57,12 +57,12 @@ __global__ void k_cell_fill(const int32_t *cell_of, int64_t n, int32_t *cursor, 
 // rowptr[m] in the order found
 template <bool WRITE>
 __global__ void __launch_bounds__(256)
-    k_near_rows(const double *__restrict__ centre, int64_t n, Cells ce,
+    k_near_rows(const double *__restrict__ centre, int64_t n, int64_t group0, Cells ce,
                 const int32_t *__restrict__ cstart, const int32_t *__restrict__ members,
                 int32_t *count, const int32_t *rowptr, int32_t *cols) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
-  const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t m = (group0 + blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (m >= n) return;
   const double cm[3] = {centre[3 * m], centre[3 * m + 1], centre[3 * m + 2]};
   const int c0 = ce.index(cm, 0), c1 = ce.index(cm, 1), c2 = ce.index(cm, 2);
@@ -94,9 +94,9 @@ __global__ void __launch_bounds__(256)
 // number of smaller ones, read 64 at a time
 __global__ void __launch_bounds__(256)
     k_sort_rows(const int32_t *__restrict__ in, const int32_t *__restrict__ rowptr, int64_t n,
-                int32_t *__restrict__ out) {
+                int64_t group0, int32_t *__restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t m = (group0 + blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (m >= n) return;
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
   for (int e = e0; e < e1; e += 64) {
@@ -153,9 +153,12 @@ void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
   hipLaunchKernelGGL(k_cell_fill, dim3(launch_blocks(n, 256)), dim3(256), 0, s, cell_of, n, count,
                      members);
   LAUNCHCHECK();
-  hipLaunchKernelGGL(k_near_rows<false>, dim3(launch_blocks(n, 4)), dim3(256), 0, s, centre, n, ce,
-                     cstart, members, count, nullptr, nullptr);
-  LAUNCHCHECK();
+  const int64_t row_groups = (n + 3) / 4;
+  for_launches(row_groups, [&](int64_t g0, unsigned groups) {
+    hipLaunchKernelGGL(k_near_rows<false>, dim3(groups), dim3(256), 0, s, centre, n, g0, ce, cstart,
+                       members, count, nullptr, nullptr);
+    LAUNCHCHECK();
+  });
   const uint64_t nnz = scan_sums<false>(count, n, sums, s);
   if (nnz > (uint64_t)INT32_MAX)
     throw Error(AIM_ERR_ARG, "near zone too large for 32-bit indexing");
@@ -166,12 +169,15 @@ void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
   LAUNCHCHECK();
   int32_t *found = ints(h.nnz);
   md.cols = (int32_t *)dev_alloc(pl, sizeof(int32_t) * std::max<int64_t>(h.nnz, 1));
-  hipLaunchKernelGGL(k_near_rows<true>, dim3(launch_blocks(n, 4)), dim3(256), 0, s, centre, n, ce,
-                     cstart, members, nullptr, md.rowptr, found);
-  LAUNCHCHECK();
-  hipLaunchKernelGGL(k_sort_rows, dim3(launch_blocks(n, 4)), dim3(256), 0, s, found, md.rowptr, n,
-                     md.cols);
-  LAUNCHCHECK();
+  for_launches(row_groups, [&](int64_t g0, unsigned groups) {
+    hipLaunchKernelGGL(k_near_rows<true>, dim3(groups), dim3(256), 0, s, centre, n, g0, ce, cstart,
+                       members, nullptr, md.rowptr, found);
+    LAUNCHCHECK();
+  });
+  for_launches(row_groups, [&](int64_t g0, unsigned groups) {
+    hipLaunchKernelGGL(k_sort_rows, dim3(groups), dim3(256), 0, s, found, md.rowptr, n, g0, md.cols);
+    LAUNCHCHECK();
+  });
   HIPCHECK(hipStreamSynchronize(s));
   for (void *p : tmp) dev_free(pl, p);
 }
