@@ -239,7 +239,8 @@ void *dev_alloc(Plan *pl, size_t bytes);
 void dev_free(Plan *pl, void *p);
 // grid size of a launch of count threads, t per work-group
 inline unsigned launch_blocks(int64_t count, int t) { return (unsigned)((count + t - 1) / t); }
-// A launch holds fewer than 2^32 threads: f(first, number) for runs of consecutive
+// A launch holds fewer than 2^32 threads (one of more is cut short without an error,
+// leaving rows untouched): f(first, number) for runs of consecutive
 // work-groups, of up to 256 threads each, that add up to `groups`
 constexpr int64_t kLaunchGroups = int64_t(1) << 23;
 template <class F>
