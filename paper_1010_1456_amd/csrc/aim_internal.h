@@ -378,7 +378,8 @@ struct StageView {
 // each stage: ev[0] .. ev[AIM_NSTAGE]. `full3d` (inspection): the 3-D passes
 // also for a scatterer in one grid plane. `views` (optional, AIM_NSTAGE
 // entries, index = stage): where the product's own passes left each stage's
-// output. `first` (set-up timings): stages before it are not launched.
+// output. `first` (set-up timings): stages before it are not launched; 7: none is,
+// and the product's buffers are allocated.
 template <typename T, typename TX>
 void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, int stop_stage,
                 hipStream_t s, hipEvent_t *ev = nullptr, bool full3d = false,

@@ -585,20 +585,29 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   const int npw = md.gather_npw[prec];
   if (npw < 1 || npw > 64 || 64 % npw != 0)
     throw Error(AIM_ERR_ARG, "projection gather: nodes per wave must divide 64");
+  // set-up: the buffers of such a product, without any stage
+  const bool reserve = first > 6;
   // the passes along y and x plane by plane, when the product runs through (the
   // stage boundaries between them then fall together: the forward y step carries
   // the time of all three)
   const bool planes = F * (md.planar_z >= 0 ? 1 : Pz) <= md.plane_fft[prec] && stop >= 6 &&
-                      first <= 1 && !full3d;
+                      (first <= 1 || reserve) && !full3d;
+  // work buffer `which` of `count` elements per field, where a stage that is asked for
+  // touches it
+  auto buf = [&](int which, int64_t count, bool touched) {
+    return touched ? (cx<T> *)work_buffer(pl, md.lane, prec, which, sizeof(cx<T>) * F * count, s)
+                   : nullptr;
+  };
+  if (reserve && multi_lanes(nrhs) > 0) (void)transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);
   if (md.planar_z >= 0 && !full3d) {
     // every source on the plane z = planar_z, and only that plane weighted by
     // the interpolation: the plane alone, g0 = [F][Nx][Ny], 2-D propagation
     // (y passes, x pass with the 2-D spectrum)
     const int64_t A1 = (int64_t)Nx * Ny, V2 = (int64_t)Nx * Py;
-    cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * A1, s);
-    cx<T> *g2 = planes ? nullptr
-                       : (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
+    cx<T> *g0 = buf(0, A1, stop > 4);
+    cx<T> *g2 = buf(2, V2, stop > 1 && !planes);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * A1, 2, s);
+    if (reserve) return;
     mark(0);
     if (first <= 1)
       project<T, TX>(pl, md, nrhs, x, ldx, md.plane_occ_ptr, md.plane_occ, md.n_plane_occ, gs, A1, s);
@@ -635,11 +644,11 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   if (planes) {
     // kz-outer grids gz and g1 [F][Pz][Nx][Ny] between the z passes
     const int64_t A1 = (int64_t)Nx * Ny, nl = md.n_occ_lines;
-    const size_t bytes = sizeof(cx<T>) * F * Pz * A1;
-    cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * V0, s);
-    cx<T> *g1 = (cx<T> *)work_buffer(pl, md.lane, prec, 1, bytes, s);
+    cx<T> *g0 = buf(0, V0, true);
+    cx<T> *g1 = buf(1, Pz * A1, true);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
-    cx<T> *gz = zeroed_buffer<T>(pl, md.fzp, md.fzp_bytes, bytes, s);
+    cx<T> *gz = zeroed_buffer<T>(pl, md.fzp, md.fzp_bytes, sizeof(cx<T>) * F * Pz * A1, s);
+    if (reserve) return;
     mark(0);
     project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
     mark(1);
@@ -663,10 +672,9 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     // g2 [F][Pz][Nx][Py], no row padding; the y lines are contiguous, the x
     // pass tiles consecutive ky
     const int64_t A1 = (int64_t)Nx * Ny, V1 = Pz * A1, V2 = (int64_t)Pz * Nx * Py;
-    cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * V0, s);
-    cx<T> *g1 = (cx<T> *)work_buffer(pl, md.lane, prec, 1, sizeof(cx<T>) * F * V1, s);
-    cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
+    cx<T> *g0 = buf(0, V0, stop > 5), *g1 = buf(1, V1, stop > 1), *g2 = buf(2, V2, stop > 2);
     cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
+    if (reserve) return;
     mark(0);
     if (first <= 1)
       project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
@@ -713,41 +721,44 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   const int Pzs = (Pz + blk - 1) / blk * blk;  // z rows padded to 128-byte multiples
   const int64_t V1 = (int64_t)Nx * Ny * Pzs;
   const int64_t V2 = (int64_t)Nx * Py * ((Pz + blk - 1) / blk * blk);  // kz-blocked
-  cx<T> *g0 = (cx<T> *)work_buffer(pl, md.lane, prec, 0, sizeof(cx<T>) * F * V0, s);
-  cx<T> *g1 = (cx<T> *)work_buffer(pl, md.lane, prec, 1, sizeof(cx<T>) * F * V1, s);
-  cx<T> *g2 = (cx<T> *)work_buffer(pl, md.lane, prec, 2, sizeof(cx<T>) * F * V2, s);
+  const int64_t A1 = (int64_t)Nx * Ny;
+  cx<T> *g0 = buf(0, V0, stop > 5), *g1 = buf(1, V1, stop > 1), *g2 = buf(2, V2, stop > 2);
   const fftk::LineMap m1 = fftk::plain_map((int64_t)Ny * Pzs, Pzs);
   const fftk::LineMap m2 = fftk::blocked_map(V2, Nx, Py, blk);
-  cx<T> *gz = g1;  // forward z output, forward y input
-  mark(0);
   // projection fused with the forward z pass: the projected grid is never
   // stored (except for inspection, or for FFT lengths without a fused kernel).
-  // The variant is tuned on one right-hand side and walks the right-hand
-  // sides in turn, so several take the two-launch form (right-hand sides in
-  // parallel).
-  if (first > 2) {  // (set-up) the passes after the forward z pass alone
-    gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
-  } else if (stop <= 1 || !md.fuse_proj[prec] || nrhs > 1 ||
-      !anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, (int64_t)Nx * Ny, g1,
-                   Pzs, (int64_t)Nx * Ny * Pzs, tw_of<T>(md, 2), md.plan[2], s)) {
-    cx<T> *gs = src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
+  // The variant walks the right-hand sides in turn, so several take the two-launch
+  // form (right-hand sides in parallel).
+  const bool later = first > 2 && !reserve;  // (set-up) the passes after the forward z pass alone
+  const bool fused = stop > 1 && md.fuse_proj[prec] && nrhs == 1 && fft_anterp_fused(md.plan[2]);
+  cx<T> *gs = fused || later ? nullptr : src_buffer<T>(pl, md, sizeof(cx<T>) * F * V0, 1, s);
+  // forward z output, forward y input: every line (fused, inspection), or the mesh's
+  // zeroed buffer, of which the occupied lines are written
+  const bool all_lines = (fused && !later) || full3d || stop <= 1;
+  cx<T> *gz = all_lines ? g1 : zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
+  if (reserve) return;
+  mark(0);
+  if (later) {
+  } else if (fused) {
+    if (!anterp_fftz(x, ldx, nrhs, md.node_ptr, md.ent_col, lamT_of<T>(md), Nz, A1, g1, Pzs, V1,
+                     tw_of<T>(md, 2), md.plan[2], s))
+      throw Error(AIM_ERR_ARG, "no fused projection for this FFT length");
+    mark(1);
+  } else {
     project<T, TX>(pl, md, nrhs, x, ldx, md.occ_ptr, md.occ, md.n_occ, gs, V0, s);
     mark(1);
-    view(1, gs, (int64_t)Nx * Ny, Nz, V0, Nz, 1);
+    view(1, gs, A1, Nz, V0, Nz, 1);
     if (stop <= 1) return;
-    if (full3d) {  // inspection: every line, into g1
-      fft_pass_contig(gs, g1, md.plan[2], Nz, Pz, F * Nx * Ny, fftk::contig_map(Nz),
+    if (full3d) {
+      fft_pass_contig(gs, gz, md.plan[2], Nz, Pz, F * A1, fftk::contig_map(Nz),
                       fftk::contig_map(Pzs), false, tw_of<T>(md, 2), s);
-    } else {  // the occupied lines into the mesh's zeroed buffer (the others stay zero)
-      const int64_t nl = md.n_occ_lines, A1 = (int64_t)Nx * Ny;
-      gz = zeroed_buffer<T>(pl, md.fz, md.fz_bytes, sizeof(cx<T>) * F * V1, s);
+    } else {
+      const int64_t nl = md.n_occ_lines;
       fft_pass_contig(gs, gz, md.plan[2], Nz, Pz, F * nl,
                       fftk::select_lines(fftk::contig_map(Nz), md.occ_lines, nl, A1, md.occ_zrange),
                       fftk::select_lines(fftk::contig_map(Pzs), md.occ_lines, nl, A1), false,
                       tw_of<T>(md, 2), s);
     }
-  } else {
-    mark(1);
   }
   mark(2);
   view(2, gz, (int64_t)Nx * Ny, Pz, (int64_t)Nx * Ny * Pzs, Pzs, 1);
@@ -1115,6 +1126,21 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       }
       if (groups > 0 && !thin && xy_pipeline_available(md.plan[0], md.plan[1]))
         md.xy_groups[prec] = groups;
+    }
+    // every buffer of a product with up to nr right-hand sides, so that none is
+    // allocated by the first one (which may be captured into a graph): those of nr
+    // and, where nr are too many planes, of the most that still run plane by plane
+    for (int prec = 0; prec < 2; ++prec) {
+      if (prec == 1 && !pl->mixed) break;
+      auto reserve = [&](int r) {
+        if (prec == 0)
+          far_stages<double, double>(pl, md, r, nullptr, n, 6, s, nullptr, false, nullptr, 7);
+        else
+          far_stages<float, double>(pl, md, r, nullptr, n, 6, s, nullptr, false, nullptr, 7);
+      };
+      reserve(nr);
+      const int64_t most = md.plane_fft[prec] / (4 * (md.planar_z >= 0 ? 1 : md.hp.pad[2]));
+      if (most > 0 && most < nr) reserve((int)most);
     }
   } catch (...) {
     (void)hipEventDestroy(e0);
