@@ -491,7 +491,8 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
 // interpolation together, 4-lambda CFIE sphere: 8 right-hand sides 145 -> 119 us
 // in c64 and 276 -> 209 in FP64, 16: 248 -> 170 and 528 -> 306); with 3 or 4 their
 // short runs lose (4: 85 -> 99 and 164 -> 170), at 5 the two are equal.
-static int multi_lanes(int nrhs) { return nrhs < 6 ? 0 : (nrhs <= 8 ? 8 : 16); }
+constexpr int kMultiFrom = 6;
+static int multi_lanes(int nrhs) { return nrhs < kMultiFrom ? 0 : (nrhs <= 8 ? 8 : 16); }
 
 // x of one mesh transposed to [n][nrhs] in T
 template <typename T, typename TX>
@@ -1043,15 +1044,15 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
   try {
     x = dev_alloc(pl, sizeof(double2) * n * nr);
     HIPCHECK(hipMemsetAsync(x, 0, sizeof(double2) * n * nr, s));
-    // the stages first .. stop alone (zero grids stay zero)
-    auto time_stages = [&](int prec, int first, int stop) {
+    // the stages first .. stop alone (zero grids stay zero), with r right-hand sides
+    auto time_stages = [&](int prec, int first, int stop, int r) {
       for (int rep = 0; rep < 4; ++rep) {  // first repetition is a warm-up
         if (rep == 1) HIPCHECK(hipEventRecord(e0, s));
         if (prec == 0)
-          far_stages<double, double>(pl, md, nr, (const double2 *)x, n, stop, s, nullptr, false,
+          far_stages<double, double>(pl, md, r, (const double2 *)x, n, stop, s, nullptr, false,
                                      nullptr, first);
         else
-          far_stages<float, double>(pl, md, nr, (const double2 *)x, n, stop, s, nullptr, false,
+          far_stages<float, double>(pl, md, r, (const double2 *)x, n, stop, s, nullptr, false,
                                     nullptr, first);
       }
       HIPCHECK(hipEventRecord(e1, s));
@@ -1060,14 +1061,15 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       HIPCHECK(hipEventElapsedTime(&ms, e0, e1));
       return ms;
     };
-    // projection gather: occupied nodes per wave
+    // projection gather: occupied nodes per wave, with the most right-hand sides it
+    // takes if nr are more (k_anterp_multi has no such variants)
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       float best = 0;
       int choice = kGatherNpwCand[1];
       for (int c = 0; c < 3; ++c) {
         md.gather_npw[prec] = kGatherNpwCand[c];
-        const float ms = time_stages(prec, 1, 1);
+        const float ms = time_stages(prec, 1, 1, std::min(nr, kMultiFrom - 1));
         if (c == 0 || ms < best) {
           best = ms;
           choice = kGatherNpwCand[c];
@@ -1075,6 +1077,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       }
       md.gather_npw[prec] = choice;
     }
+    // projection fused with the forward z pass, which one right-hand side alone takes
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       const bool thin = prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]);
@@ -1086,7 +1089,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       int choice = 0;
       for (int v = 0; v < 2; ++v) {
         md.fuse_proj[prec] = v;
-        const float ms = time_stages(prec, 1, 2);
+        const float ms = time_stages(prec, 1, 2, 1);
         if (v == 0 || ms < best) {
           best = ms;
           choice = v;
@@ -1114,13 +1117,13 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       md.xy_groups[prec] = 1;
       md.x_row[prec] = md.y_row[prec] = rows == 2 ? 64 : 128;
       if (rows == 0 && md.plane_fft[prec] < INT64_MAX) {
-        const float x128 = time_stages(prec, 4, 4);
+        const float x128 = time_stages(prec, 4, 4, nr);
         md.x_row[prec] = 64;
-        if (time_stages(prec, 4, 4) >= margin * x128) md.x_row[prec] = 128;
+        if (time_stages(prec, 4, 4, nr) >= margin * x128) md.x_row[prec] = 128;
         if (!thin) {  // (the y lines of the thin layouts are contiguous)
-          const float y128 = time_stages(prec, 3, 3) + time_stages(prec, 5, 5);
+          const float y128 = time_stages(prec, 3, 3, nr) + time_stages(prec, 5, 5, nr);
           md.y_row[prec] = 64;
-          if (time_stages(prec, 3, 3) + time_stages(prec, 5, 5) >= margin * y128)
+          if (time_stages(prec, 3, 3, nr) + time_stages(prec, 5, 5, nr) >= margin * y128)
             md.y_row[prec] = 128;
         }
       }
