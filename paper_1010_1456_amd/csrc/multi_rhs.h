@@ -24,6 +24,16 @@ namespace {
 
 constexpr int kMultiThreads = 256;
 constexpr int kMultiRows = kMultiThreads / 32;  // nodes (rows) per work-group
+// Partial sums per lane of the near product (half as many for the stencil and the
+// projection), added in pairs at the end. In float 16 per row, of some 5 entries
+// each: with 8 the product's error against FP64 was 1.04e-7 on the 2-lambda sphere
+// (16 right-hand sides) where 32 lanes per row, one right-hand side at a time, have
+// 0.978e-7; with 16 it is 0.977e-7, and the interpolation takes 114 us on the
+// 4-lambda sphere (8: 117; 16 also for the stencil 150). In FP64 four per lane.
+template <typename T, int SEG>
+constexpr int near_sums() {
+  return sizeof(T) == 4 ? 16 / SEG : 4;
+}
 
 // xt[i R + r] = x[r ldx + i]
 template <typename T, typename TX>
@@ -71,7 +81,12 @@ __global__ void __launch_bounds__(kMultiThreads)
   const int b0 = occ_ptr[v0], b1 = occ_ptr[vend];
   const int rr = blockIdx.y * LR + r;
   const cx<T> *xr = xt + (rr < R ? rr : R - 1);
-  T a[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}}, b[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+  constexpr int NS = near_sums<T, SEG>() / 2;
+  T a[NS][4][2];
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[j][q][0] = a[j][q][1] = 0;
   for (int c0 = b0; c0 < b1; c0 += C) {
     const int cnt = min(C, b1 - c0);
     __syncthreads();
@@ -87,33 +102,40 @@ __global__ void __launch_bounds__(kMultiThreads)
       }
     };
     int k = max(e0 - c0, 0) + seg;
-#pragma unroll 2
-    for (; k + SEG < hi; k += 2 * SEG) {  // two sums: the float sums stay short
-      const cx<T> x0 = xr[(int64_t)cl[k] * R], x1 = xr[(int64_t)cl[k + SEG] * R];
-      add(a, k, x0);
-      add(b, k + SEG, x1);
+    for (; k + (NS - 1) * SEG < hi; k += NS * SEG) {
+      cx<T> xv[NS];
+#pragma unroll
+      for (int j = 0; j < NS; ++j) xv[j] = xr[(int64_t)cl[k + j * SEG] * R];
+#pragma unroll
+      for (int j = 0; j < NS; ++j) add(a[j], k + j * SEG, xv[j]);
     }
-    if (k < hi) add(a, k, xr[(int64_t)cl[k] * R]);
+#pragma unroll
+    for (int j = 0; j < NS - 1; ++j)
+      if (k + j * SEG < hi) add(a[j], k + j * SEG, xr[(int64_t)cl[k + j * SEG] * R]);
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    a[q][0] += b[q][0];
-    a[q][1] += b[q][1];
-  }
+  for (int h = NS / 2; h > 0; h /= 2)
+#pragma unroll
+    for (int j = 0; j < h; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        a[j][q][0] += a[j + h][q][0];
+        a[j][q][1] += a[j + h][q][1];
+      }
 #pragma unroll
   for (int off = LR; off < 32; off <<= 1)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      a[q][0] += __shfl_xor(a[q][0], off, 64);
-      a[q][1] += __shfl_xor(a[q][1], off, 64);
+      a[0][q][0] += __shfl_xor(a[0][q][0], off, 64);
+      a[0][q][1] += __shfl_xor(a[0][q][1], off, 64);
     }
   __syncthreads();
   cx<T> *out = reinterpret_cast<cx<T> *>(lds);
   if (seg == 0)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      out[(4 * r + q) * (NB + 1) + g].x = a[q][0];
-      out[(4 * r + q) * (NB + 1) + g].y = a[q][1];
+      out[(4 * r + q) * (NB + 1) + g].x = a[0][q][0];
+      out[(4 * r + q) * (NB + 1) + g].y = a[0][q][1];
     }
   __syncthreads();
   const int i = threadIdx.x % NB;  // node of the store
@@ -157,11 +179,12 @@ __global__ void __launch_bounds__(kMultiThreads)
   const int rr = blockIdx.y * LR + r, rc = rr < R ? rr : R - 1;
   const int e0 = rowptr[m], e1 = rowptr[m + 1], b0 = rowptr[m0], b1 = rowptr[mend];
   const V *ph = phi + ((int64_t)anchor_lin[m] * R + rc) * 4;
-  V far[2], fk[2], nr[4];
+  constexpr int NN = near_sums<T, SEG>(), NF = NN / 2;  // far and near sums per lane
+  V far[NF], fk[NF], nr[NN];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) far[j].x = far[j].y = fk[j].x = fk[j].y = 0;
+  for (int j = 0; j < NF; ++j) far[j].x = far[j].y = fk[j].x = fk[j].y = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) nr[j].x = nr[j].y = 0;
+  for (int j = 0; j < NN; ++j) nr[j].x = nr[j].y = 0;
   // stencil: weights [q][rows][UC] of UC nodes at a time
   T *wl = reinterpret_cast<T *>(lds);
   for (int u0 = 0; u0 < K; u0 += UC) {
@@ -194,15 +217,22 @@ __global__ void __launch_bounds__(kMultiThreads)
       }
     };
     int u = seg;
-#pragma unroll 2
-    for (; u + SEG < uc; u += 2 * SEG) {  // two sums, as below
-      add(far[0], fk[0], u);
-      add(far[1], fk[1], u + SEG);
-    }
-    if (u < uc) add(far[0], fk[0], u);
+    for (; u + (NF - 1) * SEG < uc; u += NF * SEG)
+#pragma unroll
+      for (int j = 0; j < NF; ++j) add(far[j], fk[j], u + j * SEG);
+#pragma unroll
+    for (int j = 0; j < NF - 1; ++j)
+      if (u + j * SEG < uc) add(far[j], fk[j], u + j * SEG);
   }
-  far[0].x += far[1].x, far[0].y += far[1].y;
-  fk[0].x += fk[1].x, fk[0].y += fk[1].y;
+  auto halve = [&](V *v, int h) {  // v[j] += v[j + h], j < h
+#pragma unroll
+    for (int j = 0; j < h; ++j) {
+      v[j].x += v[j + h].x;
+      v[j].y += v[j + h].y;
+    }
+  };
+#pragma unroll
+  for (int h = NF / 2; h > 0; h /= 2) halve(far, h), halve(fk, h);
   // near zone: entries of the work-group's rows, C at a time
   V *zl = reinterpret_cast<V *>(lds);
   int32_t *cl = reinterpret_cast<int32_t *>(zl + C);
@@ -215,30 +245,28 @@ __global__ void __launch_bounds__(kMultiThreads)
     }
     __syncthreads();
     const int hi = min(e1 - c0, cnt);
-    // four sums, so that no float sum runs over more than some ten entries (one
-    // sum per lane loses half a digit: error 1.4e-7 instead of 1.0e-7)
     int k = max(e0 - c0, 0) + seg;
-    for (; k + 3 * SEG < hi; k += 4 * SEG) {
-      V xv[4];
+    for (; k + (NN - 1) * SEG < hi; k += NN * SEG) {
+      V xv[NN];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xv[j] = xt[(int64_t)cl[k + j * SEG] * R + rc];
+      for (int j = 0; j < NN; ++j) xv[j] = xt[(int64_t)cl[k + j * SEG] * R + rc];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NN; ++j) {
         const V z = zl[k + j * SEG];
         nr[j].x += z.x * xv[j].x - z.y * xv[j].y;
         nr[j].y += z.x * xv[j].y + z.y * xv[j].x;
       }
     }
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < NN - 1; ++j)
       if (k + j * SEG < hi) {
         const V xv = xt[(int64_t)cl[k + j * SEG] * R + rc], z = zl[k + j * SEG];
         nr[j].x += z.x * xv.x - z.y * xv.y;
         nr[j].y += z.x * xv.y + z.y * xv.x;
       }
   }
-  nr[0].x += nr[1].x + (nr[2].x + nr[3].x);
-  nr[0].y += nr[1].y + (nr[2].y + nr[3].y);
+#pragma unroll
+  for (int h = NN / 2; h > 0; h /= 2) halve(nr, h);
   V acc;
   acc.x = -keta * far[0].y + nr[0].x - (CF ? eta_h * fk[0].x : (T)0);  // j k eta * far
   acc.y = keta * far[0].x + nr[0].y - (CF ? eta_h * fk[0].y : (T)0);
