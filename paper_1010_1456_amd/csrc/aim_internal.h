@@ -111,6 +111,13 @@ constexpr bool thin_layout(int Pz) {
   return Pz < kGridBlock<T>;
 }
 
+// numbers of planes, lo to hi (none: hi < lo)
+struct PlaneRange {
+  int64_t lo = 1, hi = 0;
+  constexpr bool any() const { return lo <= hi; }
+  constexpr bool has(int64_t planes) const { return lo <= planes && planes <= hi; }
+};
+
 // streams a multi-mesh product spreads its meshes over
 constexpr int kMaxLanes = 4;
 
@@ -185,10 +192,10 @@ struct MeshDev {
   int32_t *plane_anchor = nullptr;    // n
   int32_t *plane_soff = nullptr;      // (M+1)^2
   int plane_K = 0;                    // (M+1)^2
-  // per precision: up to this many planes (fields times kz), the passes along y and
-  // x run plane by plane in LDS (fft_plane.h), on kz-outer grids [F][Pz][Nx][Ny]; for
+  // per precision: for how many planes (fields times kz) the passes along y and x run
+  // plane by plane in LDS (fft_plane.h), on kz-outer grids [F][Pz][Nx][Ny]; for
   // a scatterer off one grid plane with the octant kz-outer too, [H2][H0][H1]
-  int64_t plane_fft[2] = {0, 0};
+  PlaneRange plane_fft[2];
   double2 *ghatp64 = nullptr;
   float2 *ghatp32 = nullptr;
   // occupied nodes per wave of the projection gather, per precision [FP64,
@@ -291,9 +298,11 @@ void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 // area, anchor3: device, per triangle and 3 per basis
 void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *anchor3,
                     hipStream_t s);
-// up to how many planes the passes along y and x of one mesh run plane by plane
+// for how many planes the passes along y and x of one mesh run plane by plane
 // (md.plane_fft), from its FFT plans and planar_z
 void choose_plane_fft(const Plan *pl, MeshDev &md);
+// whether those of a product with nrhs right-hand sides do
+bool plane_by_plane(const MeshDev &md, int prec, int64_t nrhs);
 // times the alternative kernel variants of one mesh and keeps the faster
 void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s);
 
@@ -333,8 +342,8 @@ AIM_DECLARE_XY(double2)
 #undef AIM_DECLARE_XY
 
 // the y, x and y passes of kz-outer planes in one launch, and the z passes between
-// kz-outer grids (fft_plane_*.hip; see fft_plane.h). plane_limit: the
-// planes up to which the length's kernel is the faster one (0: it has none); the first
+// kz-outer grids (fft_plane_*.hip; see fft_plane.h). plane_range: the
+// numbers of planes for which the length's kernel is the faster one; the first
 // argument only names the precision
 #define AIM_DECLARE_PLANE(V)                                                                      \
   void fft_plane_pass(const V *in, V *out, const fftk::PlaneOut &om, const FftPlan &pl, int Nx,   \
@@ -343,7 +352,7 @@ AIM_DECLARE_XY(double2)
   void fft_zplane_pass(const V *in, V *out, const FftPlan &pl, int n_in, int n_out, int F,        \
                        int64_t nl, const int32_t *sel, const int32_t *range, int64_t A1,          \
                        bool inverse, const V *tw, hipStream_t s);                                 \
-  int64_t fft_plane_limit(const V *, const FftPlan &pl);                                          \
+  PlaneRange fft_plane_range(const V *, const FftPlan &pl);                                       \
   bool fft_zplane_available(const V *, const FftPlan &pl);
 AIM_DECLARE_PLANE(float2)
 AIM_DECLARE_PLANE(double2)

@@ -105,12 +105,12 @@ static double model_bytes(const MeshDev &md, int sc, int sr) {
                            // in-plane stencils; the 2-D spectrum
     const double K2 = (double)md.plane_K;
     const double lam2 = 2.0 * n * (4.0 * K2 * sr + 4.0);
-    const double y2 = 4.0 <= md.plane_fft[sc == 16 ? 0 : 1] ? 0.0 : 4.0;  // plane kept in LDS
+    const double y2 = plane_by_plane(md, sc == 16 ? 0 : 1, 1) ? 0.0 : 4.0;  // plane kept in LDS
     const double grid = 4.0 * sc * (4.0 * Nx * Ny + y2 * Nx * Py);
     return vec + lam2 + nearb + (double)md.H[0] * md.H[1] * sc + grid;
   }
   const double v0_terms = md.fuse_proj[sc == 16 ? 0 : 1] ? 2.0 : 4.0;
-  const double v2_terms = 4.0 * Pz <= md.plane_fft[sc == 16 ? 0 : 1] ? 0.0 : 4.0;
+  const double v2_terms = plane_by_plane(md, sc == 16 ? 0 : 1, 1) ? 0.0 : 4.0;
   const double grid = 4.0 * sc * (v0_terms * V0 + 4.0 * V1 + v2_terms * V2);
   const double curl = md.curl64 ? 3.0 * n * K * sr : 0.0;  // combined field: interpolation only
   return vec + lam + curl + nearb + ghat + grid;
@@ -521,7 +521,7 @@ aim_status aim_debug_product_stage(aim_plan *plan, aim_precision prec, int32_t m
     // those grids in place
     // (where the passes along y and x run plane by plane, there is no stage 3 or 4 to
     // find afterwards: those run the separate passes)
-    const bool sep = stage == 4 && md.plane_fft[prec == AIM_FP64 ? 0 : 1] > 0;
+    const bool sep = stage == 4 && md.plane_fft[prec == AIM_FP64 ? 0 : 1].any();
     const int stop = (stage <= 3 || sep) ? stage : 6;
     StageView v[AIM_NSTAGE];
     if (prec == AIM_FP64) {

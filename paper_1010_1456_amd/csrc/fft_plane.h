@@ -79,30 +79,38 @@ struct PlaneCfg {
   static constexpr int NW = waves();
 };
 
-// planes (fields times kz) up to which the kernel is faster than the separate passes,
-// 0: never. Not all lengths divide well among the lanes of a wave: with P = R0 RM a
-// line takes R0 lanes, of which the outer stages use RM (112 = 14 x 8, 126 = 14 x 9),
-// and long lines leave one work-group per CU. Product on a 2-lambda sphere, separate ->
-// plane by plane, us, with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46 -> 37, 74 ->
-// 59, 137 -> 114, 272 -> 185; 90 47 -> 40, 77 -> 67, 149 -> 129, 300 -> 222; 96 47 -> 46,
-// 79 -> 78, 154 -> 152, 308 -> 262; 108 53 -> 45, 91 -> 88, 197 -> 177, 389 -> 333; 112
-// 53 -> 50, 94 -> 101, 208 -> 214, 407 -> 397; 120 56 -> 48, 100 -> 96, 243 -> 209, 440 ->
-// 391; 126 59 -> 52, 112 -> 107, 262 -> 239, 498 -> 454; 144 64 -> 67, 123 -> 134, 312 ->
-// 320, 576 -> 623; 162 84 -> 78, 180 -> 174, 492 -> 416, 935 -> 815. c128: 81 63 -> 53,
-// 115 -> 90, 262 -> 185, 487 -> 346; 90 67 -> 57, 125 -> 108, 305 -> 222, 572 -> 412; 96
-// 66 -> 61, 124 -> 120, 311 -> 263, 548 -> 489; 108 74 -> 70, 154 -> 159, 396 -> 355, 705
-// -> 692; 112 75 -> 76, 160 -> 178, 402 -> 420, 724 -> 798; 120 83 -> 72, 179 -> 167, 432
-// -> 410, 836 -> 777; 126 90 -> 84, 196 -> 204, 487 -> 505, 925 -> 984. Lengths up to 72
-// are faster by 5 to 35% throughout, but for 48 in c128 with 16 (71 -> 73).
+// Numbers of planes (fields times kz) for which the kernel is the faster one. Up to 90
+// points always. Above, few planes leave most CUs without one, and the time is one
+// plane's chain, which the separate passes spread over the chip (a flat scatterer
+// between grid planes, with one right-hand side 4 P_z planes). The bounds differ with the
+// chain: with P = R0 RM a line takes R0 lanes, of which the outer stages use RM (112 = 14
+// x 8 and 126 = 14 x 9 divide worst), and in FP64 there is one work-group per CU. Product, us, separate -> plane by plane, on scatterers that fill
+// their planes.
+// Spheres (P_z = P) with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46 -> 36, 73 -> 57,
+// 132 -> 108, 273 -> 188; 96 51 -> 49, 88 -> 84, 188 -> 165, 369 -> 310; 108 60 -> 53, 112 ->
+// 105, 272 -> 224, 521 -> 428; 112 64 -> 58, 123 -> 122, 300 -> 272, 531 -> 511; 126 77 ->
+// 66, 170 -> 140, 422 -> 339, 776 -> 643; 144 92 -> 92, 228 -> 205, 537 -> 503, 1031 -> 952
+// (64 of its 72 nodes: 84 -> 85, 196 -> 176, 466 -> 462, 899 -> 881); 162 142 -> 113, 359 ->
+// 281, 861 -> 687, 1684 -> 1298. c128: 48 34 -> 25, 47 -> 43, 74 -> 72, 109 -> 109; 81 62 ->
+// 51, 114 -> 89, 257 -> 179, 472 -> 333; 96 72 -> 66, 155 -> 132, 372 -> 299, 646 -> 550; 108
+// 94 -> 84, 222 -> 195, 498 -> 443, 925 -> 841; 112 98 -> 94, 235 -> 230, 532 -> 541, 1009 ->
+// 1011; 120 115 -> 94, 287 -> 232, 634 -> 552, 1207 -> 1018; 126 133 -> 112, 326 -> 286, 752
+// -> 695, 1446 -> 1316. Other lengths up to 120 are faster by 3 to 28%.
+// Plates of third order (P_z = 8) with 1, 3 and 8 right-hand sides (32, 96, 256 planes).
+// c64: 90 28 -> 23, 37 -> 30, 55 -> 51; 96 28 -> 27, 37 -> 32, 57 -> 57; 112 33 -> 33, 42 ->
+// 39, 65 -> 69; 126 35 -> 35, 46 -> 43, 73 -> 73; 144 38 -> 39, 52 -> 48, 85 -> 83; 162 42 ->
+// 44, 64 -> 58, 105 -> 98. c128: 90 36 -> 32, 50 -> 44, 76 -> 72; 96 37 -> 38, 51 -> 50, 77 ->
+// 80; 108 41 -> 43, 60 -> 57, 92 -> 92; 112 40 -> 50, 59 -> 65, 93 -> 106; 120 42 -> 46, 69 ->
+// 66, 103 -> 104; 126 44 -> 53, 75 -> 75, 111 -> 119.
 template <typename T, class PC>
-constexpr int64_t plane_limit() {
+constexpr PlaneRange plane_range() {
   constexpr int P = PC::P;
   constexpr bool f32 = sizeof(T) == 4;
-  if (!PlaneCfg<T, PC>::ok) return 0;
-  if (P == 144 || (!f32 && P == 112)) return 0;
-  if (P == (f32 ? 112 : 126)) return 512;  // one right-hand side
-  if (!f32 && P == 48) return 2048;        // up to ten
-  return INT64_MAX;
+  if (!PlaneCfg<T, PC>::ok) return PlaneRange{};
+  if (P <= 90) return PlaneRange{1, INT64_MAX};
+  if (f32) return PlaneRange{P < 144 ? 32 : 64, INT64_MAX};
+  if (P == 112) return PlaneRange{400, 511};  // (a sphere with one right-hand side)
+  return PlaneRange{P == 126 ? 300 : 64, INT64_MAX};
 }
 
 // Orders LDS accesses of a wave's lanes in the program (the hardware executes a
@@ -474,7 +482,7 @@ void launch_plane(const cx<T> *in, cx<T> *out, const PlaneOut &om, int Nx, int N
                   int Hy, const cx<T> *ghat, const cx<T> *tw, const int32_t *yrange,
                   hipStream_t s) {
   using C = PlaneCfg<T, PC>;
-  if constexpr (plane_limit<T, PC>() > 0) {
+  if constexpr (plane_range<T, PC>().any()) {
     if (Nx < 1 || Ny < 1 || 2 * Nx > PC::P + 1 || 2 * Ny > PC::P + 1 ||
         (PC::P % 2 == 0 && (2 * Nx > PC::P || 2 * Ny > PC::P)) || Hy != PC::P / 2 + 1)
       throw Error(AIM_ERR_ARG, "plane pass: more than P/2 sources on a line");

@@ -39,15 +39,15 @@ void fft_zplane_pass(const double2 *in, double2 *out, const FftPlan &pl, int n_i
   fftk::bad_length(pl.P);
 }
 
-int64_t fft_plane_limit(const double2 *, const FftPlan &pl) {
+PlaneRange fft_plane_range(const double2 *, const FftPlan &pl) {
   switch (pl.P) {
 #define AIM_X(P, a, b, c) \
   case P:                 \
-    return fftk::plane_limit<double, fftk::PlanC<a, b, c>>();
+    return fftk::plane_range<double, fftk::PlanC<a, b, c>>();
     AIM_FOR_EACH_FFT_PLAN(AIM_X)
 #undef AIM_X
     default:
-      return 0;
+      return PlaneRange{};
   }
 }
 bool fft_zplane_available(const double2 *, const FftPlan &pl) {

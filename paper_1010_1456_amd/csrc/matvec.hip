@@ -551,19 +551,26 @@ static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int6
   LAUNCHCHECK();
 }
 
-// plane by plane where both lengths have the kernel; a flat scatterer's few planes only
-// up to 81 points, above which one work-group's chain takes longer than three launches
-// (c64, product: 3-lambda plate 17.5 -> 13.4 us at 63 points, 5-lambda plate 18.6 ->
-// 19.1 us at 108); a caller that asks for tile rows or field groups gets the passes
-// these belong to
+// plane by plane where both lengths have the kernel; a flat scatterer's four planes
+// per right-hand side only up to 90 points in c64 and 81 in c128, above which one
+// work-group's chain takes longer than three launches (full plates, product, separate ->
+// plane by plane with 1 and 16 right-hand sides, us: c64 81 points 19.1 -> 15.0 and 33.2
+// -> 27.5, 90 18.8 -> 16.1 and 34.1 -> 30.1, 96 18.5 -> 19.4 and 34.2 -> 32.7, 126 20.0 ->
+// 23.2 and 46.2 -> 44.6; c128 81 19.5 -> 19.2 and 43.3 -> 37.0, 90 20.2 -> 21.4 and 45.2
+// -> 41.8, 126 22.6 -> 36.1 and 54.1 -> 60.6); a caller that asks for tile rows or field
+// groups gets the passes these belong to
 void choose_plane_fft(const Plan *pl, MeshDev &md) {
-  auto limit = [&](auto *v) -> int64_t {
-    if ((pl->params.tuning & 0xffff) != 0 || md.plan[0].P != md.plan[1].P) return 0;
-    if (md.planar_z >= 0 ? md.plan[0].P > 81 : !fft_zplane_available(v, md.plan[2])) return 0;
-    return fft_plane_limit(v, md.plan[0]);
+  auto range = [&](auto *v, int flat) {
+    if ((pl->params.tuning & 0xffff) != 0 || md.plan[0].P != md.plan[1].P) return PlaneRange{};
+    if (md.planar_z >= 0 ? md.plan[0].P > flat : !fft_zplane_available(v, md.plan[2]))
+      return PlaneRange{};
+    return fft_plane_range(v, md.plan[0]);
   };
-  md.plane_fft[0] = limit((const double2 *)nullptr);
-  md.plane_fft[1] = pl->mixed ? limit((const float2 *)nullptr) : 0;
+  md.plane_fft[0] = range((const double2 *)nullptr, 81);
+  md.plane_fft[1] = pl->mixed ? range((const float2 *)nullptr, 90) : PlaneRange{};
+}
+bool plane_by_plane(const MeshDev &md, int prec, int64_t nrhs) {
+  return md.plane_fft[prec].has(4 * nrhs * (md.planar_z >= 0 ? 1 : md.hp.pad[2]));
 }
 
 template <typename T, typename TX>
@@ -605,8 +612,8 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
   // the passes along y and x plane by plane, when the product runs through (the
   // stage boundaries between them then fall together: the forward y step carries
   // the time of all three)
-  const bool planes = F * (md.planar_z >= 0 ? 1 : Pz) <= md.plane_fft[prec] && stop >= 6 &&
-                      (first <= 1 || reserve) && !full3d;
+  const bool planes =
+      plane_by_plane(md, prec, nrhs) && stop >= 6 && (first <= 1 || reserve) && !full3d;
   // work buffer `which` of `count` elements per field, where a stage that is asked for
   // touches it
   auto buf = [&](int which, int64_t count, bool touched) {
@@ -1091,11 +1098,15 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       }
       md.gather_npw[prec] = choice;
     }
+    // whether every product runs plane by plane
+    auto all_planes = [&](int prec) {
+      return plane_by_plane(md, prec, 1) && md.plane_fft[prec].hi == INT64_MAX;
+    };
     // projection fused with the forward z pass, which one right-hand side alone takes
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       const bool thin = prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]);
-      if (thin || md.plane_fft[prec] == INT64_MAX || !fft_anterp_fused(md.plan[2])) {
+      if (thin || all_planes(prec) || !fft_anterp_fused(md.plan[2])) {
         md.fuse_proj[prec] = 0;
         continue;
       }
@@ -1130,7 +1141,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
           (prec == 0 ? thin_layout<double>(md.hp.pad[2]) : thin_layout<float>(md.hp.pad[2]));
       md.xy_groups[prec] = 1;
       md.x_row[prec] = md.y_row[prec] = rows == 2 ? 64 : 128;
-      if (rows == 0 && md.plane_fft[prec] < INT64_MAX) {
+      if (rows == 0 && !all_planes(prec)) {
         const float x128 = time_stages(prec, 4, 4, nr);
         md.x_row[prec] = 64;
         if (time_stages(prec, 4, 4, nr) >= margin * x128) md.x_row[prec] = 128;
@@ -1146,7 +1157,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
     }
     // every buffer of a product with up to nr right-hand sides, so that none is
     // allocated by the first one (which may be captured into a graph): those of nr
-    // and, where nr are too many planes, of the most that still run plane by plane
+    // and of the most below that whose passes are the others (separate or plane by plane)
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       auto reserve = [&](int r) {
@@ -1156,8 +1167,9 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
           far_stages<float, double>(pl, md, r, nullptr, n, 6, s, nullptr, false, nullptr, 7);
       };
       reserve(nr);
-      const int64_t most = md.plane_fft[prec] / (4 * (md.planar_z >= 0 ? 1 : md.hp.pad[2]));
-      if (most > 0 && most < nr) reserve((int)most);
+      int other = nr - 1;
+      while (other > 0 && plane_by_plane(md, prec, other) == plane_by_plane(md, prec, nr)) --other;
+      if (other > 0) reserve(other);
     }
   } catch (...) {
     (void)hipEventDestroy(e0);

@@ -405,8 +405,8 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
                          out, md.H[0], md.H[1], md.H[2]);
       LAUNCHCHECK();
     };
-    if (md.planar_z < 0 && md.plane_fft[0] > 0) planes(md.ghat64, md.ghatp64);
-    if (md.planar_z < 0 && md.plane_fft[1] > 0) planes(md.ghat32, md.ghatp32);
+    if (md.planar_z < 0 && md.plane_fft[0].any()) planes(md.ghat64, md.ghatp64);
+    if (md.planar_z < 0 && md.plane_fft[1].any()) planes(md.ghat32, md.ghatp32);
     HIPCHECK(hipStreamSynchronize(s));
     dev_free(pl, e0);
     dev_free(pl, e1);
