@@ -302,7 +302,11 @@ __global__ void __launch_bounds__(kMomThreads)
 // in one grid plane, whose other weights are zero.
 constexpr int kGridThreads = 256;
 constexpr int kGridNodes = 256;
-constexpr int kGridCells = 16384;  // largest box whose node map fits LDS (32 KB)
+// largest box (node map of 32 KB) and LDS in all of the per-row kernel: second-order
+// stencils fit up to a reach of 11 nodes (92 KB, 44 of them the table), in one grid
+// plane up to 55 (94 KB)
+constexpr int kGridCells = 16384;
+constexpr size_t kGridLds = 96 * 1024;
 struct GridNear {
   const int32_t *anchor3;
   const double *lam, *curl;
@@ -434,8 +438,8 @@ __global__ void __launch_bounds__(kGridThreads)
 }
 
 // The same subtraction one thread per entry by the double sum over the two
-// stencils, for near zones whose box of nodes does not fit LDS (reach beyond
-// about 11 nodes); the table may be large.
+// stencils, for near zones whose box of nodes and table do not fit LDS (kGridCells,
+// kGridLds); the table may be large.
 template <bool CF>
 __global__ void __launch_bounds__(128)
     k_near_grid_direct(GridNear gn, const int32_t *__restrict__ rowptr,
@@ -527,10 +531,9 @@ void near_fill_mesh(Plan *pl, MeshDev &md, const double *area, const int32_t *an
   hipLaunchKernelGGL(k_green_table, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, gtab,
                      gn.gd, h.k, h.h);
   LAUNCHCHECK();
-  // (the table has about an eighth of the box's nodes: at most 32 KB here)
   const size_t lds = sizeof(double2) * (4 * kGridNodes + ng) +
                      sizeof(unsigned short) * (kGridNodes + (size_t)ncell);
-  if (ncell <= kGridCells && lds <= 96 * 1024) {
+  if (ncell <= kGridCells && lds <= kGridLds) {
     auto go = [&](auto kern) {
       for_launches(n, [&](int64_t row0, unsigned rows) {
         hipLaunchKernelGGL(kern, dim3(rows), dim3(kGridThreads), lds, s, gn, md.rowptr, md.cols,

@@ -52,3 +52,40 @@ def test_near_matrix(name):
         assert np.abs(zd - op.zmom_diag).max() <= 1e-12 * np.abs(op.zmom_diag).max()
     finally:
         plan.close()
+
+
+# the per-row kernel with more than 64 KB of LDS, up to its bounds, and the first
+# reach beyond them: boxes of 23^3, 25^3 and 27^3 nodes; in one grid plane of 89^2,
+# 113^2 and 115^2
+WIDE = {
+    "box_reach_10": (lambda: sphere_mesh(0.8, FREQ, nf=3), 0.9, 0.6),
+    "box_reach_11": (lambda: sphere_mesh(0.8, FREQ, nf=3), 1.0, 0.6),
+    "box_reach_11_efie": (lambda: sphere_mesh(0.8, FREQ, nf=3), 1.0, None),
+    "box_reach_12": (lambda: sphere_mesh(0.8, FREQ, nf=3), 1.1, 0.6),
+    "plane_reach_43": (lambda: plate_mesh(6.2, FREQ, squares_per_lambda=1), 4.25, None),
+    "plane_reach_55": (lambda: plate_mesh(6.2, FREQ, squares_per_lambda=1), 5.45, None),
+    "plane_reach_56": (lambda: plate_mesh(6.2, FREQ, squares_per_lambda=1), 5.55, None),
+}
+
+
+@pytest.mark.parametrize("name", list(WIDE))
+def test_wide_near_zone(name):
+    from paper_1010_1456_amd import aim as A
+
+    make, radius, alpha = WIDE[name]
+    m = make()
+    kw = {} if alpha is None else {"cfie_alpha": alpha}
+    op = oaim.build_operator(build_rwg(m.verts, m.tris), wavenumber(FREQ), 0.1 * m.lam, 2,
+                             radius * m.lam, **kw)
+    plan = A.Plan([(m.verts, m.tris, FREQ)], near_radius_lambda=radius, mixed=False, **kw)
+    try:
+        reach = int(name.split("_")[2])
+        info = plan.info()
+        assert min(info["grid"][0][:2]) - 3 >= reach
+        assert (info["planar_z"][0] >= 0) == name.startswith("plane")
+        near = plan.export(0, A.AIM_DATA_NEAR64)
+        ref = op.near.data
+        assert near.shape == ref.shape
+        assert np.abs(near - ref).max() <= 1e-12 * np.abs(ref).max()
+    finally:
+        plan.close()
