@@ -37,15 +37,65 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 METRIC = "AIM matvec/s + % HBM roofline, mixed vs FP64 at equal RCS err (sphere 8λ)"
 STAGES = ["projection", "fwd_z", "fwd_y", "x_green", "inv_y", "inv_z", "interp_near"]
-# kernel of each stage on the mixed path (the projection's depends on the tuned variant)
-KERNELS = [None, "k_fft_contig<float, false", "k_fft_strided<float, false", "k_fft_mid<float",
-           "k_fft_strided<float, true", "k_fft_contig<float, true", "k_interp_near<float"]
 
 
-def stage_kernel(d, fused):
-    if d == 0:
-        return "k_anterp_fftz<float" if fused else "k_anterp_gather<float"
-    return KERNELS[d]
+def kernel_stages(names, planar):
+    """{stage: kernel} of one scatterer's product from its kernels in launch order: the
+    passes before the x pass are forward ones, those after it inverse; one kernel runs
+    stages 2 to 4 where they go plane by plane (k_fft_plane) or are pipelined
+    (k_fft_xy); a scatterer in one grid plane has no z passes."""
+    out, past = {}, False
+    for k in names:
+        if k.startswith("k_interp"):
+            out[6] = k
+        elif k.startswith("k_anterp"):
+            out[0] = k
+        elif k.startswith(("k_fft_plane", "k_fft_xy")):
+            out[2], past = k, True
+        elif k.startswith("k_fft_mid"):
+            out[3], past = k, True
+        elif k.startswith("k_fft") and not past:
+            out[2 if planar or 1 in out or "fftz" in out.get(0, "") else 1] = k
+        elif k.startswith("k_fft"):
+            out[4 if 3 in out and 4 not in out else 5] = k
+    return out
+
+
+def product_kernels(plan, A, info, prec, x, y):
+    """kernel_stages of every scatterer of one product, as the library launched it
+    (None where the profiler shows nothing, as under another profiler)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    if any(k.startswith(("ROCPROF", "ROCP_")) for k in os.environ):
+        return None
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        plan.matvec_timed(x, y, prec, 1)
+        torch.cuda.synchronize()
+    events = sorted((e for e in prof.events() if "aim::" in e.name), key=lambda e: e.time_range.start)
+    groups = [[]]
+    for e in events:
+        groups[-1].append(short_kernel(e.name))
+        if groups[-1][-1].startswith("k_interp"):
+            groups.append([])
+    if groups.pop() or len(groups) < info["nmesh"]:
+        return None
+    # (the leftover right-hand sides of a scatterer are a second k_interp launch)
+    merged = []
+    for g in groups:
+        if len(g) == 1 and merged:
+            continue
+        merged.append(g)
+    if len(merged) != info["nmesh"]:
+        return None
+    return [kernel_stages(g, info["planar_z"][m] >= 0) for m, g in enumerate(merged)]
+
+
+def planes_of(kernels, nmesh):
+    """Per scatterer: whether one kernel runs the y, x and inverse y passes plane by plane."""
+    if kernels is None:
+        return [False] * nmesh
+    return [k.get(2, "").startswith("k_fft_plane") for k in kernels]
 
 
 CSRC = os.path.join(ROOT, "paper_1010_1456_amd", "csrc")
@@ -58,11 +108,10 @@ def log(msg):
 
 
 # sources that define the product's kernels, their launches and the layout of
-# the operator data they read (the solver, RCS, ABI glue, host planning and
-# near-field quadrature do not change a product kernel's memory traffic)
+# the operator data they read, its order included (the solver, RCS, ABI glue, host
+# planning and near-field quadrature do not change a product kernel's memory traffic)
 MATVEC_SOURCES_EXCLUDED = ("api.hip", "solver.hip", "rcs.hip", "host_plan.cpp", "geom_device.h",
-                           "turns.h", "scan.h", "node_tables.hip", "near_pattern.hip",
-                           "near_fill.hip")
+                           "turns.h", "near_fill.hip")
 
 
 def sources_digest():
@@ -142,12 +191,14 @@ def measured_traffic(workload, kernel_prefix, row=None):
     return float(t["kernels"][hits[0]]["bytes"]) if len(hits) == 1 else None
 
 
-def stage_bytes(info, mesh, nrhs, s_grid, s_real, s_x, s_y, path):
+def stage_bytes(info, mesh, nrhs, s_grid, s_real, s_x, s_y, path, planes=False):
     """Algorithmic HBM bytes of each step of one product: every operator datum
     read once, vectors read/written once, grid fields per the pruned passes:
     the projection writes and the interpolation reads the occupied nodes only
     (O of them, on L z lines), the z passes move the L occupied lines, the
-    forward y pass reads their rows and the inverse y pass writes them."""
+    forward y pass reads their rows and the inverse y pass writes them. With
+    planes (plane by plane) the forward y step stands for the y, x and inverse y
+    passes: unpadded planes in and out, and the spectrum."""
     n = info["n"][mesh]
     nnz = info["nnz"][mesh]
     K = (info["order"] + 1) ** 3
@@ -163,39 +214,41 @@ def stage_bytes(info, mesh, nrhs, s_grid, s_real, s_x, s_y, path):
         A1, A2 = Nx * Ny, Nx * Py
         H2 = (Px // 2 + 1) * (Py // 2 + 1)
         lam2 = n * (4 * (info["order"] + 1) ** 2 * s_real + 4)
+        y_x_y = ([2 * F * A1 * s_grid + H2 * s_grid, 0.0, 0.0] if planes else
+                 [F * (A1 + A2) * s_grid, 2 * F * A2 * s_grid + H2 * s_grid, F * (A2 + A1) * s_grid])
         return np.array([
             F * O * s_grid + lam2 + nrhs * n * s_x,
             0.0,
-            F * (A1 + A2) * s_grid,
-            2 * F * A2 * s_grid + H2 * s_grid,
-            F * (A2 + A1) * s_grid,
+            *y_x_y,
             0.0,
             F * O * s_grid + lam2 + nnz * (s_grid + 4) + 4 * (n + 1) + nrhs * n * (s_x + s_y),
         ], dtype=np.float64)
-    if info["fused_projection"][mesh][path]:  # projection inside the forward z pass
+    if info["fused_projection"][mesh][path] and nrhs == 1 and not planes:  # projection inside the forward z pass
         proj, fwdz = lam + nrhs * n * s_x + F * L * Pz * s_grid, 0.0
     else:
         proj, fwdz = F * O * s_grid + lam + nrhs * n * s_x, F * L * (Nz + Pz) * s_grid
+    y_x_y = ([2 * F * L * Pz * s_grid + H * s_grid, 0.0, 0.0] if planes else
+             [F * (L * Pz + V2) * s_grid, 2 * F * V2 * s_grid + H * s_grid, F * (V2 + L * Pz) * s_grid])
     return np.array([
         proj,                                                          # projection (+ forward z)
         fwdz,                                                          # forward z
-        F * (L * Pz + V2) * s_grid,                                    # forward y
-        2 * F * V2 * s_grid + H * s_grid,                              # x pass + spectrum
-        F * (V2 + L * Pz) * s_grid,                                    # inverse y
+        *y_x_y,                                                        # forward y, x pass, inverse y
         F * L * (Pz + Nz) * s_grid,                                    # inverse z
         F * O * s_grid + lam + nnz * (s_grid + 4) + 4 * (n + 1)
         + nrhs * n * (s_x + s_y) + curl,                               # interp + near
     ], dtype=np.float64)
 
 
-def x_pass_flops(info, nrhs):
+def x_pass_flops(info, nrhs, planes):
     """Algorithmic floating-point operations of the x pass of one product,
-    summed over the scatterers: per line a forward and an inverse complex FFT
+    summed over the scatterers that have one of its own (planes[mesh] not set): per line a forward and an inverse complex FFT
     of the padded length P (5 P log2 P each, the radix-2 count) and the
     spectrum multiply (6 P); lines = fields x P_y x P_z (P_y only for a
     scatterer in one grid plane)."""
     total = 0.0
     for mesh in range(info["nmesh"]):
+        if planes[mesh]:
+            continue
         Px, Py, Pz = info["pad"][mesh]
         lines = 4 * nrhs * Py * (1 if info["planar_z"][mesh] >= 0 else Pz)
         total += lines * (2 * 5 * Px * np.log2(Px) + 6 * Px)
@@ -220,10 +273,12 @@ def pipelined_bytes(info, mesh, path, b):
     return b
 
 
-def x_pass_alu(info, nrhs, ms):
+def x_pass_alu(info, nrhs, ms, planes):
     """The x pass is bound by vector-ALU issue rather than HBM: its FLOP rate
-    against the FP32 vector peaks."""
-    fl = x_pass_flops(info, nrhs)
+    against the FP32 vector peaks (None if no scatterer has an x pass of its own)."""
+    if all(planes):
+        return None
+    fl = x_pass_flops(info, nrhs, planes)
     tf = fl / (ms * 1e-3) / 1e12
     return {"bound": "alu", "flops_per_launch": fl, "avg_launch_ms": float(ms),
             "achieved_TFLOPs": tf,
@@ -569,10 +624,14 @@ def measure_plan(plan, A, info, R, x, y, steps, warmup, launches):
                                      ("fp64", A.AIM_FP64, 16, 8, 0)):
         log(f"[bench] timing {name}: {warmup} warm-up, {launches} graph launches of {steps} products")
         launch_ms, st_ms, wall = time_path(plan, A, prec, x, y, steps, warmup, launches)
-        b = sum(pipelined_bytes(info, mi, path, stage_bytes(info, mi, R, sg, sr, 16, 16, path))
+        kernels = product_kernels(plan, A, info, prec, x, y)
+        planes = planes_of(kernels, info["nmesh"])
+        b = sum(pipelined_bytes(info, mi, path,
+                                stage_bytes(info, mi, R, sg, sr, 16, 16, path, planes[mi]))
                 for mi in range(info["nmesh"]))
         med = float(np.median(launch_ms))
         res[name] = dict(launch_ms=launch_ms, ms_per_step=med / steps, stage_ms=st_ms, bytes=b,
+                         kernels=kernels, planes=planes,
                          wall=wall, value=R * steps / (med * 1e-3))
         log(f"[bench] {name}: {med / steps:.4f} ms/product (graph, median of {launches}; launches "
             + ",".join(f"{v / steps:.4f}" for v in launch_ms) + "), stages(ms)="
@@ -685,12 +744,13 @@ def main(argv=None):
     res = measure_plan(plan, A, info, R, x, y, args.steps, args.warmup, args.launches)
 
     mx = res["mixed"]
-    fused = bool(info["fused_projection"][0][1])  # (first scatterer's variant names the kernel)
-    piped = info["xy_groups"][0][1] > 1
     d = int(np.argmax(mx["stage_ms"]))
-    kname = ("k_fft_xy<float> (fwd_y + x_green + inv_y pipelined over "
-             f"{info['xy_groups'][0][1]} field groups)" if piped and d == 2
-             else stage_kernel(d, fused) + f"> ({STAGES[d]})")
+    # the dominant step's kernels, one per kind over the scatterers
+    used = sorted({k[d].split(", PlanC")[0] for k in mx["kernels"] or [] if d in k})
+    whole = d == 2 and (any(mx["planes"]) or info["xy_groups"][0][1] > 1)
+    kname = (" and ".join(u if u.endswith(">") else u + ">" for u in used)
+             or "kernel not identified") + (
+        " (fwd_y + x_green + inv_y)" if whole else f" ({STAGES[d]})")
     achieved = mx["bytes"][d] / (mx["stage_ms"][d] * 1e-3) / 1e9
     total_bytes = float(mx["bytes"].sum())
     forms = sorted({"EFIE" if a is None else f"CFIE alpha={a}" for a in info["cfie_alpha"]})
@@ -727,6 +787,7 @@ def main(argv=None):
             "gather_nodes_per_wave": info["gather_npw"][0][1],
             "xy_pipeline_groups": info["xy_groups"][0][1],
             "tile_bytes_x_y": info["tile_bytes"][0][1],
+            "plane_by_plane": mx["planes"],
         },
         "roofline": {
             "bound": "hbm",
@@ -735,16 +796,16 @@ def main(argv=None):
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": measured_traffic(args.workload, "k_fft_xy<float" if piped and d == 2
-                                        else stage_kernel(d, fused),
+            "traffic": measured_traffic(args.workload, used[0],
                                         row=(info["tile_bytes"][0][1][0] if d == 3 else
-                                             info["tile_bytes"][0][1][1] if d in (2, 4) else None)),
+                                             info["tile_bytes"][0][1][1] if d in (2, 4) else None))
+            if len(used) == 1 else None,
             "algorithmic_bytes_per_launch": float(mx["bytes"][d]),
             "avg_launch_ms": float(mx["stage_ms"][d]),
             "copy_GBs": copy_gbs,
             "frac_of_copy": achieved / copy_gbs,
         },
-        "x_pass_alu": x_pass_alu(info, R, mx["stage_ms"][3]) if mx["stage_ms"][3] > 0.01 else None,
+        "x_pass_alu": x_pass_alu(info, R, mx["stage_ms"][3], mx["planes"]) if mx["stage_ms"][3] > 0.01 else None,
         "matvec_roofline": {
             "algorithmic_bytes": total_bytes,
             "achieved_GBs": total_bytes / (mx["ms_per_step"] * 1e-3) / 1e9,
