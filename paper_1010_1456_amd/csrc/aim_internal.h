@@ -246,6 +246,11 @@ void *dev_alloc(Plan *pl, size_t bytes);
 void dev_free(Plan *pl, void *p);
 // grid size of a launch of count threads, t per work-group
 inline unsigned launch_blocks(int64_t count, int t) { return (unsigned)((count + t - 1) / t); }
+// the same, at most 2^16, for kernels whose threads go through the count in strides
+inline unsigned loop_blocks(int64_t count, int t) {
+  const int64_t n = (count + t - 1) / t;
+  return (unsigned)(n < 65536 ? n : 65536);
+}
 // A launch holds fewer than 2^32 threads (one of more is cut short without an error,
 // leaving rows untouched): f(first, number) for runs of consecutive
 // work-groups, of up to 256 threads each, that add up to `groups`

@@ -124,10 +124,18 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// (grids of many right-hand sides have more elements than a launch has threads)
 template <typename T>
 __global__ void k_zero(cx<T> *__restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i].x = p[i].y = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    p[i].x = p[i].y = 0;
+}
+template <typename T>
+void clear(cx<T> *p, int64_t n, hipStream_t s) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL((k_zero<T>), dim3(loop_blocks(n, 256)), dim3(256), 0, s, p, n);
+  LAUNCHCHECK();
 }
 
 // thin [F][Pz][A] grid -> plain [F][A][Pz] (inspection)
@@ -442,10 +450,7 @@ static cx<T> *zeroed_buffer(Plan *pl, void *(&buf)[2], size_t (&have)[2], size_t
     buf[prec] = dev_alloc(pl, bytes);
     have[prec] = bytes;
     ++pl->work_gen;
-    const int64_t n = (int64_t)(bytes / sizeof(cx<T>));
-    hipLaunchKernelGGL((k_zero<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       (cx<T> *)buf[prec], n);
-    LAUNCHCHECK();
+    clear<T>((cx<T> *)buf[prec], (int64_t)(bytes / sizeof(cx<T>)), s);
   }
   return (cx<T> *)buf[prec];
 }
@@ -461,11 +466,8 @@ static cx<T> *src_buffer(Plan *pl, MeshDev &md, size_t bytes, int layout, hipStr
   cx<T> *p = zeroed_buffer<T>(pl, md.src, md.src_bytes, bytes, s);
   if (md.src_layout[prec] != layout) {
     ++pl->work_gen;
-    if (md.src_bytes[prec] == had) {  // not just zeroed
-      const int64_t n = (int64_t)(had / sizeof(cx<T>));
-      hipLaunchKernelGGL((k_zero<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
-      LAUNCHCHECK();
-    }
+    if (md.src_bytes[prec] == had)  // not just zeroed
+      clear<T>(p, (int64_t)(had / sizeof(cx<T>)), s);
   }
   md.src_layout[prec] = layout;
   return p;
@@ -485,16 +487,10 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
       // the propagated fields: the inverse z pass writes the occupied lines
       // only and the interpolation multiplies the others by zero weights, so
       // they must hold finite values
-      if (prec == 0) {
-        const int64_t n = (int64_t)(bytes / sizeof(double2));
-        hipLaunchKernelGGL((k_zero<double>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (double2 *)work[which], n);
-      } else {
-        const int64_t n = (int64_t)(bytes / sizeof(float2));
-        hipLaunchKernelGGL((k_zero<float>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                           (float2 *)work[which], n);
-      }
-      LAUNCHCHECK();
+      if (prec == 0)
+        clear<double>((double2 *)work[which], (int64_t)(bytes / sizeof(double2)), s);
+      else
+        clear<float>((float2 *)work[which], (int64_t)(bytes / sizeof(float2)), s);
     }
   }
   return work[which];

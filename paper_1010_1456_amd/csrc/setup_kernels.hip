@@ -104,9 +104,11 @@ __global__ void k_curl_projection(const int32_t *rwg, const double *len, const d
   curl[(b * 3 + 2) * K + u] = acc.z;
 }
 
+// (high orders of large meshes have more weights than a launch has threads)
 __global__ void k_to_float(const double *in, float *out, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (float)in[i];
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = (float)in[i];
 }
 
 // g on the circulant embedding [Px][Py][Pz]: index i folds to min(i, P - i)
@@ -308,7 +310,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
   LAUNCHCHECK();
   if (pl->mixed) {
     md.lam32 = (float *)dev_alloc(pl, sizeof(float) * n * 4 * K);
-    hipLaunchKernelGGL(k_to_float, dim3(blocks_for(n * 4 * K, 256)), dim3(256), 0, s, md.lam64,
+    hipLaunchKernelGGL(k_to_float, dim3(loop_blocks(n * 4 * K, 256)), dim3(256), 0, s, md.lam64,
                        md.lam32, n * 4 * K);
     LAUNCHCHECK();
   }
@@ -320,7 +322,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     LAUNCHCHECK();
     if (pl->mixed) {
       md.curl32 = (float *)dev_alloc(pl, sizeof(float) * n * 3 * K);
-      hipLaunchKernelGGL(k_to_float, dim3(blocks_for(n * 3 * K, 256)), dim3(256), 0, s, md.curl64,
+      hipLaunchKernelGGL(k_to_float, dim3(loop_blocks(n * 3 * K, 256)), dim3(256), 0, s, md.curl64,
                          md.curl32, n * 3 * K);
       LAUNCHCHECK();
     }
@@ -349,7 +351,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     LAUNCHCHECK();
     if (pl->mixed) {
       md.plane_lam32 = (float *)dev_alloc(pl, sizeof(float) * n * 4 * K2);
-      hipLaunchKernelGGL(k_to_float, dim3(blocks_for(n * 4 * K2, 256)), dim3(256), 0, s,
+      hipLaunchKernelGGL(k_to_float, dim3(loop_blocks(n * 4 * K2, 256)), dim3(256), 0, s,
                          md.plane_lam64, md.plane_lam32, n * 4 * K2);
       LAUNCHCHECK();
     }
@@ -394,7 +396,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     LAUNCHCHECK();
     if (pl->mixed) {
       md.ghat32 = (float2 *)dev_alloc(pl, sizeof(float2) * noct);
-      hipLaunchKernelGGL(k_to_float, dim3(blocks_for(2 * noct, 256)), dim3(256), 0, s,
+      hipLaunchKernelGGL(k_to_float, dim3(loop_blocks(2 * noct, 256)), dim3(256), 0, s,
                          (const double *)md.ghat64, (float *)md.ghat32, 2 * noct);
       LAUNCHCHECK();
     }
@@ -419,7 +421,7 @@ void setup_mesh_device(Plan *pl, MeshDev &md, hipStream_t s) {
     LAUNCHCHECK();
     if (pl->mixed) {
       md.ghat2d32 = (float2 *)dev_alloc(pl, sizeof(float2) * n2);
-      hipLaunchKernelGGL(k_to_float, dim3(blocks_for(2 * n2, 256)), dim3(256), 0, s,
+      hipLaunchKernelGGL(k_to_float, dim3(loop_blocks(2 * n2, 256)), dim3(256), 0, s,
                          (const double *)md.ghat2d64, (float *)md.ghat2d32, 2 * n2);
       LAUNCHCHECK();
     }
