@@ -2,7 +2,7 @@
 // transforms, forward x, product with the spectrum, inverse x, inverse y, with the
 // plane kept in LDS in between. The three separate passes move the plane's padded
 // rows through memory four times and its unpadded ones twice; this reads and writes
-// the unpadded plane once (20 -> 4 units of N^2 elements, N = P / 2).
+// the unpadded plane once (10 -> 2 N^2 elements, N = P / 2).
 //
 // Data are kz-outer, [F][Pz][Nx][Ny], and so is the spectrum, [Hz][Hx][Hy]. Lines
 // are transformed by groups of lanes of one wave, several lines per wave, so that a
@@ -84,8 +84,8 @@ struct PlaneCfg {
 // plane's chain, which the separate passes spread over the chip (a flat scatterer
 // between grid planes, with one right-hand side 4 P_z planes). The bounds differ with the
 // chain: with P = R0 RM a line takes R0 lanes, of which the outer stages use RM (112 = 14
-// x 8 and 126 = 14 x 9 divide worst), and in FP64 there is one work-group per CU. Product, us, separate -> plane by plane, on scatterers that fill
-// their planes.
+// x 8 and 126 = 14 x 9 divide worst), and in FP64 there is one work-group per CU.
+// Product, us, separate -> plane by plane, on scatterers that fill their planes.
 // Spheres (P_z = P) with 1, 3, 8 and 16 right-hand sides. c64: P = 81 46 -> 36, 73 -> 57,
 // 132 -> 108, 273 -> 188; 96 51 -> 49, 88 -> 84, 188 -> 165, 369 -> 310; 108 60 -> 53, 112 ->
 // 105, 272 -> 224, 521 -> 428; 112 64 -> 58, 123 -> 122, 300 -> 272, 531 -> 511; 126 77 ->

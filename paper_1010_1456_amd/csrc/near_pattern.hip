@@ -25,10 +25,6 @@ struct Cells {
   }
 };
 
-__global__ void k_zero_ints(int32_t *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
 __global__ void k_cell_count(const double *centre, int64_t n, Cells ce, int32_t *cell_of,
                              int32_t *count) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -141,7 +137,7 @@ void near_pattern_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
   HIPCHECK(hipMemcpyAsync(centre, h.centre.data(), sizeof(double) * 3 * n, hipMemcpyHostToDevice, s));
   int32_t *count = ints(std::max(ncell, n)), *cell_of = ints(n), *cstart = ints(ncell + 1),
           *members = ints(n);
-  hipLaunchKernelGGL(k_zero_ints, dim3(launch_blocks(ncell, 256)), dim3(256), 0, s, count, ncell);
+  hipLaunchKernelGGL(k_clear, dim3(launch_blocks(ncell, 256)), dim3(256), 0, s, count, ncell);
   LAUNCHCHECK();
   hipLaunchKernelGGL(k_cell_count, dim3(launch_blocks(n, 256)), dim3(256), 0, s, centre, n, ce,
                      cell_of, count);

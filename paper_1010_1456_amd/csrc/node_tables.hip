@@ -14,11 +14,6 @@ namespace aim {
 
 namespace {
 
-__global__ void k_clear(int32_t *p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 // whether basis b has any non-zero weight at its stencil node u: projection or,
 // for the combined field, curl weight (the node is then read by the
 // interpolation even where its projection weights vanish, as off a flat face

@@ -12,6 +12,11 @@
 namespace aim {
 namespace {
 
+__global__ void k_clear(int32_t *p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
 constexpr int kScanThreads = 256, kScanPer = 8, kScanItems = kScanThreads * kScanPer;
 inline int64_t scan_blocks(int64_t count) { return (count + kScanItems - 1) / kScanItems; }
 
