@@ -222,9 +222,9 @@ __global__ void __launch_bounds__(256)
                   cx<TY> *__restrict__ y, int64_t ldy, int64_t n, T keta, T inv_k2, T eta_h) {
   using V = cx<T>;
   constexpr int NU = kNearUnroll * kRowLanes / LANES, SU = kStencilUnroll;
-  // sums per lane: in float two with 16 lanes, so that they are as short as with 32
-  // (8-lambda sphere, error against FP64: one 1.043e-7, two 1.024e-7, 32 lanes 1.025e-7;
-  // the same time)
+  // near sums per lane: in float two with 16 lanes, so that they are as short as with
+  // 32 (8-lambda sphere, error against FP64: one 1.043e-7, two 0.994e-7, 32 lanes
+  // 1.025e-7; the same registers and time)
   constexpr int NS = sizeof(T) == 4 ? 32 / LANES : 1;
   const int lane = threadIdx.x & (LANES - 1);
   const int64_t m = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
@@ -235,12 +235,13 @@ __global__ void __launch_bounds__(256)
   const int64_t a = anchor_lin[m];
   const int e0 = rowptr[m], e1 = rowptr[m + 1];
   const int r0 = r_first + blockIdx.y * RB;  // first right-hand side of this row
-  V far[RB][NS], nr[RB][NS], fk[RB][NS];
+  V far[RB], nr[RB][NS], fk[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int rb = 0; rb < RB; ++rb) {
+    far[rb].x = far[rb].y = fk[rb].x = fk[rb].y = 0;
 #pragma unroll
-    for (int j = 0; j < NS; ++j)
-      far[rb][j].x = far[rb][j].y = nr[rb][j].x = nr[rb][j].y = fk[rb][j].x = fk[rb][j].y = 0;
+    for (int j = 0; j < NS; ++j) nr[rb][j].x = nr[rb][j].y = 0;
+  }
   V z[NU];
   int c[NU];
   auto load_near = [&](int eb) {  // entries eb, eb + 16, ... of this lane
@@ -276,16 +277,16 @@ __global__ void __launch_bounds__(256)
       }
     }
   };
-  auto far_node = [&](int j, int64_t o, T l0, T l1, T l2, T l3, T w0, T w1, T w2) {
+  auto far_node = [&](int64_t o, T l0, T l1, T l2, T l3, T w0, T w1, T w2) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const V *ph = phi + o * nf + (r0 + rb) * 4;  // fields interleaved per node
       const V p0 = ph[0], p1 = ph[1], p2 = ph[2], p3 = ph[3];
-      far[rb][j].x += l0 * p0.x + l1 * p1.x + l2 * p2.x - inv_k2 * l3 * p3.x;
-      far[rb][j].y += l0 * p0.y + l1 * p1.y + l2 * p2.y - inv_k2 * l3 * p3.y;
+      far[rb].x += l0 * p0.x + l1 * p1.x + l2 * p2.x - inv_k2 * l3 * p3.x;
+      far[rb].y += l0 * p0.y + l1 * p1.y + l2 * p2.y - inv_k2 * l3 * p3.y;
       if (CF) {
-        fk[rb][j].x += w0 * p0.x + w1 * p1.x + w2 * p2.x;
-        fk[rb][j].y += w0 * p0.y + w1 * p1.y + w2 * p2.y;
+        fk[rb].x += w0 * p0.x + w1 * p1.x + w2 * p2.x;
+        fk[rb].y += w0 * p0.y + w1 * p1.y + w2 * p2.y;
       }
     }
   };
@@ -304,8 +305,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
     for (int k = 0; k < SU; ++k)
       if (u0 + LANES * k < K)
-        far_node(k % NS, a + so[k], l[k][0], l[k][1], l[k][2], l[k][3], w[k][0], w[k][1],
-                 w[k][2]);
+        far_node(a + so[k], l[k][0], l[k][1], l[k][2], l[k][3], w[k][0], w[k][1], w[k][2]);
     if (u0 + LANES * SU < K)  // the next nodes (orders above 2)
 #pragma unroll
       for (int k = 0; k < SU; ++k) {
@@ -321,18 +321,16 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     V acc;
-    acc.x = acc.y = 0;
+    acc.x = -keta * far[rb].y;  // j k eta * far
+    acc.y = keta * far[rb].x;
+    if (CF) {
+      acc.x -= eta_h * fk[rb].x;
+      acc.y -= eta_h * fk[rb].y;
+    }
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-      V part;
-      part.x = -keta * far[rb][j].y + nr[rb][j].x;  // j k eta * far
-      part.y = keta * far[rb][j].x + nr[rb][j].y;
-      if (CF) {
-        part.x -= eta_h * fk[rb][j].x;
-        part.y -= eta_h * fk[rb][j].y;
-      }
-      acc.x += part.x;
-      acc.y += part.y;
+      acc.x += nr[rb][j].x;
+      acc.y += nr[rb][j].y;
     }
     acc = row_sum<LANES>(acc);
     if (lane == 0) {
