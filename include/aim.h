@@ -256,9 +256,9 @@ typedef struct aim_host_plan aim_host_plan;
 /* ---- set-up ------------------------------------------------------------ */
 
 /* Builds the operator for nmesh (1..AIM_MAX_MESH) scatterers: host planning
- * (mesh validation, RWG table, grid, stencil anchors, near-zone pattern),
- * then on the GPU the projection weights, the spectrum of the grid Green's
- * function, and the FP64 near-zone matrix Z^MOM - Z^grid with singularity
+ * (mesh validation, RWG table, grid, stencil anchors), then on the GPU the
+ * projection weights, the spectrum of the grid Green's function, and the
+ * near-zone pattern and FP64 matrix Z^MOM - Z^grid with singularity
  * extraction on touching triangle pairs; finally it times the alternative
  * kernel variants of each mesh and keeps the faster (results do not depend
  * on the choice beyond rounding). Unknowns of mesh i occupy rows
@@ -276,7 +276,12 @@ void aim_destroy(aim_plan *plan);
 
 /* y = Z^AIM x for nrhs right-hand sides (asynchronous). x, y: device,
  * column-major [n_total][nrhs]; c128 for AIM_FP64, c64 for AIM_MIXED.
- * x and y must not overlap. */
+ * x and y must not overlap. The kernels depend on nrhs, so a column may round
+ * differently with another number of columns; with the same number its bits
+ * are the same on every call. Set-up leaves the buffers of products with up to
+ * the right-hand sides announced in aim_params.tuning (one if none), which so
+ * allocate nothing and can be captured into a graph; the first product with
+ * more grows them. */
 aim_status aim_matvec(aim_plan *plan, aim_precision prec, int32_t nrhs,
                       const void *x, void *y, void *hip_stream);
 

@@ -495,10 +495,12 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
 }
 
 // Lanes per node (row) of the several-right-hand-sides kernels (multi_rhs.h), 0:
-// the others. From 6 on they are faster on every mesh measured (projection and
-// interpolation together, 4-lambda CFIE sphere: 8 right-hand sides 145 -> 119 us
-// in c64 and 276 -> 209 in FP64, 16: 248 -> 170 and 528 -> 306); with 3 or 4 their
-// short runs lose (4: 85 -> 99 and 164 -> 170), at 5 the two are equal.
+// the others. From 6 on they are faster on nearly every mesh measured (projection and
+// interpolation together, 4-lambda CFIE sphere, the others -> these: 4 right-hand sides
+// 82 -> 109 us in c64 and 154 -> 178 in FP64, 5 106 -> 111 and 191 -> 182; 16-lambda
+// plate: 4 45 -> 56 and 74 -> 74, 5 58 -> 56 and 94 -> 75; 8 and 16 on that sphere take
+// 118 and 185, and 200 and 290, where four per launch row took 149 and 276, and 354 and
+// 671)
 constexpr int kMultiFrom = 6;
 static int multi_lanes(int nrhs) { return nrhs < kMultiFrom ? 0 : (nrhs <= 8 ? 8 : 16); }
 

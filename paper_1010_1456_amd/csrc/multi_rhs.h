@@ -8,13 +8,14 @@
 // (row): its 32 / LR groups of lanes walk every (32 / LR)-th entry and add their
 // sums by exchanges in a fixed order (a group alone per row waits on a chain four
 // times as long, and a whole wave per row leaves most of it idle: 4-lambda CFIE
-// sphere, 16 right-hand sides, c64: 64 + 118 us and 87 + 110 against 70 + 101).
+// sphere, 16 right-hand sides, c64, with 8 near sums per row: 64 + 118 us and 87 + 110
+// against 70 + 101).
 // The entries, columns and weights, the same for all right-hand sides, are staged
 // through LDS, and results leave through LDS so that stores run along nodes
 // (rows). Bound by the latency of those gathers and the L1 traffic of the fields
 // (27 x 512 bytes per row and 16 right-hand sides). One right-hand side per launch
-// row in the projection and four in the interpolation took 113 + 154 us there, and
-// 294 + 253 in FP64 at third order on the 2.7-lambda sphere (now 85 + 169).
+// row in the projection and four in the interpolation took 94 + 183 us there (now 71 +
+// 114), and 227 + 360 in FP64 at third order on the 2.7-lambda sphere (now 73 + 162).
 #pragma once
 
 #include "aim_internal.h"
@@ -25,11 +26,13 @@ namespace {
 constexpr int kMultiThreads = 256;
 constexpr int kMultiRows = kMultiThreads / 32;  // nodes (rows) per work-group
 // Partial sums per lane of the near product (half as many for the stencil and the
-// projection), added in pairs at the end. In float 16 per row, of some 5 entries
-// each: with 8 the product's error against FP64 was 1.04e-7 on the 2-lambda sphere
-// (16 right-hand sides) where 32 lanes per row, one right-hand side at a time, have
-// 0.978e-7; with 16 it is 0.977e-7, and the interpolation takes 114 us on the
-// 4-lambda sphere (8: 117; 16 also for the stencil 150). In FP64 four per lane.
+// projection), added in pairs, the last two to the far part. In float 16 per row, of
+// some 5 entries each: with 8 the product's error against FP64 is 1.04e-7 on the
+// 2-lambda sphere (16 right-hand sides) where 32 lanes per row, one right-hand side at
+// a time, have 0.978e-7; with 16 it is 0.930e-7 (0.977e-7 where the near sum is
+// complete before it meets the far part, which it partly cancels), and the
+// interpolation takes 114 us on the 4-lambda sphere (8: 117; 16 also for the stencil:
+// 150). In FP64 four per lane.
 template <typename T, int SEG>
 constexpr int near_sums() {
   return sizeof(T) == 4 ? 16 / SEG : 4;
@@ -266,10 +269,15 @@ __global__ void __launch_bounds__(kMultiThreads)
       }
   }
 #pragma unroll
-  for (int h = NN / 2; h > 0; h /= 2) halve(nr, h);
+  for (int h = NN / 2; h >= 2; h /= 2) halve(nr, h);
   V acc;
-  acc.x = -keta * far[0].y + nr[0].x - (CF ? eta_h * fk[0].x : (T)0);  // j k eta * far
-  acc.y = keta * far[0].x + nr[0].y - (CF ? eta_h * fk[0].y : (T)0);
+  acc.x = -keta * far[0].y - (CF ? eta_h * fk[0].x : (T)0);  // j k eta * far
+  acc.y = keta * far[0].x - (CF ? eta_h * fk[0].y : (T)0);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    acc.x += nr[j].x;
+    acc.y += nr[j].y;
+  }
 #pragma unroll
   for (int off = LR; off < 32; off <<= 1) {
     acc.x += __shfl_xor(acc.x, off, 64);
