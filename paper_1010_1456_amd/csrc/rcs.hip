@@ -108,10 +108,20 @@ struct FarMesh {
   const double *len;
   int64_t nt;
   double k;
+  // k / 6 pi and what its rounding leaves: a relative error there turns the phases of
+  // all triangles together
+  double third_hi, third_lo;
 };
 
 __device__ __forceinline__ void load_tri(const FarMesh &fm, int64_t tri, D3 *T) {
   for (int c = 0; c < 3; ++c) T[c] = vtx(fm.verts, fm.tris[3 * tri + c]);
+}
+// (k / 6 pi) (a + b + c), rounded once: rounding the sum would give all triangles of a
+// grid line the same error
+__device__ __forceinline__ double centroid_turns(const FarMesh &fm, double a, double b, double c) {
+  const double s = a + b, u = s - a, e = (a - (s - u)) + (b - u);
+  const double t = s + c, v = t - s, f = (s - (t - v)) + (c - v);
+  return fma(fm.third_hi, t, fma(fm.third_hi, e + f, fm.third_lo * t));
 }
 __device__ __forceinline__ void stage_geometry(const FarMesh &fm, int64_t tri, double *o) {
   D3 c = d3(0, 0, 0), p1 = c, p2 = c;
@@ -119,7 +129,8 @@ __device__ __forceinline__ void stage_geometry(const FarMesh &fm, int64_t tri, d
   if (tri < fm.nt) {
     D3 T[3];
     load_tri(fm, tri, T);
-    c = (fm.k * (0.5 / 3.14159265358979323846 / 3.0)) * (T[0] + T[1] + T[2]);
+    c = d3(centroid_turns(fm, T[0].x, T[1].x, T[2].x), centroid_turns(fm, T[0].y, T[1].y, T[2].y),
+           centroid_turns(fm, T[0].z, T[1].z, T[2].z));
     p1 = fm.k * ((T[1] - T[0]) + (T[1] - T[2]));
     p2 = fm.k * ((T[2] - T[0]) + (T[2] - T[1]));
     const double m = fmax(fmax(dot(p1, p1), dot(p2, p2)), dot(p1 + p2, p1 + p2));
@@ -137,7 +148,10 @@ __device__ __forceinline__ void stage_current(const FarMesh &fm, int64_t tri, co
   if (tri < fm.nt) {
     D3 T[3];
     load_tri(fm, tri, T);
-    const D3 c = (1.0 / 3.0) * (T[0] + T[1] + T[2]);
+    // 3 (c - v_i) from edges, not from c: its rounding is that of the coordinates
+    const D3 e1 = T[1] - T[0], e2 = T[2] - T[0];
+    const D3 d3c[3] = {e1 + e2, e2 - 2.0 * e1, e1 - 2.0 * e2};
+#pragma unroll
     for (int i = 0; i < 3; ++i) {
       const int code = fm.tri_basis[3 * tri + i];
       if (code < 0) continue;
@@ -145,7 +159,7 @@ __device__ __forceinline__ void stage_current(const FarMesh &fm, int64_t tri, co
       // A f_n = (s l / 2) (r - v_i) on this triangle, v_i the free vertex
       const double f = ((code & 1) ? -0.5 : 0.5) * fm.len[n];
       const double2 I = xr[n];
-      const D3 d = c - T[i];
+      const D3 d = d3c[i];
       const double fr = f * I.x, fi = f * I.y;
       cr[0] += d.x * fr, ci[0] += d.x * fi;
       cr[1] += d.y * fr, ci[1] += d.y * fi;
@@ -153,7 +167,7 @@ __device__ __forceinline__ void stage_current(const FarMesh &fm, int64_t tri, co
       gr += fr, gi += fi;
     }
   }
-  for (int q = 0; q < 3; ++q) o[2 * q] = cr[q], o[2 * q + 1] = ci[q];
+  for (int q = 0; q < 3; ++q) o[2 * q] = cr[q] * (1.0 / 3.0), o[2 * q + 1] = ci[q] * (1.0 / 3.0);
   o[6] = gr / fm.k, o[7] = gi / fm.k;
 }
 
@@ -376,7 +390,9 @@ static void rcs_launch(MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int
   const int64_t ndir = (int64_t)ntheta * nphi, groups = (ndir + kDirGroup - 1) / kDirGroup;
   if (groups > INT32_MAX) throw Error(AIM_ERR_ARG, "rcs: too many directions");
   const int64_t per_chunk = (h.nt + nchunk - 1) / nchunk;
-  const FarMesh fm{md.tris, md.verts, md.tri_basis, md.len, h.nt, h.k};
+  const long double third = (long double)h.k / (6.0L * 3.141592653589793238462643383279502884L);
+  const FarMesh fm{md.tris, md.verts, md.tri_basis, md.len, h.nt, h.k,
+                   (double)third, (double)(third - (long double)(double)third)};
   for (int r0 = 0; r0 < nrhs; r0 += 16) {
     const int left = nrhs - r0;
     auto go = [&](auto kern) {

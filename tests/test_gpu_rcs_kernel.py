@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 from oracle import farfield as off
-from oracle.constants import wavenumber
+from oracle.constants import ETA0, wavenumber
 from oracle.rwg import build_rwg
 from workloads import plate_mesh, random_current, sphere_mesh
 
@@ -66,3 +66,54 @@ def test_triangle_sizes(squares_per_lambda):
 def test_displaced_scatterer():
     m = sphere_mesh(0.5, FREQ, nf=5)
     _check(m.verts + np.array([700.0, -600.0, 300.0]), m.tris, FREQ, 1, 9, 7, 1e-11)
+
+
+def _sigma_extended(rwg, verts, k, x, th, ph):
+    """sigma_tt by the 7-point rule of every triangle in extended precision."""
+    L = np.longdouble
+    s15 = np.sqrt(L(15))
+    weights = [L(9) / 40] + [(155 - s15) / 1200] * 3 + [(155 + s15) / 1200] * 3
+    bary = [[L(1) / 3] * 3] + [[1 - 2 * a if c == p else a for c in range(3)]
+                               for a in ((6 - s15) / 21, (6 + s15) / 21) for p in range(3)]
+    V = verts.astype(L)
+    T = V[rwg.tris]
+    area = np.sqrt((np.cross(T[:, 1] - T[:, 0], T[:, 2] - T[:, 0]) ** 2).sum(1)) / 2
+    pts = np.stack([sum(b[c] * T[:, c] for c in range(3)) for b in bary], 1)
+    J = np.zeros(pts.shape, dtype=np.clongdouble)
+    length = np.sqrt(((V[rwg.edge[:, 1]] - V[rwg.edge[:, 0]]) ** 2).sum(1))
+    for s, t, v in ((1, rwg.tplus, rwg.vplus), (-1, rwg.tminus, rwg.vminus)):
+        f = (s * length / (2 * area[t])) * x.astype(np.clongdouble)
+        np.add.at(J, t, f[:, None, None] * (pts[t] - V[v][:, None]))
+    wt = np.array(weights) * area[:, None]
+    scale = (L(k) * L(ETA0)) ** 2 / (4 * L("3.14159265358979323846264338327950288"))
+    out = np.empty((len(th), len(ph)), dtype=L)
+    for i, a in enumerate(th.astype(L)):
+        for j, b in enumerate(ph.astype(L)):
+            rh = np.array([np.sin(a) * np.cos(b), np.sin(a) * np.sin(b), np.cos(a)])
+            tt = np.array([np.cos(a) * np.cos(b), np.cos(a) * np.sin(b), -np.sin(a)])
+            p = L(k) * (pts @ rh)
+            out[i, j] = scale * abs(((J @ tt) * wt * (np.cos(p) + 1j * np.sin(p))).sum()) ** 2
+    return out
+
+
+@pytest.mark.parametrize("current", ["random", "wave"])
+def test_rounding_of_the_phases(current):
+    """An 8-lambda plate against extended precision, rms relative to the rms sigma: each
+    phase is rounded a handful of times by up to half an ulp of 4 wavelengths, 2.8e-15
+    radians, alike along a grid line (72 lines): 2 x 2.8e-15 x sqrt(3 / 72) = 1.2e-15.
+    (A rounded k / 6 pi, the sum of the corners rounded before it and the edge vectors
+    taken from the centroid gave 2.2e-15 and 5.5e-15.)"""
+    from paper_1010_1456_amd import aim as A
+
+    m = plate_mesh(8.0, FREQ)
+    rwg = build_rwg(m.verts, m.tris)
+    k = wavenumber(FREQ)
+    x = (random_current(rwg.n, nrhs=1, seed=3)[0] if current == "random"
+         else np.exp(1j * k * rwg.centre[:, 0]))
+    th, ph = np.linspace(0.1, 3.0, 7), np.linspace(0.0, 6.0, 6)
+    ref = _sigma_extended(rwg, m.verts, k, x, th, ph)
+    plan = A.Plan([(m.verts, m.tris, FREQ)], mixed=False)
+    got = plan.rcs(torch.from_numpy(x).cuda()[None], th, ph)[0, 0]
+    plan.close()
+    err = np.sqrt(((got.astype(np.longdouble) - ref) ** 2).sum() / (ref**2).sum())
+    assert err <= 1.2e-15
