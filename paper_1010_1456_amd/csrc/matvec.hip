@@ -222,10 +222,11 @@ __global__ void __launch_bounds__(256)
                   cx<TY> *__restrict__ y, int64_t ldy, int64_t n, T keta, T inv_k2, T eta_h) {
   using V = cx<T>;
   constexpr int NU = kNearUnroll * kRowLanes / LANES, SU = kStencilUnroll;
-  // near sums per lane: in float two with 16 lanes, so that they are as short as with
-  // 32 (8-lambda sphere, error against FP64: one 1.043e-7, two 0.994e-7, 32 lanes
-  // 1.025e-7; the same registers and time)
-  constexpr int NS = sizeof(T) == 4 ? 32 / LANES : 1;
+  // near sums per lane: two with 16 lanes, so that they are as short as with 32
+  // (8-lambda sphere in c64, error against FP64: one 1.043e-7, two 0.994e-7, 32 lanes
+  // 1.025e-7; this kernel alone in FP64 on the 1-lambda sphere: 1.60e-16, 1.50e-16 and
+  // 1.52e-16; the same registers and time)
+  constexpr int NS = 32 / LANES;
   const int lane = threadIdx.x & (LANES - 1);
   const int64_t m = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   if (m >= n) return;  // whole rows exit

@@ -25,17 +25,23 @@ namespace {
 
 constexpr int kMultiThreads = 256;
 constexpr int kMultiRows = kMultiThreads / 32;  // nodes (rows) per work-group
-// Partial sums per lane of the near product (half as many for the stencil and the
-// projection), added in pairs, the last two to the far part. In float 16 per row, of
-// some 5 entries each: with 8 the product's error against FP64 is 1.04e-7 on the
-// 2-lambda sphere (16 right-hand sides) where 32 lanes per row, one right-hand side at
-// a time, have 0.978e-7; with 16 it is 0.930e-7 (0.977e-7 where the near sum is
-// complete before it meets the far part, which it partly cancels), and the
-// interpolation takes 114 us on the 4-lambda sphere (8: 117; 16 also for the stencil:
-// 150). In FP64 four per lane.
-template <typename T, int SEG>
+// Partial sums per lane: of the near product 16 per row, of some 5 entries each, added
+// in pairs, the last two to the far part. With 8 in float the product's error against
+// FP64 is 1.04e-7 on the 2-lambda sphere (16 right-hand sides) where 32 lanes per row,
+// one right-hand side at a time, have 0.978e-7; with 16 it is 0.930e-7 (0.977e-7 where
+// the near sum is complete before it meets the far part, which it partly cancels), and
+// the interpolation takes 114 us on the 4-lambda sphere (8: 117). FP64, 8 and 16 and
+// those 32 lanes: 1.66e-16, 1.53e-16 and 1.56e-16 (1-lambda sphere, this kernel alone),
+// 203 and 201 us.
+template <int SEG>
 constexpr int near_sums() {
-  return sizeof(T) == 4 ? 16 / SEG : 4;
+  return 16 / SEG;
+}
+// of the stencil and the projection (float 8 per row; with 16 the interpolation takes
+// 150 us there, in FP64 with 8 271)
+template <typename T, int SEG>
+constexpr int stencil_sums() {
+  return sizeof(T) == 4 ? 8 / SEG : 2;
 }
 
 // xt[i R + r] = x[r ldx + i]
@@ -84,7 +90,7 @@ __global__ void __launch_bounds__(kMultiThreads)
   const int b0 = occ_ptr[v0], b1 = occ_ptr[vend];
   const int rr = blockIdx.y * LR + r;
   const cx<T> *xr = xt + (rr < R ? rr : R - 1);
-  constexpr int NS = near_sums<T, SEG>() / 2;
+  constexpr int NS = stencil_sums<T, SEG>();
   T a[NS][4][2];
 #pragma unroll
   for (int j = 0; j < NS; ++j)
@@ -182,7 +188,7 @@ __global__ void __launch_bounds__(kMultiThreads)
   const int rr = blockIdx.y * LR + r, rc = rr < R ? rr : R - 1;
   const int e0 = rowptr[m], e1 = rowptr[m + 1], b0 = rowptr[m0], b1 = rowptr[mend];
   const V *ph = phi + ((int64_t)anchor_lin[m] * R + rc) * 4;
-  constexpr int NN = near_sums<T, SEG>(), NF = NN / 2;  // far and near sums per lane
+  constexpr int NN = near_sums<SEG>(), NF = stencil_sums<T, SEG>();  // far and near sums per lane
   V far[NF], fk[NF], nr[NN];
 #pragma unroll
   for (int j = 0; j < NF; ++j) far[j].x = far[j].y = fk[j].x = fk[j].y = 0;
