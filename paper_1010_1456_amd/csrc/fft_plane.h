@@ -16,7 +16,7 @@
 // of the three passes on a 4.6-lambda sphere), P <= 126 for c128.
 //
 // Bound by the vector ALU and LDS together (4-lambda sphere with 16 right-hand sides
-// in c64: 65% and 50% of the time, measured), with 12 to 20 waves per CU to overlap
+// in c64: 82% and 50% of the time, measured), with 12 to 20 waves per CU to overlap
 // them. The three passes against this one: that sphere 1256 -> 831 us (c64, P = 162);
 // 2-lambda sphere with 16 right-hand sides 171 -> 93 us (c64, P = 81); 2.7-lambda
 // sphere of third order with three 183 -> 166 us (c128, P = 126).
