@@ -495,15 +495,39 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
   return work[which];
 }
 
+// Few rows: the time is one wave's chain, so from 5 right-hand sides on each takes rows
+// (waves) of its own, all in one launch, projected by the gather (product, us, groups of 4
+// and a launch for those left over or a lane each -> a row each; 225 rows, planar, second
+// order, c64: 5 right-hand sides 15.7 -> 12.0, 9 18.5 -> 12.1; fifth order in FP64: 5 58 ->
+// 43, 17 122 -> 55; CFIE spheres: 1 080 rows, third order in FP64, 17 76 -> 51; 1 920
+// rows, fifth order, c64, 9 103 -> 78). Of more rows the gathers' traffic is what counts
+// (2 133 rows, planar, fifth order in FP64: 8 87 -> 114; 3 630 rows, fourth order, c64: 5
+// 53 -> 59), and so it is of many right-hand sides (936 rows, planar, fifth order in FP64:
+// 24 105 -> 132, 64 168 -> 292), later where nodes with long lists are few, which half a
+// wave each sums slowly (1 080 rows, sphere, c64: fifth order, 175 entries per node, 33
+// 205 -> 128; fourth, 102 per node, 33 89 -> 76, 64 101 -> 122).
+constexpr int64_t kLoneRows = 2048;                      // n
+constexpr int64_t kLoneWork = 20480, kLoneLong = 36864;  // n nrhs
+constexpr int64_t kLongList = 96;                        // entries per node
+static bool lone_rows(const MeshDev &md, int nrhs) {
+  const int64_t n = md.hp.n;
+  const bool plane = md.planar_z >= 0;
+  const int64_t nodes = plane ? md.n_plane_occ : md.n_occ;
+  const bool longer = n * (plane ? md.plane_K : md.hp.K) >= kLongList * nodes;
+  return nrhs > 4 && n <= kLoneRows && n * nrhs <= (longer ? kLoneLong : kLoneWork);
+}
+
 // Lanes per node (row) of the several-right-hand-sides kernels (multi_rhs.h), 0:
-// the others. From 6 on they are faster on nearly every mesh measured (projection and
+// the others. From 6 on they are faster on nearly every mesh of more rows (projection and
 // interpolation together, 4-lambda CFIE sphere, the others -> these: 4 right-hand sides
 // 82 -> 109 us in c64 and 154 -> 178 in FP64, 5 106 -> 111 and 191 -> 182; 16-lambda
 // plate: 4 45 -> 56 and 74 -> 74, 5 58 -> 56 and 94 -> 75; 8 and 16 on that sphere take
 // 118 and 185, and 200 and 290, where four per launch row took 149 and 276, and 354 and
 // 671)
 constexpr int kMultiFrom = 6;
-static int multi_lanes(int nrhs) { return nrhs < kMultiFrom ? 0 : (nrhs <= 8 ? 8 : 16); }
+static int multi_lanes(const MeshDev &md, int nrhs) {
+  return nrhs < kMultiFrom || lone_rows(md, nrhs) ? 0 : (nrhs <= 8 ? 8 : 16);
+}
 
 // x of one mesh transposed to [n][nrhs] in T
 template <typename T, typename TX>
@@ -526,7 +550,7 @@ static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int6
                     const int32_t *occ_ptr, const int32_t *occ, int64_t n_occ, cx<T> *grid,
                     int64_t Vg, hipStream_t s) {
   const int npw = md.gather_npw[sizeof(T) == 8 ? 0 : 1];
-  const int LR = multi_lanes(nrhs);
+  const int LR = multi_lanes(md, nrhs);
   if (LR > 0) {
     const cx<T> *xt = transposed_x<T, TX>(pl, md, nrhs, x, ldx, true, s);
     auto go = [&](auto kern) {
@@ -617,7 +641,7 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     return touched ? (cx<T> *)work_buffer(pl, md.lane, prec, which, sizeof(cx<T>) * F * count, s)
                    : nullptr;
   };
-  if (reserve && multi_lanes(nrhs) > 0) (void)transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);
+  if (reserve && multi_lanes(md, nrhs) > 0) (void)transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);
   if (md.planar_z >= 0 && !full3d) {
     // every source on the plane z = planar_z, and only that plane weighted by
     // the interpolation: the plane alone, g0 = [F][Nx][Ny], 2-D propagation
@@ -857,7 +881,6 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
   const int64_t nf = 4 * (int64_t)nrhs;  // fields per node of the interleaved grid
   const bool cf = h.cfie;
   if (cf && (plane || !curl_of<T>(md))) throw Error(AIM_ERR_STATE, "combined field without curl weights");
-  // right-hand sides in groups of 4, then the 1 to 3 left over in one group
   auto launch = [&](auto kern, int r_first, int groups, int lanes = kRowLanes) {
     hipLaunchKernelGGL(kern, dim3(launch_blocks(h.n, 256 / lanes), groups), dim3(256), 0, s, phi, nf, r_first,
                        plane ? plane_lam_of<T>(md) : lam_of<T>(md), cf ? curl_of<T>(md) : nullptr,
@@ -867,6 +890,7 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
                        (T)(h.alpha * h.k * kEta0), (T)(1.0 / (h.k * h.k)),
                        (T)((1.0 - h.alpha) * kEta0));
   };
+  // right-hand sides in groups of 4, then the 1 to 3 left over in one group
   auto groups = [&](auto cf_) {
     constexpr bool CF = decltype(cf_)::value;
     const int left = nrhs % 4, r_left = nrhs - left;
@@ -895,11 +919,13 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
                        (T)(1.0 / (h.k * h.k)), (T)((1.0 - h.alpha) * kEta0));
   };
   auto all = [&](auto cf_) {
-    const int LR = multi_lanes(nrhs);
+    const int LR = multi_lanes(md, nrhs);
     if (LR == 16)
       multi(cf_, std::integral_constant<int, 16>{});
     else if (LR == 8)
       multi(cf_, std::integral_constant<int, 8>{});
+    else if (lone_rows(md, nrhs))
+      launch(k_interp_near<T, TX, TY, 1, decltype(cf_)::value>, 0, nrhs);
     else
       groups(cf_);
   };
@@ -1080,7 +1106,7 @@ void autotune_mesh(Plan *pl, MeshDev &md, hipStream_t s) {
       return ms;
     };
     // projection gather: occupied nodes per wave, with the most right-hand sides it
-    // takes if nr are more (k_anterp_multi has no such variants)
+    // takes on any number of rows if nr are more (k_anterp_multi has no such variants)
     for (int prec = 0; prec < 2; ++prec) {
       if (prec == 1 && !pl->mixed) break;
       float best = 0;

@@ -115,3 +115,69 @@ def test_double_sums_stay_short(nrhs):
         err += (np.abs(y[r] - ref) ** 2).sum()
         norm += (np.abs(ref) ** 2).sum()
     assert np.sqrt(err / norm) <= 1.575e-16
+
+
+@functools.lru_cache(maxsize=None)
+def _larger(shape, order):
+    from paper_1010_1456_amd import aim as A
+
+    if shape == "sphere":  # 3 630 rows, no multiple of 8
+        m, kw = sphere_mesh(1.0, FREQ, nf=11), {"cfie_alpha": 0.6}
+    else:
+        m, kw = plate_mesh(4.0, FREQ), {}  # 3 816 rows, planar
+    return A.Plan([(m.verts, m.tris, FREQ)], order=order, near_radius_lambda=0.5, tune_rhs=17, **kw)
+
+
+@pytest.mark.parametrize("nrhs", [6, 8, 9, 16, 17])
+@pytest.mark.parametrize("shape,order", [("sphere", 1), ("sphere", 3), ("sphere", 5), ("plate", 2)])
+def test_a_lane_each(shape, order, nrhs):
+    """A lane per right-hand side, on meshes with rows enough for it, near rows and
+    stencils in several stages: each product that of the right-hand side alone, with
+    buffers that set-up left."""
+    from paper_1010_1456_amd import aim as A
+
+    plan = _larger(shape, order)
+    held = plan.info()["device_bytes"]
+    x = torch.from_numpy(random_current(plan.n_total, nrhs=nrhs, seed=nrhs)).cuda()
+    for prec, dtype, tol in ((A.AIM_FP64, torch.complex128, 1e-12), (A.AIM_MIXED, torch.complex64, 2e-5)):
+        xs = x.to(dtype)
+        y = plan.matvec(xs, prec)
+        assert plan.info()["device_bytes"] == held
+        for r in range(nrhs):
+            one = plan.matvec(xs[r], prec)
+            assert torch.linalg.norm(y[r] - one) <= tol * torch.linalg.norm(one), r
+
+
+@pytest.mark.parametrize("make,nrhs,multi,launches", [
+    (lambda: plate_mesh(1.0, FREQ), 4, 0, 1),
+    (lambda: plate_mesh(1.0, FREQ), 5, 0, 1),
+    (lambda: plate_mesh(1.0, FREQ), 17, 0, 1),
+    (lambda: plate_mesh(2.0, FREQ), 21, 0, 1),
+    (lambda: plate_mesh(2.0, FREQ), 22, 1, 0),
+    (lambda: plate_mesh(3.0, FREQ), 6, 1, 0),
+    (lambda: sphere_mesh(0.5, FREQ, nf=6), 34, 0, 1),
+    (lambda: sphere_mesh(0.5, FREQ, nf=6), 35, 1, 0),
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 5, 0, 2),
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 6, 1, 0),
+])
+def test_route(make, nrhs, multi, launches):
+    """Few rows: a row (and a place in one launch) for each of 5 or more right-hand
+    sides, up to 20 480 rows together, or 36 864 of long lists per node (936 rows, and
+    1 080 at fifth order); else groups of 4, from 6 on a lane each."""
+    from torch.profiler import ProfilerActivity, profile
+
+    from paper_1010_1456_amd import aim as A
+
+    m = make()
+    plan = A.Plan([(m.verts, m.tris, FREQ)], order=5 if nrhs > 30 else 3)
+    x = torch.from_numpy(random_current(plan.n_total, nrhs=nrhs, seed=nrhs)).cuda()
+    ref = plan.matvec(x[nrhs - 1], A.AIM_FP64)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        y = plan.matvec(x, A.AIM_FP64)
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events()]
+    assert sum("k_interp_multi<" in s for s in names) == multi
+    assert sum("k_anterp_multi<" in s for s in names) == multi
+    assert sum("k_interp_near<" in s for s in names) == launches
+    assert torch.linalg.norm(y[nrhs - 1] - ref) <= 1e-12 * torch.linalg.norm(ref)
+    plan.close()
