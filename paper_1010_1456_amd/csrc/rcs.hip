@@ -172,7 +172,7 @@ __device__ __forceinline__ void stage_current(const FarMesh &fm, int64_t tri, co
 }
 
 // part[(r ndir + d) nchunk + blockIdx.y] = theta_hat . N of the chunk's
-// triangles, r = r0 .. r0 + RB - 1 (those below nrhs).
+// triangles, r = RB blockIdx.z + r0 .. + RB - 1 (those below nrhs).
 //
 // Bound by FP64 issue: 114 + 14 RB multiply-adds per triangle and direction. A
 // lane owns kDirs directions (their unit vectors and sums stay in registers), a
@@ -197,6 +197,7 @@ __global__ void __launch_bounds__(64 * kRcsWaves, RB <= 4 ? 4 : (RB <= 8 ? 3 : 2
     k_rcs_part(FarMesh fm, const double2 *__restrict__ x, int64_t ldx, int r0, int nrhs,
                int64_t per_chunk, const double *__restrict__ theta, int ntheta,
                const double *__restrict__ phi, int nphi, int nchunk, double2 *__restrict__ part) {
+  r0 += RB * blockIdx.z;
   constexpr int TB = rcs_batch<RB>(), REC = kTriGeom + kTriRhs * RB;
   constexpr int kRed = 2 * kRcsWaves * kDirGroup;  // the final sums' exchange
   __shared__ __align__(16) double lds[TB * REC > kRed ? TB * REC : kRed];
@@ -317,18 +318,26 @@ __global__ void __launch_bounds__(64 * kRcsWaves, RB <= 4 ? 4 : (RB <= 8 ? 3 : 2
   }
 }
 
-// sigma[rr ndir + d] = scale |sum over chunks of part|^2 (chunks in order)
-__global__ void k_rcs_reduce(const double2 *part, int nchunk, int64_t count, double scale,
-                             double *sigma) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= count) return;
-  double a = 0, b = 0;
-  for (int c = 0; c < nchunk; ++c) {
-    const double2 v = part[t * nchunk + c];
-    a += v.x;
-    b += v.y;
+// sigma[rr ndir + d] = scale |sum over chunks of part|^2: `lanes` (a power of two up to
+// 64) lanes per slot take every lanes-th chunk and add their sums by exchanges
+__global__ void __launch_bounds__(256)
+    k_rcs_reduce(const double2 *part, int nchunk, int64_t count, int lanes, double scale,
+                 double *sigma) {
+  const int lane = threadIdx.x & (lanes - 1);
+  const int64_t step = (int64_t)gridDim.x * (256 / lanes);
+  for (int64_t t = (int64_t)blockIdx.x * (256 / lanes) + threadIdx.x / lanes; t < count; t += step) {
+    double a = 0, b = 0;
+    for (int c = lane; c < nchunk; c += lanes) {
+      const double2 v = part[t * nchunk + c];
+      a += v.x;
+      b += v.y;
+    }
+    for (int off = 1; off < lanes; off <<= 1) {
+      a += __shfl_xor(a, off, 64);
+      b += __shfl_xor(b, off, 64);
+    }
+    if (lane == 0) sigma[t] = scale * (a * a + b * b);
   }
-  sigma[t] = scale * (a * a + b * b);
 }
 
 }  // namespace
@@ -368,54 +377,78 @@ void *rcs_scratch_ptr(int device) {
   return g_scratch_ptr[device];
 }
 
-// Triangle chunks of the part kernel: enough work-groups for several rounds of
-// the chip (kRcsGroups), chunks of at least two batches, and at most `most`
-// partial sums per direction and right-hand side.
-constexpr int64_t kRcsGroups = 4096;
-static int64_t rcs_chunks(int64_t nt, int64_t ndir, int nrhs, int64_t most) {
-  const int64_t groups = (ndir + kDirGroup - 1) / kDirGroup * ((nrhs + 15) / 16);
-  int64_t n = std::min((kRcsGroups + groups - 1) / groups, (nt + 127) / 128);
-  n = std::min<int64_t>(std::min(n, most), 65535);
-  return std::max<int64_t>(n, 1);
+// How the part kernel's work is split: triangle chunks, at most `most` (partial sums
+// per direction and right-hand side), and right-hand sides per work-group. Many
+// directions: chunks of at least two batches, for several rounds of the chip
+// (kRcsGroups). Where those are fewer than kRcsFew work-groups the time is one
+// work-group's chain: chunks down to kRcsLeast triangles, and right-hand sides in
+// smaller groups until there are kRcsSplit (1 direction, 1, 9 and 17 right-hand sides,
+// us: 162 triangles 28, 62 and 89 -> 13, 13 and 13; 16 820 triangles 48, 105 and 144 ->
+// 26, 55 and 70; 324 directions there 83, 163 and 223 -> 45, 122 and 170; kRcsSplit
+// 1024: 17 right-hand sides and 324 directions on those 200; 8-lambda plate, 1 369
+// directions: 2 right-hand sides 94 -> 157 with it). The sums of many chunks are then
+// added by a wave per slot (a lane each took 20 us there for 600 chunks).
+constexpr int64_t kRcsGroups = 4096, kRcsFew = 1024, kRcsSplit = 512, kRcsLeast = 16;
+struct RcsSplit {
+  int64_t nchunk;
+  int rb;
+};
+static RcsSplit rcs_split(int64_t nt, int64_t ndir, int nrhs, int64_t most) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t dirs = up(ndir, kDirGroup), groups = dirs * up(nrhs, 16);
+  int64_t n = std::min(up(kRcsGroups, groups), up(nt, 128));
+  int rb = 16;
+  if (groups * n < kRcsFew) {
+    n = std::min(std::max<int64_t>(kRcsFew / groups, 1), up(nt, kRcsLeast));
+    while (rb > 1 && dirs * n * up(nrhs, rb) < kRcsSplit) rb /= 2;
+  }
+  n = std::max<int64_t>(std::min({n, most, (int64_t)65535}), 1);
+  return {n, rb};
 }
 
-// Partial sums of nchunk chunks into part, then sigma (all device memory). 16
-// right-hand sides share a launch; the rest takes the smallest kernel that
-// holds them (one with an unused right-hand side or three costs 14 multiply-adds
-// each, a second launch 114).
+// Partial sums into part, then sigma (all device memory). Of 16 right-hand sides per
+// work-group, the rest takes the smallest kernel that holds them (one with an unused
+// right-hand side or three costs 14 multiply-adds each, a second launch 114).
 static void rcs_launch(MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int ntheta,
                        const double *theta, int nphi, const double *phi, double *sigma,
-                       double2 *part, int64_t nchunk, hipStream_t s) {
+                       double2 *part, RcsSplit split, hipStream_t s) {
   const HostPlan &h = md.hp;
+  const int64_t nchunk = split.nchunk;
   const int64_t ndir = (int64_t)ntheta * nphi, groups = (ndir + kDirGroup - 1) / kDirGroup;
   if (groups > INT32_MAX) throw Error(AIM_ERR_ARG, "rcs: too many directions");
   const int64_t per_chunk = (h.nt + nchunk - 1) / nchunk;
   const long double third = (long double)h.k / (6.0L * 3.141592653589793238462643383279502884L);
   const FarMesh fm{md.tris, md.verts, md.tri_basis, md.len, h.nt, h.k,
                    (double)third, (double)(third - (long double)(double)third)};
-  for (int r0 = 0; r0 < nrhs; r0 += 16) {
+  constexpr int kMostZ = 32768;
+  for (int r0 = 0; r0 < nrhs;) {
     const int left = nrhs - r0;
-    auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)nchunk), dim3(64 * kRcsWaves), 0,
-                         s, fm, x, ldx, r0, nrhs, per_chunk, theta, ntheta, phi, nphi, (int)nchunk,
-                         part);
+    auto go = [&](auto kern, int rb, int z) {
+      z = std::min(z, kMostZ);
+      hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)nchunk, z), dim3(64 * kRcsWaves),
+                         0, s, fm, x, ldx, r0, nrhs, per_chunk, theta, ntheta, phi, nphi,
+                         (int)nchunk, part);
+      r0 += std::min(left, z * rb);
     };
-    if (left == 1)
-      go(k_rcs_part<1>);
-    else if (left == 2)
-      go(k_rcs_part<2>);
-    else if (left <= 4)
-      go(k_rcs_part<4>);
-    else if (left <= 8)
-      go(k_rcs_part<8>);
+    const int rb = left < split.rb ? left : split.rb;
+    if (rb == 1)
+      go(k_rcs_part<1>, 1, left);
+    else if (rb == 2)
+      go(k_rcs_part<2>, 2, (left + 1) / 2);
+    else if (rb <= 4)
+      go(k_rcs_part<4>, 4, (left + 3) / 4);
+    else if (rb <= 8)
+      go(k_rcs_part<8>, 8, (left + 7) / 8);
     else
-      go(k_rcs_part<16>);
+      go(k_rcs_part<16>, 16, std::max(left / 16, 1));
     LAUNCHCHECK();
   }
   const double keta = h.k * kEta0;
   const int64_t slots = ndir * nrhs;
-  hipLaunchKernelGGL(k_rcs_reduce, dim3((unsigned)((slots + 255) / 256)), dim3(256), 0, s, part,
-                     (int)nchunk, slots, keta * keta / (4.0 * kPi), sigma);
+  int lanes = 1;
+  while (lanes < 64 && lanes < nchunk) lanes *= 2;
+  hipLaunchKernelGGL(k_rcs_reduce, dim3(loop_blocks(slots * lanes, 256)), dim3(256), 0, s, part,
+                     (int)nchunk, slots, lanes, keta * keta / (4.0 * kPi), sigma);
   LAUNCHCHECK();
 }
 
@@ -434,9 +467,9 @@ void rcs_mesh(Plan *pl, MeshDev &md, int nrhs, const double2 *x, int64_t ldx, in
     double *dsig = (double *)alloc(sizeof(double) * ndir * nrhs);
     HIPCHECK(hipMemcpyAsync(dth, theta, sizeof(double) * ntheta, hipMemcpyHostToDevice, s));
     HIPCHECK(hipMemcpyAsync(dph, phi, sizeof(double) * nphi, hipMemcpyHostToDevice, s));
-    const int64_t nchunk = rcs_chunks(md.hp.nt, ndir, nrhs, INT32_MAX);
-    double2 *part = (double2 *)alloc(sizeof(double2) * (size_t)ndir * nrhs * nchunk);
-    rcs_launch(md, nrhs, x, ldx, ntheta, dth, nphi, dph, dsig, part, nchunk, s);
+    const RcsSplit split = rcs_split(md.hp.nt, ndir, nrhs, INT32_MAX);
+    double2 *part = (double2 *)alloc(sizeof(double2) * (size_t)ndir * nrhs * split.nchunk);
+    rcs_launch(md, nrhs, x, ldx, ntheta, dth, nphi, dph, dsig, part, split, s);
     HIPCHECK(hipMemcpyAsync(sigma, dsig, sizeof(double) * ndir * nrhs, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
   } catch (...) {
@@ -456,8 +489,8 @@ void rcs_mesh_noalloc(MeshDev &md, int nrhs, const double2 *x, int64_t ldx, int 
                                  " exceeds its fixed scratch of " +
                                  std::to_string(kRcsScratchElems) + " partial sums");
   // as many chunks as aim_rcs uses, fewer if the scratch cannot hold them
-  const int64_t nchunk = rcs_chunks(md.hp.nt, ndir, nrhs, kRcsScratchElems / slots);
-  rcs_launch(md, nrhs, x, ldx, ntheta, theta, nphi, phi, sigma, part, nchunk, s);
+  rcs_launch(md, nrhs, x, ldx, ntheta, theta, nphi, phi, sigma, part,
+             rcs_split(md.hp.nt, ndir, nrhs, kRcsScratchElems / slots), s);
 }
 
 }  // namespace aim

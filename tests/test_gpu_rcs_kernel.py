@@ -117,3 +117,33 @@ def test_rounding_of_the_phases(current):
     plan.close()
     err = np.sqrt(((got.astype(np.longdouble) - ref) ** 2).sum() / (ref**2).sum())
     assert err <= 1.2e-15
+
+
+@pytest.mark.parametrize("ntheta,nphi,nrhs,wide", [
+    (1, 1, 17, 1), (2, 128, 16, 2), (4, 128, 16, 4), (8, 128, 5, 4), (8, 128, 9, 8),
+    (8, 128, 17, 16), (91, 180, 17, 16)])
+def test_work_split(ntheta, nphi, nrhs, wide):
+    """Few directions are summed in shorter chunks and, if that gives too few
+    work-groups, with fewer right-hand sides in each: every width, also where the
+    scratch of the interface without allocation limits the chunks."""
+    from torch.profiler import ProfilerActivity, profile
+
+    from paper_1010_1456_amd import aim as A
+
+    m = plate_mesh(2.0, FREQ, jitter_seed=5)  # 648 triangles
+    rwg = build_rwg(m.verts, m.tris)
+    plan = A.Plan([(m.verts, m.tris, FREQ)], mixed=False)
+    x = random_current(rwg.n, nrhs=nrhs, seed=nrhs)
+    th = np.linspace(0.1, math.pi - 0.1, ntheta)
+    ph = np.linspace(0.0, 2.0 * math.pi, nphi, endpoint=False) + 0.1
+    xt, dth, dph = (torch.from_numpy(v).cuda() for v in (x, th, ph))
+    got = [plan.rcs(xt, th, ph)[0]]
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        got.append(plan.rcs_noalloc(xt, dth, dph)[0].cpu().numpy())
+    assert any(f"k_rcs_part<{wide}>" in e.name for e in prof.events())
+    rows = [0, ntheta // 2, ntheta - 1]
+    for r in (0, nrhs // 2, nrhs - 1):
+        ref = off.sigma_tt(rwg, wavenumber(FREQ), x[r], th[rows], ph)
+        for g in got:
+            assert np.abs(g[r][rows] - ref).max() <= 1e-12 * np.abs(g[r]).max(), r
+    plan.close()
