@@ -201,11 +201,12 @@ __device__ __forceinline__ V row_sum(V v) {
 constexpr int kRowLanes = 16;
 constexpr int kNearUnroll = 6;
 constexpr int kStencilUnroll = 2;
-// 32 lanes per row, a half and the same number of these, where higher orders
-// (64 nodes and more) meet fewer rows than 16 lanes each fill the chip with: the
+// 32 lanes per row, a half and the same number of these, where the fields of a volume
+// (a plane's 9 nodes need none) meet fewer rows than 16 lanes each fill the chip with: the
 // time is then one wave's chain (third order, 1-lambda sphere, 3 630 rows, c64:
-// 7.9 -> 6.8 us; 25 230 rows: 16 lanes are faster)
-constexpr int64_t kFewRows = 8192;
+// 7.9 -> 6.8 us; 25 230 rows: 16 lanes are faster; product of second order, 1 080 rows,
+// c64 19.4 -> 18.6, FP64 20.3 -> 19.4, 3 630 rows 20.7 -> 19.9 and 23.4 -> 23.0)
+constexpr int64_t kFewRows = 8192, kFewRowsLow = 4096;  // of 64 nodes and more, of fewer
 
 // RB right-hand sides from r_first + RB blockIdx.y: the stencil weights, the
 // near-zone entries and their columns are loaded once for the RB products.
@@ -495,26 +496,36 @@ void *work_buffer(Plan *pl, int lane, int prec, int which, size_t bytes, hipStre
   return work[which];
 }
 
-// Few rows: the time is one wave's chain, so from 5 right-hand sides on each takes rows
-// (waves) of its own, all in one launch, projected by the gather (product, us, groups of 4
-// and a launch for those left over or a lane each -> a row each; 225 rows, planar, second
-// order, c64: 5 right-hand sides 15.7 -> 12.0, 9 18.5 -> 12.1; fifth order in FP64: 5 58 ->
-// 43, 17 122 -> 55; CFIE spheres: 1 080 rows, third order in FP64, 17 76 -> 51; 1 920
-// rows, fifth order, c64, 9 103 -> 78). Of more rows the gathers' traffic is what counts
-// (2 133 rows, planar, fifth order in FP64: 8 87 -> 114; 3 630 rows, fourth order, c64: 5
-// 53 -> 59), and so it is of many right-hand sides (936 rows, planar, fifth order in FP64:
-// 24 105 -> 132, 64 168 -> 292), later where nodes with long lists are few, which half a
+// Few rows: the time is one wave's chain, so each of several right-hand sides, or each two
+// of an even number with 32 lanes (936 rows, third order, c64, 8: 38 us alone, 33 in
+// twos), takes rows (waves) of its own, all in one launch, projected by the gather
+// (product, us, groups of 4 and a launch for those left over or a lane each -> rows each;
+// 225 rows, planar, second order, c64: 5 right-hand sides 15.7 -> 12.0, 9 18.5 -> 12.1;
+// fifth order in FP64: 3 35 -> 30, 5 58 -> 43, 17 122 -> 55; CFIE spheres: 1 080 rows,
+// third order in FP64, 17 76 -> 51; 2 430 rows, second order in FP64, 5 37 -> 32). Of more
+// rows the gathers' traffic is what counts (3 630 rows, fourth order, c64: 5 53 -> 59), from 2 048 with stencils of 64
+// nodes and more (2 133 rows, planar, fifth order in FP64: 8 87 -> 114), and so it is of
+// many right-hand sides (936 rows, planar, fifth order in FP64: 24 105 -> 132, 64 168 ->
+// 292; second order 64 31 -> 34), later where nodes with long lists are few, which half a
 // wave each sums slowly (1 080 rows, sphere, c64: fifth order, 175 entries per node, 33
-// 205 -> 128; fourth, 102 per node, 33 89 -> 76, 64 101 -> 122).
-constexpr int64_t kLoneRows = 2048;                      // n
-constexpr int64_t kLoneWork = 20480, kLoneLong = 36864;  // n nrhs
-constexpr int64_t kLongList = 96;                        // entries per node
+// 205 -> 128; fourth, 102 per node, 33 89 -> 76, 64 101 -> 122). 3 and 4 right-hand sides
+// share what they load, which wins earlier (2 133 rows, second order in FP64, 4 equal;
+// fourth 26 -> 28).
+constexpr int64_t kLoneRows = 2560;       // n
+constexpr int64_t kLoneRowsHigh = 2048;   // n, with kLoneHigh nodes per stencil and more
+constexpr int kLoneHigh = 28;
+constexpr int64_t kLoneFew = 6144, kLoneWork = 28672;       // n nrhs, up to 4; more
+constexpr int64_t kLoneHighWork = 20480, kLoneLong = 36864;  // with those stencils
+constexpr int64_t kLongList = 96;         // entries per node
 static bool lone_rows(const MeshDev &md, int nrhs) {
-  const int64_t n = md.hp.n;
+  const int64_t n = md.hp.n, work = n * nrhs;
+  if (nrhs < 3 || n > kLoneRows) return false;
+  if (nrhs <= 4) return work <= kLoneFew;
   const bool plane = md.planar_z >= 0;
-  const int64_t nodes = plane ? md.n_plane_occ : md.n_occ;
-  const bool longer = n * (plane ? md.plane_K : md.hp.K) >= kLongList * nodes;
-  return nrhs > 4 && n <= kLoneRows && n * nrhs <= (longer ? kLoneLong : kLoneWork);
+  const int K = plane ? md.plane_K : md.hp.K;
+  if (K < kLoneHigh || nrhs == 5) return work <= kLoneWork;
+  const bool longer = n * K >= kLongList * (plane ? md.n_plane_occ : md.n_occ);
+  return n <= kLoneRowsHigh && work <= (longer ? kLoneLong : kLoneHighWork);
 }
 
 // Lanes per node (row) of the several-right-hand-sides kernels (multi_rhs.h), 0:
@@ -523,10 +534,18 @@ static bool lone_rows(const MeshDev &md, int nrhs) {
 // 82 -> 109 us in c64 and 154 -> 178 in FP64, 5 106 -> 111 and 191 -> 182; 16-lambda
 // plate: 4 45 -> 56 and 74 -> 74, 5 58 -> 56 and 94 -> 75; 8 and 16 on that sphere take
 // 118 and 185, and 200 and 290, where four per launch row took 149 and 276, and 354 and
-// 671)
+// 671), but not in c64 at low order, where full groups of 4 are on up to 48 K rows together
+// (products of second order, a lane each -> groups: 2 133 rows, planar, 16 right-hand sides
+// 29.6 -> 25.8; 3 816 rows, planar, 8 26.6 -> 22.6; 3 630 rows, sphere, 8 51 -> 48, 16 57 ->
+// 59; 5 070 rows, 12 within 5%)
 constexpr int kMultiFrom = 6;
+constexpr int64_t kGroupWork = 49152;
+template <typename T>
 static int multi_lanes(const MeshDev &md, int nrhs) {
-  return nrhs < kMultiFrom || lone_rows(md, nrhs) ? 0 : (nrhs <= 8 ? 8 : 16);
+  const int K = md.planar_z >= 0 ? md.plane_K : md.hp.K;
+  const bool groups =
+      sizeof(T) == 4 && nrhs % 4 == 0 && K < kLoneHigh && md.hp.n * nrhs <= kGroupWork;
+  return nrhs < kMultiFrom || groups || lone_rows(md, nrhs) ? 0 : (nrhs <= 8 ? 8 : 16);
 }
 
 // x of one mesh transposed to [n][nrhs] in T
@@ -550,7 +569,7 @@ static void project(Plan *pl, const MeshDev &md, int nrhs, const cx<TX> *x, int6
                     const int32_t *occ_ptr, const int32_t *occ, int64_t n_occ, cx<T> *grid,
                     int64_t Vg, hipStream_t s) {
   const int npw = md.gather_npw[sizeof(T) == 8 ? 0 : 1];
-  const int LR = multi_lanes(md, nrhs);
+  const int LR = multi_lanes<T>(md, nrhs);
   if (LR > 0) {
     const cx<T> *xt = transposed_x<T, TX>(pl, md, nrhs, x, ldx, true, s);
     auto go = [&](auto kern) {
@@ -641,7 +660,8 @@ void far_stages(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, i
     return touched ? (cx<T> *)work_buffer(pl, md.lane, prec, which, sizeof(cx<T>) * F * count, s)
                    : nullptr;
   };
-  if (reserve && multi_lanes(md, nrhs) > 0) (void)transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);
+  if (reserve && (multi_lanes<T>(md, nrhs) > 0 || multi_lanes<T>(md, nrhs - 1) > 0))
+    (void)transposed_x<T, TX>(pl, md, nrhs, x, ldx, false, s);  // (for nrhs or fewer)
   if (md.planar_z >= 0 && !full3d) {
     // every source on the plane z = planar_z, and only that plane weighted by
     // the interpolation: the plane alone, g0 = [F][Nx][Ny], 2-D propagation
@@ -899,7 +919,7 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
       launch(k_interp_near<T, TX, TY, 3, CF>, r_left, 1);
     else if (left == 2)
       launch(k_interp_near<T, TX, TY, 2, CF>, r_left, 1);
-    else if (left == 1 && !plane && h.K >= 64 && h.n <= kFewRows)
+    else if (left == 1 && !plane && h.n <= (h.K >= 64 ? kFewRows : kFewRowsLow))
       launch(k_interp_near<T, TX, TY, 1, CF, 32>, r_left, 1, 32);
     else if (left == 1)
       launch(k_interp_near<T, TX, TY, 1, CF>, r_left, 1);
@@ -919,11 +939,13 @@ void matvec_mesh(Plan *pl, MeshDev &md, int nrhs, const cx<TX> *x, int64_t ldx, 
                        (T)(1.0 / (h.k * h.k)), (T)((1.0 - h.alpha) * kEta0));
   };
   auto all = [&](auto cf_) {
-    const int LR = multi_lanes(md, nrhs);
+    const int LR = multi_lanes<T>(md, nrhs);
     if (LR == 16)
       multi(cf_, std::integral_constant<int, 16>{});
     else if (LR == 8)
       multi(cf_, std::integral_constant<int, 8>{});
+    else if (lone_rows(md, nrhs) && nrhs % 2 == 0)
+      launch(k_interp_near<T, TX, TY, 2, decltype(cf_)::value, 32>, 0, nrhs / 2, 32);
     else if (lone_rows(md, nrhs))
       launch(k_interp_near<T, TX, TY, 1, decltype(cf_)::value>, 0, nrhs);
     else

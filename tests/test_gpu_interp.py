@@ -161,7 +161,7 @@ def test_a_lane_each(shape, order, nrhs):
     (lambda: sphere_mesh(1.0, FREQ, nf=11), 6, 1, 0),
 ])
 def test_route(make, nrhs, multi, launches):
-    """Few rows: a row (and a place in one launch) for each of 5 or more right-hand
+    """Few rows: rows (and a place in one launch) for each one or two of 3 or more right-hand
     sides, up to 20 480 rows together, or 36 864 of long lists per node (936 rows, and
     1 080 at fifth order); else groups of 4, from 6 on a lane each."""
     from torch.profiler import ProfilerActivity, profile
@@ -180,4 +180,52 @@ def test_route(make, nrhs, multi, launches):
     assert sum("k_anterp_multi<" in s for s in names) == multi
     assert sum("k_interp_near<" in s for s in names) == launches
     assert torch.linalg.norm(y[nrhs - 1] - ref) <= 1e-12 * torch.linalg.norm(ref)
+    plan.close()
+
+
+@pytest.mark.parametrize("make,nrhs,fp64,kernel", [
+    (lambda: plate_mesh(1.0, FREQ), 2, True, "2, false, 16"),
+    (lambda: plate_mesh(2.0, FREQ), 3, True, "1, false, 16"),
+    (lambda: sphere_mesh(0.7, FREQ, nf=8), 3, False, "1, false, 16"),  # 1 920 rows
+    (lambda: plate_mesh(2.0, FREQ), 4, False, "2, false, 32"),
+    (lambda: sphere_mesh(0.7, FREQ, nf=8), 4, False, "4, false, 16"),
+    (lambda: sphere_mesh(0.85, FREQ, nf=9), 6, True, "2, false, 32"),
+    (lambda: sphere_mesh(0.85, FREQ, nf=9), 11, True, "1, false, 16"),  # 2 430 rows
+    (lambda: sphere_mesh(0.85, FREQ, nf=9), 13, True, "multi"),
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 8, False, "4, false, 16"),  # 3 630 rows
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 12, False, "4, false, 16"),
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 8, True, "multi"),
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 16, False, "multi"),
+    (lambda: sphere_mesh(1.2, FREQ, nf=13), 12, False, "multi"),  # 5 070 rows
+    (lambda: sphere_mesh(1.0, FREQ, nf=11), 1, True, "1, false, 32"),
+    (lambda: plate_mesh(1.0, FREQ), 1, True, "1, false, 16"),
+    (lambda: sphere_mesh(1.2, FREQ, nf=13), 1, True, "1, false, 16"),
+])
+def test_route_second_order(make, nrhs, fp64, kernel):
+    """Second order keeps rows for each one or two up to 2 560 rows (28 672 together, 6 144 of 3 or 4
+    right-hand sides), c64 full groups of 4 up to 49 152 rows together, and one
+    right-hand side 32 lanes per row up to 4 096; set-up leaves the buffers of the route."""
+    from torch.profiler import ProfilerActivity, profile
+
+    from paper_1010_1456_amd import aim as A
+
+    m = make()
+    plan = A.Plan([(m.verts, m.tris, FREQ)], tune_rhs=nrhs)
+    held = plan.info()["device_bytes"]
+    prec = A.AIM_FP64 if fp64 else A.AIM_MIXED
+    x = torch.from_numpy(random_current(plan.n_total, nrhs=nrhs, seed=nrhs)).cuda()
+    x = x if fp64 else x.to(torch.complex64)
+    few = plan.matvec(x[:max(nrhs - 1, 1)], prec)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        y = plan.matvec(x, prec)
+        torch.cuda.synchronize()
+    assert plan.info()["device_bytes"] == held
+    names = [e.name for e in prof.events() if "k_interp_" in e.name]
+    arith = "double, double, double" if fp64 else "float, float, float"
+    want = "k_interp_multi<" if kernel == "multi" else f"k_interp_near<{arith}, {kernel}>"
+    assert len(names) == 1 and want in names[0], names
+    tol = 1e-12 if fp64 else 2e-5
+    assert torch.linalg.norm(y[0] - few[0]) <= tol * torch.linalg.norm(few[0])
+    one = plan.matvec(x[nrhs - 1], prec)
+    assert torch.linalg.norm(y[nrhs - 1] - one) <= tol * torch.linalg.norm(one)
     plan.close()
